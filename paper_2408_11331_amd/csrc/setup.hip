@@ -630,10 +630,19 @@ __global__ __launch_bounds__(kBlock) void k_count_nonzero(const int32_t* __restr
   if (threadIdx.x == 0 && c) atomicAdd(count, c);
 }
 
+// first[x] = the smallest v in [v0, v1) and the ranges before with in[v] = x.
+// Bound by atomics on one address where few ids cover the vertices: only
+// the first lane of a run of equal ids in the wave asks, and the launcher
+// walks the vertices in growing ranges, so that an id that covers a share f
+// of them has mostly been seen before a range of more than 1 / f vertices
+// starts and costs a load there (2 M vertices, 50 ids: 2.6 ms in one range).
 __global__ __launch_bounds__(kBlock) void k_first_occurrence(const int32_t* __restrict__ in,
-                                                             int64_t n, int32_t* __restrict__ first) {
-  for (int64_t v = gtid(); v < n; v += gstride()) {
-    int32_t x = in[v];
+                                                             int64_t v0, int64_t v1,
+                                                             int32_t* __restrict__ first) {
+  for (int64_t v = v0 + gtid(); v < v1; v += gstride()) {
+    const int32_t x = in[v];
+    const int32_t left = __shfl_up(x, 1, 64);
+    if ((threadIdx.x & 63) != 0 && left == x) continue;
     if (__hip_atomic_load(&first[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > v)
       atomicMin(&first[x], (int32_t)v);
   }
@@ -994,7 +1003,11 @@ void launch_count_nonzero(const int32_t* a, int64_t n, int32_t* count, hipStream
 }
 
 void launch_first_occurrence(const int32_t* in, int64_t n, int32_t* first, hipStream_t st) {
-  k_first_occurrence<<<grid_for(n, kBlock, 2048), kBlock, 0, st>>>(in, n, first);
+  // growing ranges (see the kernel); each starts when the one before is done
+  for (int64_t v0 = 0, v1 = 1024; v0 < n; v0 = v1, v1 *= 32) {
+    if (v1 > n || n - v1 < v1) v1 = n;
+    k_first_occurrence<<<grid_for(v1 - v0, kBlock, 2048), kBlock, 0, st>>>(in, v0, v1, first);
+  }
 }
 
 void launch_first_flags(const int32_t* in, int64_t n, const int32_t* first, int32_t* flags,
