@@ -921,6 +921,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
       launch_fill_i32(a.churn, 2 * (int64_t)S.K0, 0, st);
     }
     const int sms = device_sms();
+    a.tile_grid = sms * 8;
     const int64_t blocks_needed =
         lanes ? (n * lanes + kBlock - 1) / kBlock : (n + kBlock - 1) / kBlock;
     const int grid_score = (int)std::max<int64_t>(1, std::min<int64_t>(blocks_needed, sms * 8));

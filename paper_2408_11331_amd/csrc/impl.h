@@ -462,6 +462,8 @@ struct PassArgs {
   // the proposal list; 0: the hashed aggregation (k_apply_all).
   int32_t delta_lds;
   int32_t delta_slices;
+  int32_t tile_grid;    // most workgroups of the tiled scorer
+  int32_t pad4;
 };
 
 constexpr int kDeltaLdsMax = 48 << 10;

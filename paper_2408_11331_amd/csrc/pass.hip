@@ -29,6 +29,8 @@
 // 2 old d + 1; summed over all updates of a pass this telescopes to the
 // exact change of the sum of squares whatever order the atomics land in, so
 // the batch's objective change is exact and deterministic.
+#include <algorithm>
+
 #include "impl.h"
 
 namespace mcc {
@@ -600,7 +602,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
 }
 
 // ---------------------------------------------------------------------------
-// Tiled scorer.  A workgroup owns a tile of kBlock consecutive vertices:
+// Tiled scorer.  A workgroup owns a tile of TV consecutive vertices:
 //  1. the tile's row offsets and clusters go to LDS;
 //  2. its arcs are walked in chunks, every thread taking consecutive arcs
 //     with independent loads; each arc whose head lies in another cluster
@@ -617,48 +619,74 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
 // A vertex whose key finds no slot in the set is deferred to a list that
 // the group scorer finishes in the same pass, so results never depend on
 // the set's capacity.
+//
+// Bound by the latency of the chain arcs -> clusters -> set -> rows -> table
+// lines at 16 waves a compute unit, so the tile is sized to give every unit
+// its four workgroups (launch_tile), and a lane holds ceil(k / 16) labels
+// (NR; 0: any k) of four pairs, of eight where that is two or fewer: the
+// loads in flight, not the arithmetic, set the pace.
 // ---------------------------------------------------------------------------
 constexpr int kArcChunk = 1024;
 constexpr int kSetSlots = 2048;
 constexpr int kSetProbe = 64;
-constexpr int kPairMax = kSetSlots + kBlock;  // every candidate plus one own pair per vertex
 constexpr int kProbeLanes = 16;
-constexpr int kProbeRegs = 64 / kProbeLanes;  // labels per lane when k <= 64
-constexpr int kProbeBatch = 4;
+constexpr int64_t kSmallTileMax = (int64_t)1 << 18;  // vertices scored by tiles of 64
 static_assert(kMemberSumMax <= kProbeLanes, "member ids of a small cluster fit one probe group");
-static_assert(kSetSlots / kBlock == kTileCandAvg, "the tile's key set per vertex");
 
-template <int CN, int TK>
+// Clusters at the heads of a thread's arcs (-1 where the tail is -1): one
+// uniform branch on the width of the narrow copy, all loads of a width in
+// flight together.
+template <int U>
+__device__ inline void tile_clusters(const PassArgs& a, const int (&tl)[U], const int32_t (&hd)[U],
+                                     int32_t (&cu)[U]) {
+  if (a.ac) {  // the per-arc cache: the clusters themselves were streamed
+#pragma unroll
+    for (int r = 0; r < U; ++r) cu[r] = tl[r] >= 0 ? hd[r] : -1;
+  } else if (a.cn_bytes == 1) {
+#pragma unroll
+    for (int r = 0; r < U; ++r) cu[r] = tl[r] >= 0 ? (int32_t)((const uint8_t*)a.Cn)[hd[r]] : -1;
+  } else if (a.cn_bytes == 2) {
+#pragma unroll
+    for (int r = 0; r < U; ++r) cu[r] = tl[r] >= 0 ? (int32_t)((const uint16_t*)a.Cn)[hd[r]] : -1;
+  } else {
+#pragma unroll
+    for (int r = 0; r < U; ++r) cu[r] = tl[r] >= 0 ? ((const int32_t*)a.Cn)[hd[r]] : -1;
+  }
+}
+
+template <int TK, int TV, int NR>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8)))
 void k_score_tile(PassArgs a) {
   if (a.ctl->done) return;
-  __shared__ int32_t s_off[kBlock + 1];
-  __shared__ int32_t s_c[kBlock];
-  __shared__ int32_t s_nc[kBlock];    // candidates of each vertex
-  __shared__ int32_t s_def[kBlock];   // 1: vertex deferred to the group scorer
-  __shared__ int32_t s_cur[kBlock];   // fill cursor of the vertex's run
-  __shared__ int32_t s_clean[kBlock]; // 1: candidate set taken from the cache
+  constexpr int kPairMax = kSetSlots + TV;  // every candidate plus one own pair per vertex
+  constexpr int kProbeRegs = NR > 0 ? NR : 1;       // labels per lane when k <= 16 NR
+  constexpr int kProbeBatch = NR > 2 || NR == 0 || TK == kHashed ? 4 : 8;  // pairs in flight
+  __shared__ int32_t s_off[TV + 1];
+  __shared__ int32_t s_c[TV];
+  __shared__ int32_t s_nc[TV];    // candidates of each vertex
+  __shared__ int32_t s_def[TV];   // 1: vertex deferred to the group scorer
+  __shared__ int32_t s_cur[TV];   // fill cursor of the vertex's run
+  __shared__ int32_t s_clean[TV]; // 1: candidate set taken from the cache
   __shared__ int32_t s_np;            // pairs that fit the pair arrays
   __shared__ int32_t s_set[kSetSlots];
   __shared__ int32_t s_cl[kPairMax];   // pair keys (vertex << 24 | cluster), run per vertex
   __shared__ int32_t s_S[kPairMax];    // agreement sum of each pair
   const int t = threadIdx.x;
   const int32_t k = a.k;
-  const bool kfits = k <= kProbeRegs * kProbeLanes;
   const int g = t / kProbeLanes, lane = t % kProbeLanes;
   int64_t evals = 0;
   int32_t nprop = 0, boundary = 0, wide = 0;
-  const int64_t ntiles = (a.n + kBlock - 1) / kBlock;
+  const int64_t ntiles = (a.n + TV - 1) / TV;
   // passes with few vertices to rescore are left to the list scorer, and
   // passes whose vertices mostly have more candidates than a tile holds to
   // the wave-per-vertex scorer
   if (a.st && a.ctl->rescore_count <= a.sparse_max) return;
   if (a.ctl->defer_all) return;
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int64_t v0 = tile * kBlock;
-    const int nv = (int)min((int64_t)kBlock, a.n - v0);
+    const int64_t v0 = tile * TV;
+    const int nv = (int)min((int64_t)TV, a.n - v0);
     const int32_t cv = t < nv ? a.C[v0 + t] : -1;
-    s_c[t] = cv;
+    if (t < TV) s_c[t] = cv;
     // candidates of a vertex that need not be found again (from the status
     // pass: 0 also for a vertex already settled), -1: walk its arcs
     int32_t cached = -1;
@@ -666,9 +694,11 @@ void k_score_tile(PassArgs a) {
       const int32_t stv = a.st[v0 + t];
       cached = stv < 0 ? 0 : (stv > 0 ? stv : -1);
     }
-    s_clean[t] = cached >= 0;
-    s_nc[t] = cached > 0 ? cached : 0;
-    s_def[t] = 0;
+    if (t < TV) {
+      s_clean[t] = cached >= 0;
+      s_nc[t] = cached > 0 ? cached : 0;
+      s_def[t] = 0;
+    }
     for (int j = t; j < kSetSlots; j += kBlock) s_set[j] = -1;
     // the arcs are walked only when some vertex of the tile needs them
     const int walk = __syncthreads_or(t < nv && cached < 0);
@@ -689,7 +719,7 @@ void k_score_tile(PassArgs a) {
     static_assert(U == 4, "one int4 load per thread and chunk");
     const int32_t sh = a.arcs_aligned ? (int32_t)(a0 & 3) : 0;
     const int64_t base = a0 - sh;
-    const int32_t* src = CN ? a.col : a.ac;  // heads, or the per-arc clusters
+    const int32_t* src = a.ac ? a.ac : a.col;  // heads, or the per-arc clusters
     for (int32_t cb = 0; cb < A + sh; cb += kArcChunk) {
       const int32_t jt = cb + t * U - sh;  // tile-relative index of the thread's first arc
       int32_t hd[U];
@@ -730,8 +760,7 @@ void k_score_tile(PassArgs a) {
         if (!s_clean[lo]) tl[r] = lo;
       }
       int32_t cu[U];
-#pragma unroll
-      for (int r = 0; r < U; ++r) cu[r] = tl[r] >= 0 ? (CN ? cn_load_t<CN>(a, 0, hd[r]) : hd[r]) : -1;
+      tile_clusters<U>(a, tl, hd, cu);
       int32_t prev = -1;  // the last key this thread placed: repeats skip the set
 #pragma unroll
       for (int r = 0; r < U; ++r) {
@@ -762,7 +791,7 @@ void k_score_tile(PassArgs a) {
       }
     }
     __syncthreads();
-    const int nc = s_nc[t];
+    const int nc = t < nv ? s_nc[t] : 0;
     bool def = t < nv && s_def[t];
     bool is_b = t < nv && nc > 0 && !def;
     // one run per boundary vertex: its own cluster, then its candidates.
@@ -793,7 +822,7 @@ void k_score_tile(PassArgs a) {
         wide += nc > kTileCandAvg;
       }
     }
-    s_cur[t] = coff + 1;
+    if (t < TV) s_cur[t] = coff + 1;
     if (is_b) {
       s_cl[coff] = (t << 24) | s_c[t];
       if (s_clean[t])
@@ -849,7 +878,7 @@ void k_score_tile(PassArgs a) {
           for (int r = 0; r < kProbeRegs; ++r) lq[q][r] = lq[q - 1][r];
         }
     };
-    if (kfits) {
+    if constexpr (NR > 0) {
       int32_t xs[kProbeBatch], lab[kProbeBatch][kProbeRegs];
       uint32_t vs[kProbeBatch];
       int p0 = g * kProbeBatch;
@@ -1780,12 +1809,28 @@ void launch_score(const PassArgs& a, int grid, hipStream_t st) {
   k_score<G, false><<<grid, kBlock, 0, st>>>(a);
 }
 
+template <int TK, int TV>
+void launch_tile_v(const PassArgs& a, hipStream_t st) {
+  // as many workgroups as tiles, eight per compute unit at most
+  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((a.n + TV - 1) / TV, a.tile_grid));
+  if (a.k <= 16) k_score_tile<TK, TV, 1><<<grid, kBlock, 0, st>>>(a);
+  else if (a.k <= 32) k_score_tile<TK, TV, 2><<<grid, kBlock, 0, st>>>(a);
+  else if (a.k <= 64) k_score_tile<TK, TV, 4><<<grid, kBlock, 0, st>>>(a);
+  else k_score_tile<TK, TV, 0><<<grid, kBlock, 0, st>>>(a);
+}
+
 template <int TK>
 void launch_tile(const PassArgs& a, int grid, hipStream_t st) {
-  if (a.ac) k_score_tile<0, TK><<<grid, kBlock, 0, st>>>(a);
-  else if (a.cn_bytes == 1) k_score_tile<1, TK><<<grid, kBlock, 0, st>>>(a);
-  else if (a.cn_bytes == 2) k_score_tile<2, TK><<<grid, kBlock, 0, st>>>(a);
-  else k_score_tile<4, TK><<<grid, kBlock, 0, st>>>(a);
+  // Vertices a tile: up to 2^18 vertices, tiles of 64 (a launch of 256 would
+  // leave compute units without a tile: 15 passes over 100 000 vertices of
+  // an LFR graph 5.9 ms against 9.3, 24 over 30 000 3.5 against 7.9).  Above,
+  // tiles of 256 where at most 256 clusters keep the candidates few (2 M kNN
+  // vertices, 51 clusters: 8.2 ms against 8.8 with 128), else 128, whose key
+  // set holds 16 candidates a vertex (1 M LFR vertices, ten candidates each:
+  // 49.6 ms against 51.4 with 256 and 54.7 with 64).
+  if (a.n <= kSmallTileMax) launch_tile_v<TK, 64>(a, st);
+  else if (a.K0 <= 256) launch_tile_v<TK, 256>(a, st);
+  else launch_tile_v<TK, 128>(a, st);
   if (!a.st) return;
   if (a.ac) k_score_list<0, TK><<<grid, kBlock, 0, st>>>(a);
   else if (a.cn_bytes == 1) k_score_list<1, TK><<<grid, kBlock, 0, st>>>(a);
