@@ -275,8 +275,9 @@ typedef struct {
   int32_t* status;    /* optional host int32[count]: per-instance return code */
   const mcc_tune_table* tune;  /* optional host pointer, read only */
   const char* tune_cache_path; /* optional text file written by mcc_tune_save */
-  int32_t solved_in_batch; /* out: instances the persistent kernel finished
-                              (the rest went through mcc_consensus) */
+  int32_t solved_in_batch; /* out: instances within the batched solver's
+                              capacities that were solved (the rest went
+                              through mcc_consensus as too large) */
   float ms_total;     /* out: wall time of the call on the stream */
   int64_t workspace_bytes; /* out: device workspace the call held at most
                               (kept by the library for later calls on the
@@ -284,11 +285,15 @@ typedef struct {
 } mcc_batch_opts;
 
 /*
- * Many independent consensus problems in one persistent launch (the groups
- * of homogeneous partitions the paper solves independently, Methods, "The
- * algorithm").  Each workgroup of the kernel takes one instance at a time
- * from a queue ordered by estimated work (largest first) and runs the whole
- * method of mcc_consensus on it; the launch is captured in a HIP graph.
+ * Many independent consensus problems in one call (the groups of
+ * homogeneous partitions the paper solves independently, Methods, "The
+ * algorithm").  Instances of up to 65 536 vertices and 256 initial clusters
+ * with small contingency tables are solved together, each step of a pass one
+ * launch over all of them.  The others, and every instance when lanes or
+ * wg_per_cu is set, go to one persistent launch, whose workgroups take one
+ * instance at a time from a queue ordered by estimated work (largest first)
+ * and run the whole method of mcc_consensus on it; where a few are left,
+ * they are solved one after another if that is faster.
  * Instances beyond a workgroup's capacities (more than 256 partitions,
  * label values far above n, large contingency tables) are solved by
  * mcc_consensus on the same stream.  Every out[] and every stats field
@@ -346,9 +351,10 @@ int mcc_batch_tune(const mcc_problem* probs, int32_t count, const mcc_batch_opts
  *
  * mcc_batch_workspace_bytes: the workspace of one mcc_consensus_batch call
  * over these problems and options: the persistent launch's slots as the
- * call would size them (twice over for chunking, plus one chunk), or the
- * bound of the largest instance the call hands to mcc_consensus if that is
- * larger (instances with k > 256; instances that turn out to exceed a
+ * call would size them (twice over for chunking, plus one chunk), the
+ * level-by-level kernels' arrays, 192 MiB (granted to instances solved one
+ * after another), or the bound of the largest instance the call hands to
+ * mcc_consensus, whichever is largest (instances with k > 256; instances that turn out to exceed a
  * slot's table are not foreseen).  The exact figure of a finished call is
  * opts->workspace_bytes.
  *

@@ -311,7 +311,7 @@ def _batch_opts(max_rounds, flags, lanes, wg_per_cu, stream, tune, tune_cache_pa
 
 def consensus_batch(problems, *, max_rounds=0, flags=0, lanes=0, wg_per_cu=0, stream=None,
                     outs=None, tune=None, tune_cache_path=None):
-    """Solve many independent instances in one persistent launch.
+    """Solve many independent instances together.
 
     problems: sequence of dicts with CUDA tensors ``row_ptr`` (int64),
     ``col`` (int32), ``labels`` (int32 [k, n]) and optional ``init``.
@@ -319,7 +319,7 @@ def consensus_batch(problems, *, max_rounds=0, flags=0, lanes=0, wg_per_cu=0, st
     TuneTable), else the table file ``tune_cache_path``, else the built-in
     rule.  Returns ``(outs, stats, status, info)``: output tensors,
     per-instance stats dicts, per-instance return codes and the batch call's
-    info (instances finished in the persistent kernel, wall time)."""
+    info (instances within the batched solver's capacities, wall time)."""
     import torch
     count = len(problems)
     if outs is None:
@@ -559,8 +559,8 @@ def consensus_batch_packed(pb, *, max_rounds=0, flags=0, lanes=0, wg_per_cu=0, s
                            tune=None, tune_cache_path=None):
     """mcc_consensus_batch over a PackedBatch: outputs land in pb.out (see
     pb.output(j)), per-instance stats in pb.stats, codes in pb.status.
-    Returns the batch call's info (instances finished in the persistent
-    kernel, wall time, return code)."""
+    Returns the batch call's info (instances within the batched solver's
+    capacities, wall time, return code)."""
     o = _batch_opts(max_rounds, flags, lanes, wg_per_cu, stream, tune, tune_cache_path)
     o.status = ctypes.cast(pb.status, ctypes.c_void_p)
     recs = ctypes.cast(pb.records.ctypes.data, ctypes.POINTER(Problem))

@@ -14,6 +14,7 @@
 #include "batch.h"
 #include "impl.h"
 #include "mcc.h"
+#include "multi.h"
 
 namespace mcc {
 // setup.hip
@@ -132,6 +133,14 @@ class Arena {
     size_t b = 0;
     for (const Chunk& k : used_) b += k.size;
     return b;
+  }
+  // A fixed region's position, and going back to it: what was carved since
+  // is carved anew, in stream order (chunks are kept).
+  unsigned char* mark() const { return next_; }
+  void rewind(unsigned char* to) {
+    if (!fixed_) return;
+    left_ += (size_t)(next_ - to);
+    next_ = to;
   }
   // Host buffer that lives as long as the arena (source of async copies).
   template <class T>
@@ -751,6 +760,282 @@ const char* mcc_strerror(int code) {
 
 namespace {
 
+// ---------------------------------------------------------------------------
+// Instances with few clusters, solved level by level (multi.hip).
+// ---------------------------------------------------------------------------
+struct MultiResult {
+  bool known = false;  // K0, Ls and err are filled
+  bool solved = false;
+  int32_t K0 = 0, err = 0;
+  int64_t Ls = 0;
+  MultiCtl ctl{};
+};
+
+// What one launch sequence works on at a time: vertices of per-vertex state
+// (24 bytes each) and table bytes.  About a fifth of the 4096-instance
+// workload a wave: large enough that its launches and two synchronisations
+// (about 0.2 ms) are a few percent, small enough to bound the workspace.
+constexpr int64_t kMultiWaveVertices = (int64_t)1 << 23;
+constexpr int64_t kMultiWaveTable = (int64_t)1 << 28;
+
+// Counts between two rows of a slice: an odd number of 16-byte units.
+int32_t multi_row(int64_t n, int32_t K0) {
+  const int32_t unit = n < (1 << 15) ? 8 : 4;
+  return unit * (((K0 + unit - 1) / unit) | 1);
+}
+
+bool multi_fits(int64_t n, int32_t K0, int64_t Ls) {
+  return n > 0 && n <= kMultiVertices && K0 > 0 && K0 <= kMultiClusters && Ls > 0 &&
+         K0 * Ls <= kMultiCells && multi_row(n, K0) * Ls <= 2 * kMultiCells;
+}
+
+int64_t multi_table_bytes(int64_t n, int32_t k, int32_t K0, int32_t Ls) {
+  return (int64_t)multi_row(n, K0) * Ls * k * (n < (1 << 15) ? 2 : 4);
+}
+
+// The most it can be for an instance that fits.
+int64_t multi_table_bound(int64_t n, int32_t k) {
+  return (int64_t)2 * kMultiCells * k * (n < (1 << 15) ? 2 : 4);
+}
+
+// Upper bound of the workspace of one wave over instances like these (the
+// arrays multi_wave takes, allocation by allocation, doubled for the chunk
+// ends, plus a chunk).
+int64_t multi_bound(int64_t vertices, int64_t count, int64_t label_ptrs, int64_t table) {
+  const int64_t small = 24 * (vertices + 64 * count) + count * ((int64_t)sizeof(MultiInst) +
+                        (int64_t)sizeof(MultiCtl) + 12 * kMultiClusters + 4 * 256) +
+                        label_ptrs * 24 + (vertices / 256 + count) * 16;
+  return 2 * (small + table) + ((int64_t)16 << 20);
+}
+
+// One wave: the instances probs[ids[j]], results in res[ids[j]].  Instances
+// the kernels do not take are left with their ranges known.
+void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>& ids,
+                int32_t max_rounds, bool literal, hipStream_t st, MultiResult* res,
+                int64_t* dtrace = nullptr) {
+  const int32_t count = (int32_t)ids.size();
+  std::vector<MultiInst> hi(count);
+  std::vector<const int32_t*> ptrs;
+  std::vector<MultiItem> labels;
+  std::vector<MultiCtl> hc(count);
+  std::vector<int64_t> voff(count + 1, 0);
+  int64_t n_max = 1;
+  for (int32_t j = 0; j < count; ++j) {
+    const mcc_problem& p = probs[ids[j]];
+    for (int32_t i = 0; i < p.k; ++i) {
+      ptrs.push_back(p.labels[i]);
+      labels.push_back({j, i});
+    }
+    n_max = std::max<int64_t>(n_max, p.g.n);
+    // state only where the kernels may take the instance
+    voff[j + 1] = voff[j] + (p.g.n <= kMultiVertices ? (p.g.n + 63) & ~(int64_t)63 : 0);
+    hc[j].lmax = -1;
+  }
+  const int32_t** dptrs = ar.get<const int32_t*>((int64_t)ptrs.size());
+  h2d(dptrs, ar.host(ptrs), (int64_t)ptrs.size(), st);
+  MultiItem* dlabels = ar.get<MultiItem>((int64_t)labels.size());
+  h2d(dlabels, ar.host(labels), (int64_t)labels.size(), st);
+  uint16_t* C = ar.get<uint16_t>(voff[count]);
+  int32_t* rawid = ar.get<int32_t>(voff[count]);
+  int2* plist = ar.get<int2>(voff[count]);
+  int64_t* dprop = ar.get<int64_t>(voff[count]);
+  int64_t lo = 0;
+  for (int32_t j = 0; j < count; ++j) {
+    const mcc_problem& p = probs[ids[j]];
+    MultiInst& m = hi[j];
+    m.n = p.g.n;
+    m.row_ptr = p.g.row_ptr;
+    m.col = p.g.col;
+    m.labels = dptrs + lo;
+    lo += p.k;
+    m.init = p.init;
+    m.out = p.out;
+    m.k = p.k;
+    m.C = C + voff[j];
+    m.rawid = rawid + voff[j];
+    m.plist = plist + voff[j];
+    m.dprop = dprop + voff[j];
+  }
+  MultiInst* dinst = ar.get<MultiInst>(count);
+  MultiCtl* dctl = ar.get<MultiCtl>(count);
+  h2d(dinst, ar.host(hi), count, st);
+  h2d(dctl, ar.host(hc), count, st);
+  MultiArgs a{};
+  a.inst = dinst;
+  a.ctl = dctl;
+  a.count = count;
+  a.max_rounds = max_rounds;
+  a.literal = literal ? 1 : 0;
+  a.trace = dtrace;
+  launch_multi_ranges(a, dlabels, (int32_t)labels.size(), n_max, st);
+  d2h(hc.data(), dctl, count, st);
+  sync(st);
+
+  // the instances the kernels take, narrow and wide counts apart, as far as
+  // the wave's table budget goes (at least one)
+  int64_t soff = 0, toff = 0;
+  std::vector<int64_t> sat(count), tat(count);
+  std::vector<int32_t> live[2];
+  for (int32_t j = 0; j < count; ++j) {
+    MultiInst& m = hi[j];
+    MultiResult& r = res[ids[j]];
+    r.known = true;
+    r.K0 = hc[j].K0;
+    r.Ls = (int64_t)hc[j].lmax + 1;
+    r.err = hc[j].err;
+    if (r.err || !multi_fits(m.n, r.K0, r.Ls)) continue;
+    const int64_t tb = multi_table_bytes(m.n, m.k, r.K0, (int32_t)r.Ls);
+    if (toff > 0 && toff + tb > kMultiWaveTable) {
+      r.known = false;  // another wave
+      continue;
+    }
+    m.K0 = r.K0;
+    m.Ls = (int32_t)r.Ls;
+    m.rs = multi_row(m.n, m.K0);
+    m.cs = m.rs * m.Ls;
+    sat[j] = soff;
+    soff += (r.K0 + 63) & ~63;
+    tat[j] = toff;
+    toff += (tb + 255) & ~(int64_t)255;
+    live[m.n < (1 << 15) ? 0 : 1].push_back(j);
+  }
+  if (live[0].empty() && live[1].empty()) return;
+  int32_t* s = ar.get<int32_t>(soff);
+  uint64_t* owner = ar.get<uint64_t>(soff);
+  unsigned char* N = ar.get<unsigned char>(toff);
+  for (auto& l : live)
+    for (int32_t j : l) {
+      hi[j].s = s + sat[j];
+      hi[j].owner = owner + sat[j];
+      hi[j].N = N + tat[j];
+    }
+  h2d(dinst, ar.host(hi), count, st);
+
+  // Work lists of the live instances: partitions in two classes of slice
+  // size (the LDS of build and apply is sized to the class), tiles, and the
+  // instances themselves.
+  constexpr int32_t kSmallCells = 4096;
+  struct Lists {
+    std::vector<MultiItem> parts[2], tiles[kMultiModes];
+    std::vector<int32_t> ids;
+    int32_t cells[2] = {1, 1};
+    int words[kMultiModes] = {};
+    size_t slice[kMultiModes] = {}, table[kMultiModes] = {};
+    MultiItem* dparts[2] = {nullptr, nullptr};
+    MultiItem* dtiles[kMultiModes] = {};
+    int32_t* dids = nullptr;
+  } W[2];
+  int64_t total_n = 0;
+  for (auto& l : live)
+    for (int32_t j : l) total_n += hi[j].n;
+  // tiles of 1024 read the table less often; 256 when those would leave
+  // compute units without a tile
+  const int tile = total_n >= (int64_t)1024 * 2 * device_sms() ? 1024 : 256;
+  // (the lists only shrink from one call to the next, so their device arrays
+  // are taken once)
+  auto fill = [&](int w) {
+    Lists x;
+    for (int c = 0; c < 2; ++c) x.dparts[c] = W[w].dparts[c];
+    for (int q = 0; q < kMultiModes; ++q) x.dtiles[q] = W[w].dtiles[q];
+    x.dids = W[w].dids;
+    const size_t tsz = w ? 4 : 2;
+    for (int32_t j : live[w]) {
+      const MultiInst& m = hi[j];
+      const int32_t cells = m.K0 * m.Ls, cls = cells <= kSmallCells ? 0 : 1;
+      for (int32_t i = 0; i < m.k; ++i) x.parts[cls].push_back({j, i});
+      x.cells[cls] = std::max(x.cells[cls], cells);
+      const int q = multi_score_mode(m.K0, m.cs, w != 0, tile);
+      for (int32_t v = 0; v < (int32_t)((m.n + tile - 1) / tile); ++v)
+        x.tiles[q].push_back({j, v});
+      x.ids.push_back(j);
+      x.words[q] = std::max(x.words[q], (m.K0 + 31) / 32);
+      x.slice[q] = std::max(x.slice[q], (size_t)m.cs * tsz);
+      x.table[q] = std::max(x.table[q], (size_t)m.cs * tsz * (size_t)m.k);
+    }
+    auto up = [&](auto*& d, const auto& v) {
+      using T = std::remove_reference_t<decltype(*d)>;
+      if (v.empty()) return;
+      if (!d) d = ar.get<T>((int64_t)v.size());
+      h2d(d, ar.host(v), (int64_t)v.size(), st);
+    };
+    for (int c = 0; c < 2; ++c) up(x.dparts[c], x.parts[c]);
+    for (int q = 0; q < kMultiModes; ++q) up(x.dtiles[q], x.tiles[q]);
+    up(x.dids, x.ids);
+    W[w] = x;
+  };
+  for (int w = 0; w < 2; ++w) {
+    if (live[w].empty()) continue;
+    fill(w);
+    for (int c = 0; c < 2; ++c)
+      launch_multi_build(a, W[w].dparts[c], (int32_t)W[w].parts[c].size(), w != 0, W[w].cells[c],
+                         st);
+  }
+  int enqueued = 0, chunk = 2;
+  while (enqueued < max_rounds) {
+    const int todo = std::min(chunk, max_rounds - enqueued);
+    for (int q = 0; q < todo; ++q)
+      for (int w = 0; w < 2; ++w) {
+        const Lists& x = W[w];
+        if (x.ids.empty()) continue;
+        // the slice buffer: at least one slice; 16 KiB for small tiles, of
+        // which several share a compute unit, 64 KiB for large ones; none for
+        // the mode that reads the table from memory
+        for (int md = 0; md < kMultiModes; ++md) {
+          const size_t room = tile == 256 ? (16 << 10) : (64 << 10);
+          const size_t buf =
+              md == kMultiDirect ? 0 : std::max(x.slice[md], std::min(x.table[md], room));
+          launch_multi_score(a, x.dtiles[md], (int32_t)x.tiles[md].size(), w != 0, md, tile,
+                             x.words[md], buf, st);
+        }
+        for (int c = 0; c < 2; ++c)
+          launch_multi_apply(a, x.dparts[c], (int32_t)x.parts[c].size(), w != 0, x.cells[c], st);
+        launch_multi_commit(a, x.dids, (int32_t)x.ids.size(), w != 0, st);
+      }
+    enqueued += todo;
+    d2h(hc.data(), dctl, count, st);
+    sync(st);
+    bool any = false;
+    for (int w = 0; w < 2; ++w) {  // the instances still running
+      std::vector<int32_t> rest;
+      for (int32_t j : live[w])
+        if (!hc[j].done) rest.push_back(j);
+      any = any || !rest.empty();
+      if (2 * rest.size() <= live[w].size() && !live[w].empty()) {
+        for (int32_t j : live[w])
+          if (hc[j].done) {
+            res[ids[j]].solved = true;
+            res[ids[j]].ctl = hc[j];
+          }
+        live[w] = rest;
+        fill(w);
+      }
+    }
+    if (!any) break;
+    chunk = std::min(chunk * 2, 16);
+  }
+  for (auto& l : live)
+    for (int32_t j : l) {
+      res[ids[j]].solved = true;
+      res[ids[j]].ctl = hc[j];
+    }
+}
+
+void multi_stats(const MultiCtl& c, mcc_stats* o) {
+  o->passes = c.passes;
+  o->converged = c.converged;
+  o->fallback_rounds = c.fallback_rounds;
+  o->clusters = c.clusters;
+  o->moves = c.moves;
+  o->candidate_evals = c.evals;
+  o->boundary = c.boundary;
+  o->objective_init = c.O0;
+  o->objective = c.O;
+}
+
+}  // namespace
+
+namespace {
+
 // One solve.  noalloc: the workspace is the device's scratch array instead
 // of the cached chunks (nothing is allocated).
 int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
@@ -807,6 +1092,35 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     hipEvent_t evs[4] = {e0, e1, e2, e3};
     Ev guard{evs};
     HIPCK(hipEventRecord(e0, st));
+
+    // a small instance with few clusters: the level-by-level kernels, three
+    // launches a pass instead of ten or more
+    if (lanes_req == 0 && n <= kMultiVertices && k <= 256 && (init || n <= kMultiClusters) &&
+        !(flags & ~(MCC_F_TRACE | MCC_F_LITERAL | MCC_F_SYMMETRIC))) {
+      unsigned char* const before = ar.mark();
+      int64_t* dtrace = nullptr;
+      if (flags & MCC_F_TRACE) dtrace = ar.get<int64_t>((int64_t)max_rounds * 4);
+      mcc_problem one{*g, labels, k, init, out};
+      MultiResult r;
+      multi_wave(ar, &one, {0}, max_rounds, (flags & MCC_F_LITERAL) != 0, st, &r, dtrace);
+      if (r.err) throw Status{MCC_EINVAL};
+      if (r.solved) {
+        HIPCK(hipEventRecord(e3, st));
+        if (flags & MCC_F_TRACE) {
+          memset(stats->trace, 0, sizeof(int64_t) * 4 * (size_t)max_rounds);
+          d2h(stats->trace, dtrace, (int64_t)4 * r.ctl.passes, st);
+        }
+        sync(st);
+        if (stats) {
+          multi_stats(r.ctl, stats);
+          stats->workspace_bytes = (int64_t)ar.bytes_used();
+          HIPCK(hipEventElapsedTime(&stats->ms_total, e0, e3));
+          stats->ms_passes = stats->ms_total;
+        }
+        return MCC_OK;
+      }
+      ar.rewind(before);  // the scratch array holds what it held without the attempt
+    }
 
     std::vector<const int32_t*> hptrs(labels, labels + k);
     Solve S;
@@ -1412,6 +1726,38 @@ int64_t heuristic_cells_cap(const mcc_problem* probs, const std::vector<int32_t>
   return std::min<int64_t>(std::max<int64_t>(n_max * k_max, (int64_t)1 << 18), kCellsCapMax);
 }
 
+// Workspace that mcc_batch_workspace_bytes grants a call beyond the
+// persistent launch's own, for instances solved one after another.
+constexpr int64_t kAloneBytes = (int64_t)192 << 20;
+
+// Whether the instances the level-by-level kernels left are better solved
+// one after another by mcc_consensus than in one persistent launch, whose
+// workgroups take one instance each: all of their ranges must be known and
+// their workspace bounded.  Measured: a workgroup takes about 28 ns for an
+// arc or label of its instance (24 SBM instances of up to 20 000 vertices
+// and 64 partitions: 48 ms for the largest, 1.7 M of them), a lone solve
+// about 0.5 ms and 1 ns for each.
+bool rest_alone(const mcc_problem* probs, const std::vector<int32_t>& rest, int32_t count,
+                const std::vector<MultiResult>& mres, int64_t cells_cap, int wgpc) {
+  const BatchSizes z = batch_sizes(probs, rest, count, cells_cap, wgpc);
+  const int64_t grant = std::max(2 * z.bytes + ((int64_t)16 << 20), kAloneBytes);
+  double sum = 0, most = 0, lone = 0;
+  for (int32_t i : rest) {
+    const mcc_problem& p = probs[i];
+    const MultiResult& r = mres[i];
+    int64_t bound = 0;
+    if (!r.known || r.Ls < 1 ||
+        mcc_workspace_bound(p.g.n, p.g.nnz, p.k, r.Ls - 1, r.K0, 0, &bound) != MCC_OK ||
+        bound > grant)
+      return false;
+    const double w = (double)p.g.nnz + (double)p.g.n * p.k;
+    sum += w;
+    most = std::max(most, w);
+    lone += 0.5 + 1e-6 * w;
+  }
+  return lone < 28e-6 * std::max(most, sum / (double)z.slots);
+}
+
 }  // namespace
 
 extern "C" {
@@ -1469,33 +1815,94 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
     } evg{e0, e1};
     HIPCK(hipEventRecord(e0, st));
     std::vector<BatchRes> hres(count);
+    std::vector<MultiResult> mres(count);
+    auto held = [&](int64_t bytes) {
+      if (opts) opts->workspace_bytes = std::max(opts->workspace_bytes, bytes);
+    };
     if (!eligible.empty()) {
       BatchRun run;
       run.probs = probs;
-      run.ids = eligible;
       run.lanes.assign(count, 16);
-      int64_t cells = 0;
+      int64_t cells = 0, n_max = 1;
       bool covered = table != nullptr;
       for (int32_t i : eligible) {
         const mcc_tune_entry* e = tune_lookup(table, probs[i].g.n, probs[i].k);
         if (!e) covered = false;
         else cells = std::max(cells, e->cells);
         run.lanes[i] = lanes ? lanes : (e ? e->lanes : default_lanes(probs[i].g.n));
+        n_max = std::max<int64_t>(n_max, probs[i].g.n);
       }
       run.cells_cap = covered ? std::min(kCellsCapMax, std::max(kCellsCapMin, pow2_ceil(cells)))
                               : heuristic_cells_cap(probs, eligible);
       run.wgpc = wgpc;
       run.max_rounds = max_rounds;
       run.literal = (flags & MCC_F_LITERAL) ? 1 : 0;
-      int64_t ws = 0;
-      run_batch(run, count, st, &hres, &ws);
-      if (opts) opts->workspace_bytes = ws;
+      // Level by level where the launch shape is left to the library: the
+      // instances those kernels take are solved, the others' cluster counts
+      // and label ranges known (up to kMultiCount vertices).
+      if (lanes == 0 && !(opts && opts->wg_per_cu > 0)) {
+        std::vector<int32_t> todo;
+        for (int32_t i : eligible)
+          if (probs[i].g.n > 0 && probs[i].g.n <= kMultiCount) todo.push_back(i);
+        while (!todo.empty()) {
+          std::vector<int32_t> wave, later;
+          int64_t vertices = 0;
+          for (int32_t i : todo) {
+            const int64_t v = probs[i].g.n <= kMultiVertices ? probs[i].g.n : 0;
+            if (!wave.empty() && vertices + v > kMultiWaveVertices) {
+              later.push_back(i);
+            } else {
+              wave.push_back(i);
+              vertices += v;
+            }
+          }
+          Arena ar(st);
+          multi_wave(ar, probs, wave, max_rounds, run.literal != 0, st, mres.data());
+          held((int64_t)ar.bytes_used());
+          todo.clear();
+          for (int32_t i : wave)  // the wave's table budget was full
+            if (!mres[i].known) todo.push_back(i);
+          todo.insert(todo.end(), later.begin(), later.end());
+        }
+      }
+      // what the persistent kernel's slots hold
+      auto holds = [&](int32_t i) {
+        const MultiResult& r = mres[i];
+        return (int64_t)r.K0 * r.Ls * probs[i].k <= run.cells_cap &&
+               !(r.Ls > 1024 && r.Ls > 2 * n_max + 1024);
+      };
+      std::vector<int32_t> rest, alone;
       for (int32_t i : eligible) {
+        const MultiResult& r = mres[i];
+        if (r.known && r.err) {
+          status[i] = MCC_EINVAL;
+        } else if (r.solved) {
+          if (stats) multi_stats(r.ctl, &stats[i]);
+          if (opts && holds(i)) opts->solved_in_batch += 1;
+        } else if (r.known && !holds(i)) {
+          fallback.push_back(i);
+        } else {
+          rest.push_back(i);
+        }
+      }
+      if (!rest.empty() && rest_alone(probs, rest, count, mres, run.cells_cap, wgpc))
+        alone.swap(rest);
+      for (int32_t i : alone) {
+        fallback.push_back(i);
+        if (opts) opts->solved_in_batch += 1;
+      }
+      if (!rest.empty()) {
+        run.ids = rest;
+        int64_t ws = 0;
+        run_batch(run, count, st, &hres, &ws);
+        held(ws);
+      }
+      for (int32_t i : rest) {
         if (hres[i].status == kBatchTooBig) fallback.push_back(i);
         else if (hres[i].status == kBatchInvalid) status[i] = MCC_EINVAL;
         else if (opts) opts->solved_in_batch += 1;
       }
-      for (int32_t i : eligible) {
+      for (int32_t i : rest) {
         if (hres[i].status != 0 || !stats) continue;
         mcc_stats& o = stats[i];
         o.passes = hres[i].passes;
@@ -1519,7 +1926,7 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
       const int rc = mcc_consensus(&p.g, p.labels, p.k, p.init, p.out, &one);
       status[i] = rc;
       if (stats && rc == MCC_OK) stats[i] = one;
-      if (opts) opts->workspace_bytes = std::max(opts->workspace_bytes, one.workspace_bytes);
+      held(one.workspace_bytes);
     }
     HIPCK(hipEventRecord(e1, st));
     sync(st);
@@ -2042,6 +2449,10 @@ int mcc_workspace_bound(int64_t n, int64_t nnz, int32_t k, int64_t max_label, in
     add(4 * n * kCacheCand); add(8 * K0); add(4);
   }
   *bytes = big + 2 * small + kChunk;
+  // the level-by-level kernels, which take it first when it is small
+  if (n > 0 && n <= kMultiVertices && k <= 256)
+    *bytes += multi_bound(n, 1, k, multi_table_bound(n, k)) +
+              ((flags & MCC_F_TRACE) ? 8 * 4 * 1000 : 0);
   return MCC_OK;
 }
 
@@ -2082,7 +2493,21 @@ int mcc_batch_workspace_bytes(const mcc_problem* probs, int32_t count,
                                 : heuristic_cells_cap(probs, eligible);
     const BatchSizes z = batch_sizes(probs, eligible, count, cap, wgpc);
     // carved from 16 MiB chunks (larger requests get their own)
-    *bytes = 2 * z.bytes + ((int64_t)16 << 20);
+    *bytes = std::max(2 * z.bytes + ((int64_t)16 << 20), kAloneBytes);
+    // the level-by-level kernels' waves
+    int64_t vertices = 0, ptrs = 0, table = 0, largest = 0;
+    for (int32_t i : eligible) {
+      const mcc_problem& p = probs[i];
+      ptrs += p.k;
+      if (p.g.n <= 0 || p.g.n > kMultiVertices) continue;
+      vertices += p.g.n;
+      const int64_t t = multi_table_bound(p.g.n, p.k) + 256;
+      table += t;
+      largest = std::max(largest, t);
+    }
+    const int64_t waved = std::min(vertices, kMultiWaveVertices + kMultiVertices);
+    *bytes = std::max(*bytes, multi_bound(waved, (int64_t)eligible.size(), ptrs,
+                                          std::min(table, kMultiWaveTable + largest)));
   }
   *bytes = std::max(*bytes, single);
   return MCC_OK;
