@@ -142,6 +142,8 @@ class Arena {
     left_ += (size_t)(next_ - to);
     next_ = to;
   }
+  // Whether `bytes` more are to be had: always, but for a fixed region.
+  bool fits(int64_t bytes) const { return !fixed_ || bytes <= (int64_t)left_; }
   // Host buffer that lives as long as the arena (source of async copies).
   template <class T>
   T* host(const std::vector<T>& src) {
@@ -1036,6 +1038,11 @@ void multi_stats(const MultiCtl& c, mcc_stats* o) {
 
 namespace {
 
+// Workspace of the candidate sets carried over between passes.
+int64_t carry_bytes(int64_t n, int64_t K0) {
+  return 4 * (5 * n + n * kCacheCand + 2 * K0 + (n + 31) / 32) + 8 * 256;
+}
+
 // One solve.  noalloc: the workspace is the device's scratch array instead
 // of the cached chunks (nothing is allocated).
 int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
@@ -1132,7 +1139,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     int64_t* dtrace = nullptr;
     if (flags & MCC_F_TRACE) dtrace = ar.get<int64_t>((int64_t)max_rounds * 4);
     Ctl* ctl = ar.get<Ctl>(1);
-    launch_ctl_init(ctl, S.acc, k, max_rounds, dtrace, st);
+    launch_ctl_init(ctl, S.acc, n, k, max_rounds, dtrace, st);
     uint64_t* owner = ar.get<uint64_t>(S.K0);
     launch_fill_u64(owner, S.K0, ~0ull, st);
     int32_t* prop = ar.get<int32_t>(n);
@@ -1159,7 +1166,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
 
     PassArgs a{};
     a.ctl = ctl;
-    a.pc = ar.get<int64_t>(kPassCounters * kCounterStride);
+    a.pc = ar.get<int64_t>((kPassCounters + kTickets) * kCounterStride);
     a.plist = ar.get<int32_t>(n);
     if (!S.t.hashed) {  // histogram apply when a partition's slice fits in LDS
       const int64_t slice = (int64_t)S.K0 * S.maxL + 2 * (int64_t)S.K0;
@@ -1168,7 +1175,8 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
         a.delta_slices = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, n / 2048));
       }
     }
-    launch_fill_u64(reinterpret_cast<uint64_t*>(a.pc), kPassCounters * kCounterStride, 0ull, st);
+    launch_fill_u64(reinterpret_cast<uint64_t*>(a.pc), (kPassCounters + kTickets) * kCounterStride,
+                    0ull, st);
     a.n = n;
     a.k = k;
     a.literal = (flags & MCC_F_LITERAL) ? 1 : 0;
@@ -1219,7 +1227,16 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
 
     // the tiled scorer packs cluster ids in 24 bits
     const int lanes = (lanes_req == 0 && S.K0 >= (1 << 24)) ? 64 : lanes_req;
-    if ((flags & MCC_F_SYMMETRIC) && lanes == 0) {  // candidate sets carried over
+    // Candidate sets carried over between passes: dirty marks are pushed along
+    // the arcs of a symmetric graph, else pulled (not beside the arc cache,
+    // nor where the scratch array has no room for them).
+    const bool push = (flags & MCC_F_SYMMETRIC) != 0;
+    if (lanes == 0 && (push || (!(flags & MCC_F_ARC_CACHE) &&
+                                ar.fits(carry_bytes(n, S.K0))))) {
+      if (!push) {
+        a.moved = ar.get<uint32_t>((n + 31) / 32);
+        launch_fill_i32(reinterpret_cast<int32_t*>(a.moved), (n + 31) / 32, 0, st);
+      }
       a.dirty = ar.get<int32_t>(n);
       a.cnum = ar.get<int32_t>(n);
       a.ccache = ar.get<int32_t>(n * kCacheCand);
@@ -1254,10 +1271,12 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     HIPCK(hipEventRecord(e1, st));
     Ctl hc;
     memset(&hc, 0, sizeof hc);
-    int enqueued = 0, chunk = 2;
-    while (enqueued < max_rounds) {
-      const int todo = std::min(chunk, max_rounds - enqueued);
-      for (int j = 0; j < todo; ++j) {
+    // slots are enqueued ahead in growing chunks; a pass takes one, or two
+    // when it falls back
+    int chunk = 2;
+    for (int64_t enqueued = 0; enqueued < 2 * (int64_t)max_rounds; enqueued += chunk) {
+      if (enqueued) chunk = std::min(chunk * 2, 16);
+      for (int j = 0; j < chunk; ++j) {
         hipEvent_t b = nullptr, e = nullptr;
         if (profile) {
           HIPCK(hipEventCreate(&b));
@@ -1267,11 +1286,9 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
         }
         enqueue_pass(a, lanes, grid_score, grid_apply, st, b, e);
       }
-      enqueued += todo;
       d2h(&hc, ctl, 1, st);
       sync(st);
       if (hc.done) break;
-      chunk = std::min(chunk * 2, 16);
     }
     HIPCK(hipEventRecord(e2, st));
 
@@ -1315,7 +1332,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
       stats->tables = S.t.hashed ? (S.t.rows ? 3 : 2) : (S.t.interleaved ? 1 : 0);
       if (profile) {
         float tot = 0.f;
-        for (int j = 0; j < hc.passes && 2 * j + 1 < (int)pev.size(); ++j) {
+        for (int j = 0; j < hc.slots && 2 * j + 1 < (int)pev.size(); ++j) {
           HIPCK(hipEventElapsedTime(&ms, pev[2 * j], pev[2 * j + 1]));
           tot += ms;
         }
@@ -2438,15 +2455,15 @@ int mcc_workspace_bound(int64_t n, int64_t nnz, int32_t k, int64_t max_label, in
   add(4 * nk); add(24);  // label rows, objective sums
   // per-pass state
   add(sizeof(Ctl)); add(8 * K0); add(4 * n); add(8 * n); add(4 * n); add(4 * n);
-  add(8 * kPassCounters * kCounterStride); add(2 * n); add(4); add(4);
+  add(8 * (kPassCounters + kTickets) * kCounterStride); add(2 * n); add(4); add(4);
   if (flags & MCC_F_TRACE) add(8 * 4 * 1000);
   if (flags & MCC_F_ARC_CACHE) {
     add(4 * (n + 1)); add(4 * (n + 1)); add(4 * (scan_tmp_elems(n) + 1));
     add(4 * nnz); add(4 * nnz);
   }
-  if (flags & MCC_F_SYMMETRIC) {
+  if ((flags & MCC_F_SYMMETRIC) || !(flags & MCC_F_ARC_CACHE)) {  // carried-over candidates
     for (int j = 0; j < 5; ++j) add(4 * n);
-    add(4 * n * kCacheCand); add(8 * K0); add(4);
+    add(4 * n * kCacheCand); add(8 * K0); add(4); add((n + 31) / 8);
   }
   *bytes = big + 2 * small + kChunk;
   // the level-by-level kernels, which take it first when it is small

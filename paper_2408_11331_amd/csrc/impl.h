@@ -24,7 +24,6 @@ struct Ctl {
   int32_t max_rounds;       // pass cap
   int32_t k;                // number of input partitions
   int32_t err;              // input error bits (see kErr*)
-  int64_t pass_evals;       // candidate clusters scored in the current pass
   int64_t evals;            // candidate clusters scored in all passes
   int64_t dS2;              // change of sum_c s_c^2 caused by tracked updates
   int64_t dN2;              // change of sum_i sum_(c,l) N_i(c,l)^2, same
@@ -38,6 +37,12 @@ struct Ctl {
                             // scorer (most had too many candidates for the tiles)
   int64_t skipped;          // candidate evaluations proven unnecessary (all passes)
   int64_t prop_rows;        // hashed rows: rows the current pass's proposals can add
+  // A pass takes one slot of launches, or two when its batch falls back:
+  // stage 1 is the second, which commits the conflict-free subset.
+  int32_t stage;
+  int32_t slots;            // slots run
+  int32_t churn_max;        // largest move count of a cluster in the last batch applied
+  int32_t last_moves;       // committed moves of the last pass (n before the first)
   int64_t* trace;           // device int64[max_rounds * 4] or null
 };
 
@@ -416,14 +421,16 @@ struct PassArgs {
   int32_t cn_bytes;
   int32_t arcs_aligned;  // col (and ac) start on a 16-byte boundary
   int64_t nnz;
-  // Symmetric graphs (every arc has its reverse): candidate sets carried
-  // over between passes.  A vertex is dirty when it or a neighbour moved in
-  // the previous pass (a move marks the mover and its out-neighbours, which
-  // are its in-neighbours); a clean vertex with a cached set (cnum >= 0)
-  // skips its arcs.  Null when off.
+  // Candidate sets carried over between passes.  A vertex is dirty when it or
+  // a neighbour moved in the previous pass.  On symmetric graphs (every arc
+  // has its reverse) a move marks the mover and its out-neighbours, which are
+  // its in-neighbours; otherwise the movers are the bits of `moved` and every
+  // vertex looks its neighbours up (k_pull).  A clean vertex with a cached
+  // set (0 <= cnum <= kCacheCand) skips its arcs.  Null when off.
   int32_t* dirty;     // n
-  int32_t* cnum;      // n: cached candidate count, -1 none
-  int32_t* ccache;    // n * kCacheCand
+  int32_t* cnum;      // n: candidates at the last exact scoring, -1 unknown
+  int32_t* ccache;    // n * kCacheCand: the candidates where they fit
+  uint32_t* moved;    // (n + 31) / 32 words, or null (symmetric)
   // Skipping provably unchanged decisions (with the candidate cache).  The
   // gain of v for x, 2 (S_c(v) - S_x(v)) + k (|x| - |c| - 1), moves by at
   // most k for every vertex that enters or leaves c or x (each changes
@@ -433,8 +440,9 @@ struct PassArgs {
   // vertices that entered or left each cluster in the previous pass
   // (churn[(p & 1) K0 ..] is read by pass p; the other half is filled by
   // its apply).  A clean vertex whose slack stays >= 0 after subtracting
-  // k (churn of its cluster + largest churn of its cached candidates)
-  // cannot propose, and is not rescored.
+  // k (churn of its cluster + largest churn of its candidates) cannot
+  // propose, and is not rescored; of candidates that are not cached, the
+  // largest churn of any cluster is taken.
   int32_t* slack;     // n
   int32_t* churn;     // 2 * K0
   // Per-pass status (with the candidate cache), written by k_status:
@@ -450,8 +458,10 @@ struct PassArgs {
   int32_t pad3;
   // Per-pass counters of the scoring kernels (kPassCounters of them, each in
   // its own 512-byte line so that their atomics do not share an L2 channel),
-  // added once per workgroup and folded into the control block by k_begin.
-  int64_t* pc;        // kPassCounters * kCounterStride
+  // added once per workgroup and folded into the control block by pass_begin.
+  // Behind them, in lines of their own, the tickets of the props, apply and
+  // commit kernels (workgroups done).
+  int64_t* pc;        // (kPassCounters + kTickets) * kCounterStride
   // The proposers of the pass, listed by k_props: the batch apply then runs
   // on as many workgroups as the proposals need, so that a counter that many
   // proposals update receives one atomic from each of few workgroups.
@@ -470,9 +480,13 @@ constexpr int kDeltaLdsMax = 48 << 10;
 
 constexpr int kPassCounters = 5;    // evaluations, proposals, boundary vertices, skipped,
                                     // boundary vertices with more candidates than a tile holds
+constexpr int kTickets = 3;
 constexpr int kCounterStride = 64;  // int64 words between two counters
 
-constexpr int kCacheCand = 8;  // candidate clusters cached per vertex
+// Candidate clusters cached per vertex.  An LFR vertex of degree 20 has ten
+// candidates: with room for 8, half of the vertices of 1 M were scored anew
+// in each of 36 passes (0.93 ms a pass where a hundred vertices moved).
+constexpr int kCacheCand = 16;
 
 // Compile-time variants: CN is the narrow copy's width in bytes (0: read the
 // per-arc cache), IL selects the interleaved table layout.
@@ -539,11 +553,11 @@ __device__ inline int32_t block_exclusive_scan(int32_t x, int32_t* total) {
 // lanes 0: tiled scorer (with the group scorer for deferred vertices);
 // 4..64: group scorer with that many lanes per vertex.
 bool score_lanes_ok(int lanes);
-// Enqueue one pass; when the events are given they bracket the scoring
+// Enqueue one slot of a pass; when the events are given they bracket the scoring
 // kernel on the same stream.
 void enqueue_pass(const PassArgs& a, int lanes, int grid_score, int grid_apply, hipStream_t st,
                   hipEvent_t score_begin = nullptr, hipEvent_t score_end = nullptr);
-void launch_ctl_init(Ctl* ctl, const int64_t* acc, int32_t k, int32_t max_rounds,
+void launch_ctl_init(Ctl* ctl, const int64_t* acc, int64_t n, int32_t k, int32_t max_rounds,
                      int64_t* trace, hipStream_t st);
 
 }  // namespace mcc

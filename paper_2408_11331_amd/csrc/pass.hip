@@ -4,18 +4,24 @@
 //   score      every vertex, against the frozen partition, finds the
 //              neighbour cluster with the smallest (gain, cluster id) and
 //              proposes it when the gain is negative (Eq. objective3/4)
-//   begin      count the pass; stop if nothing was proposed
+//   props      list the proposals; its last workgroup counts the pass and
+//              stops the solve if there are none
 //   apply      apply every proposal to sizes and counts, measuring the exact
-//              change of the objective on the way
-//   decide     keep the batch if the objective dropped, else fall back
+//              change of the objective on the way; its last workgroup keeps
+//              the batch if the objective dropped, else lets it fall back
 //   commit     write the new cluster ids, or (fallback) undo the batch and
-//              elect an owner per touched cluster
-//   fb_commit  (fallback) apply the proposals that own both their clusters
-//   fb_finish  (fallback) release owners, write the committed cluster ids
-//   end        account the pass, enforce the pass cap
+//              elect an owner per touched cluster; its last workgroup
+//              accounts the pass and enforces the pass cap
+//
+// A pass that falls back takes a second slot of the same launches, in which
+// only fallback and commit work: fallback applies the proposals that own both
+// their clusters, commit releases the owners and writes the committed cluster
+// ids.
 //
 // Every kernel returns at once when the control block says the solve is
-// done, so the host may enqueue passes ahead of the device.
+// done, so the host may enqueue slots ahead of the device.  The control
+// steps ride on the last workgroup of a kernel (a ticket counter: nothing
+// waits) because a launch of its own costs about 4 us each.
 //
 // Gain of moving v from c to x (exact, the pair (v, v) left out):
 //   2 (S_c(v) - S_x(v)) + k (s_x - s_c - 1),  S_y(v) = sum_i N_i(y, P_i(v)),
@@ -121,7 +127,7 @@ constexpr int kCandSet = 1 << kCandSetBits;
 
 template <int G, bool LIST>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_score(PassArgs a) {
-  if (a.ctl->done) return;
+  if (a.ctl->done || a.ctl->stage) return;
   // LIST: the vertices the tiled or list scorer deferred or, in a dense pass
   // the tiled scorer leaves to this kernel (defer_all), every vertex to
   // score: the rescoring list, or all vertices when there is none
@@ -140,12 +146,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
   // list starts, clusters, and the items of clusters without member lists
   constexpr int kW = (LIST && G == 64) ? kBlock / 64 : 1;
   constexpr int kI = (LIST && G == 64) ? 130 : 1;
-  __shared__ int32_t s_ioff[kW][kI], s_isum[kW][kI], s_imst[kW][kI], s_iy[kW][kI],
-      s_ilarge[kW][kI];
+  __shared__ int32_t s_ioff[kW][kI], s_imst[kW][kI], s_iy[kW][kI], s_ilarge[kW][kI];
+  __shared__ int32_t s_isum[kW][(LIST && G == 64) ? kCandSet + 2 : 1];
   __shared__ __align__(8) int32_t s_vrow[kW][(LIST && G == 64) ? 64 : 2];
   __shared__ int32_t s_cset[kW][(LIST && G == 64) ? kCandSet : 1];
   __shared__ int32_t s_cnb[kW][(LIST && G == 64) ? kCandSet : 1];  // a neighbour in the cluster
-  __shared__ int32_t s_clist[kW][(LIST && G == 64) ? 128 : 1];
+  __shared__ int32_t s_clist[kW][(LIST && G == 64) ? kCandSet : 1];
   __shared__ int32_t s_cnbl[kW][(LIST && G == 64) ? 128 : 1];
   __shared__ int32_t s_ccount[kW];
   const int lane = threadIdx.x & (G - 1);
@@ -298,7 +304,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
         }
         __builtin_amdgcn_wave_barrier();
         int32_t nc = s_ccount[w];
-        const bool many = nc > 128;  // more than 128 candidates: the general path below
+        // more than 128 candidates (with member lists), or as many as the set
+        // holds: the general path below
+        const bool many = a.members ? nc > 128 : nc >= kCandSet;
         int32_t cand_lo = kInf, cand_hi = kInf;
         if (!many) {
           int32_t mine = 0, keys[kCandSet / 64];
@@ -314,7 +322,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
 #pragma unroll
           for (int q = 0; q < kCandSet / 64; ++q)
             if (keys[q] != -1) {
-              cnbl[pos] = cnb[lane + 64 * q];
+              if (pos < 128) cnbl[pos] = cnb[lane + 64 * q];
               clist[pos++] = keys[q];
             }
           __builtin_amdgcn_wave_barrier();
@@ -325,7 +333,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
         if (!many) {
           if (a.dirty) {  // the candidate set, cached for later passes
             if (lane < min(nc, kCacheCand)) a.ccache[v * kCacheCand + lane] = cand_lo;
-            if (lane == 0) a.cnum[v] = nc <= kCacheCand ? nc : -1;
+            if (lane == 0) a.cnum[v] = nc;
           }
           if (nc == 0) {
             if (lane == 0) a.prop[v] = kNone;
@@ -478,28 +486,37 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
             __builtin_amdgcn_wave_barrier();
             s_v = isum[0];
             s_lo = isum[1 + lane];
-            s_hi = lane < 64 ? isum[65 + lane] : 0;
+            s_hi = isum[65 + lane];
             __builtin_amdgcn_wave_barrier();
           } else {
-            for (int j0 = 0; j0 < nitems; j0 += 4) {
-              const int it = j0 + sg, ci = it - 1;
-              const int32_t y_lo = __shfl(cand_lo, ci < 0 ? 0 : (ci & 63), 64);
-              const int32_t y_hi = __shfl(cand_hi, ci < 0 ? 0 : (ci & 63), 64);
-              const int32_t y = it == 0 ? cv : (ci < 64 ? y_lo : y_hi);
-              int32_t sum = 0;
-              if (it < nitems) {
+            // table probes, four items a step and group, the sums of a lane's
+            // items kept in LDS (the latency of a probe, not the sums, is what
+            // a step costs: a hub's forty candidates took ten dependent steps)
+            constexpr int D = 4;
+            int32_t* isum = s_isum[w];
+            const int32_t* clist = s_clist[w];
+            for (int j0 = 0; j0 < nitems; j0 += 4 * D) {
+              int32_t sum[D];
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                  if (sl + 16 * q < k) sum += count_of(a.t, sl + 16 * q, y, lb[q]);
+              for (int e = 0; e < D; ++e) {
+                const int it = j0 + 4 * e + sg;
+                sum[e] = 0;
+                if (it < nitems) {
+                  const int32_t y = it == 0 ? cv : clist[it - 1];
+#pragma unroll
+                  for (int q = 0; q < 4; ++q)
+                    if (sl + 16 * q < k) sum[e] += count_of(a.t, sl + 16 * q, y, lb[q]);
+                }
               }
-              sum = group_sum<16>(sum);
-              if (j0 == 0) s_v = __shfl(sum, 0, 64);
-              const int g_lo = lane + 1 - j0, g_hi = lane + 65 - j0;  // groups holding my items
-              const int32_t got_lo = __shfl(sum, (g_lo >= 0 && g_lo < 4) ? g_lo * 16 : 0, 64);
-              const int32_t got_hi = __shfl(sum, (g_hi >= 0 && g_hi < 4) ? g_hi * 16 : 0, 64);
-              if (g_lo >= 0 && g_lo < 4) s_lo = got_lo;
-              if (g_hi >= 0 && g_hi < 4) s_hi = got_hi;
+#pragma unroll
+              for (int e = 0; e < D; ++e) {
+                const int it = j0 + 4 * e + sg;
+                const int32_t x = group_sum<16>(sum[e]);
+                if (sl == 0 && it < nitems) isum[it] = x;
+              }
             }
+            __builtin_amdgcn_wave_barrier();
+            s_v = isum[0];
           }
           const int64_t scv = a.s[cv];
           int64_t bd = INT64_MAX;
@@ -512,8 +529,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
               bx = xc;
             }
           };
-          if (lane < nc) consider(cand_lo, s_lo);
-          if (lane + 64 < nc) consider(cand_hi, s_hi);
+          if (a.members) {
+            if (lane < nc) consider(cand_lo, s_lo);
+            if (lane + 64 < nc) consider(cand_hi, s_hi);
+          } else {
+            for (int c = lane; c < nc; c += 64) consider(s_clist[w][c], s_isum[w][c + 1]);
+            __builtin_amdgcn_wave_barrier();
+          }
 #pragma unroll
           for (int o = 32; o > 0; o >>= 1) {
             const int64_t od = __shfl_xor(bd, o, 64);
@@ -547,7 +569,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
             if (cu != cv) x[r] = cu;
           }
         }
-        if (a.dirty && lane == 0) a.cnum[v] = -1;
       }
     }
 
@@ -590,6 +611,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
       evals += ncand;
       boundary += ncand > 0;
       wide += ncand > kTileCandAvg;
+      if (LIST && a.dirty) {  // nothing kept: scored anew next pass
+        a.cnum[v] = -1;
+        a.slack[v] = -1;
+      }
       const bool p = ncand > 0 && bestd < 0;
       a.prop[v] = p ? bestx : kNone;
       if (p) {
@@ -657,7 +682,7 @@ __device__ inline void tile_clusters(const PassArgs& a, const int (&tl)[U], cons
 template <int TK, int TV, int NR>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8)))
 void k_score_tile(PassArgs a) {
-  if (a.ctl->done) return;
+  if (a.ctl->done || a.ctl->stage) return;
   constexpr int kPairMax = kSetSlots + TV;  // every candidate plus one own pair per vertex
   constexpr int kProbeRegs = NR > 0 ? NR : 1;       // labels per lane when k <= 16 NR
   constexpr int kProbeBatch = NR > 2 || NR == 0 || TK == kHashed ? 4 : 8;  // pairs in flight
@@ -842,10 +867,12 @@ void k_score_tile(PassArgs a) {
     // cache the sets found this pass (interior vertices cache "none")
     if (a.dirty && t < nv && !s_clean[t]) {
       const int64_t v = v0 + t;
-      if (def || nc > kCacheCand) {
+      if (def) {
         a.cnum[v] = -1;
       } else {
-        for (int j = 0; j < nc; ++j) a.ccache[v * kCacheCand + j] = s_cl[coff + 1 + j] & 0xffffff;
+        if (nc <= kCacheCand)
+          for (int j = 0; j < nc; ++j)
+            a.ccache[v * kCacheCand + j] = s_cl[coff + 1 + j] & 0xffffff;
         a.cnum[v] = nc;
       }
     }
@@ -985,6 +1012,38 @@ void k_score_tile(PassArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// Dirty marks where the graph is not known to be symmetric: eight lanes a
+// vertex look up whether it or one of its neighbours moved in the previous
+// pass (a bit a vertex: 125 KiB for 1 M vertices).  Where more than an eighth
+// of the vertices moved nearly all are dirty, and all are marked unread.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kBlock) void k_pull(PassArgs a) {
+  const Ctl* ctl = a.ctl;
+  if (ctl->done || ctl->stage) return;
+  const int64_t n = a.n;
+  if ((int64_t)ctl->last_moves * 8 > n) {
+    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
+         v += (int64_t)gridDim.x * kBlock)
+      a.dirty[v] = 1;
+    return;
+  }
+  constexpr int G = 8;
+  const int lane = threadIdx.x & (G - 1);
+  const int64_t ngroups = (int64_t)gridDim.x * kBlock / G;
+  for (int64_t v = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / G; v < n; v += ngroups) {
+    const int64_t beg = a.row_ptr[v], end = a.row_ptr[v + 1];
+    int32_t hit = lane == 0 ? (int32_t)(a.moved[v >> 5] >> (v & 31)) & 1 : 0;
+    for (int64_t j = beg + lane; j < end; j += 2 * G) {
+      const int32_t u = a.col[j], w = a.col[j + G < end ? j + G : j];
+      hit |= (int32_t)((a.moved[u >> 5] >> (u & 31)) | (a.moved[w >> 5] >> (w & 31))) & 1;
+    }
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) hit |= __shfl_xor(hit, o, G);
+    if (lane == 0) a.dirty[v] = hit;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Status of every vertex at the start of a pass (with the candidate cache),
 // one thread per vertex.  A vertex is settled here when it has no candidate
 // (a clean vertex whose cached set is empty) or when the bound on the
@@ -994,18 +1053,21 @@ void k_score_tile(PassArgs a) {
 // vertex goes to the rescoring list.  Also clears this pass's dirty marks
 // and the per-cluster move counts the coming apply fills.
 // ---------------------------------------------------------------------------
+template <int V>  // vertices per thread and chunk: v = c0 + j kBlock + t
 __global__ __launch_bounds__(kBlock) void k_status(PassArgs a) {
   Ctl* ctl = a.ctl;
-  if (ctl->done) return;
+  if (ctl->done || ctl->stage) return;
   __shared__ int32_t s_base;
   const int par = ctl->passes & 1;
   const int32_t* churn = a.churn + (int64_t)par * a.K0;
   int32_t* next = a.churn + (int64_t)(par ^ 1) * a.K0;
+  const int32_t churn_max = ctl->churn_max;
   const int t = threadIdx.x;
-  for (int64_t x = (int64_t)blockIdx.x * kBlock + t; x < a.K0; x += (int64_t)gridDim.x * kBlock)
-    next[x] = 0;
+  const int64_t t0 = (int64_t)blockIdx.x * kBlock + t, T = (int64_t)gridDim.x * kBlock;
+  for (int64_t x = t0; x < a.K0; x += T) next[x] = 0;
+  if (a.moved)
+    for (int64_t w = t0; w < (a.n + 31) / 32; w += T) a.moved[w] = 0;
   const int32_t k = a.k;
-  constexpr int V = 4;  // vertices per thread and chunk: v = c0 + j kBlock + t
   constexpr int64_t kChunk = (int64_t)V * kBlock;
   int64_t evals = 0, skipped = 0, boundary = 0;
   for (int64_t c0 = (int64_t)blockIdx.x * kChunk; c0 < a.n; c0 += (int64_t)gridDim.x * kChunk) {
@@ -1031,26 +1093,33 @@ __global__ __launch_bounds__(kBlock) void k_status(PassArgs a) {
       stv[j] = -1;
       if (v >= a.n) continue;
       if (d[j]) a.dirty[v] = 0;  // this pass's moves mark it again
-      const int32_t cached = d[j] ? -1 : cn[j];
-      if (cached == 0) {
+      const int32_t known = d[j] ? -1 : cn[j];
+      if (known == 0) {
         a.prop[v] = kNone;
-      } else if (cached > 0) {
-        stv[j] = cached;
+      } else if (known > 0) {
+        stv[j] = known <= kCacheCand ? known : 0;
         if (sl[j] >= 0) {
-          const int4* cc = reinterpret_cast<const int4*>(a.ccache + v * kCacheCand);
-          const int4 c_lo = cc[0], c_hi = cached > 4 ? cc[1] : make_int4(0, 0, 0, 0);
-          const int32_t ids[kCacheCand] = {c_lo.x, c_lo.y, c_lo.z, c_lo.w,
-                                           c_hi.x, c_hi.y, c_hi.z, c_hi.w};
-          int32_t mx = 0;
-#pragma unroll
-          for (int q = 0; q < kCacheCand; ++q)
-            if (q < cached) mx = max(mx, churn[ids[q]]);
-          const int64_t bound = (int64_t)k * ((int64_t)churn[cv[j]] + mx);
+          // the candidates' largest move count, by the cheap bound first
+          const int64_t own = churn[cv[j]];
+          int64_t bound = (int64_t)k * (own + churn_max);
+          if ((int64_t)sl[j] < bound && known <= kCacheCand) {
+            const int4* cc = reinterpret_cast<const int4*>(a.ccache + v * kCacheCand);
+            int32_t mx = 0;
+            for (int q = 0; 4 * q < known; ++q) {
+              const int4 c = cc[q];
+              const int32_t left = known - 4 * q;
+              mx = max(mx, churn[c.x]);
+              if (left > 1) mx = max(mx, churn[c.y]);
+              if (left > 2) mx = max(mx, churn[c.z]);
+              if (left > 3) mx = max(mx, churn[c.w]);
+            }
+            bound = (int64_t)k * (own + mx);
+          }
           if ((int64_t)sl[j] >= bound) {  // no candidate's gain can have become negative
             a.slack[v] = (int32_t)(sl[j] - bound);
             a.prop[v] = kNone;
-            evals += cached;
-            skipped += cached;
+            evals += known;
+            skipped += known;
             boundary += 1;
             stv[j] = -1;
           }
@@ -1091,7 +1160,7 @@ constexpr int kListLanes = 16;
 template <int CN, int TK>
 __global__ __launch_bounds__(kBlock) void k_score_list(PassArgs a) {
   Ctl* ctl = a.ctl;
-  if (ctl->done) return;
+  if (ctl->done || ctl->stage) return;
   const int32_t count = ctl->rescore_count;
   if (count == 0 || count > a.sparse_max) return;  // the tiled scorer takes dense passes
   constexpr int G = kListLanes;
@@ -1146,7 +1215,7 @@ __global__ __launch_bounds__(kBlock) void k_score_list(PassArgs a) {
         }
         if (!defer) {  // the set found, cached for later passes
           if (lane < min(nc, kCacheCand)) a.ccache[v * kCacheCand + lane] = cand;
-          if (lane == 0) a.cnum[v] = nc <= kCacheCand ? nc : -1;
+          if (lane == 0) a.cnum[v] = nc;
         }
       }
     }
@@ -1223,15 +1292,39 @@ __global__ __launch_bounds__(kBlock) void k_score_list(PassArgs a) {
   flush_counts(a, evals, nprop, boundary, 0, wide);
 }
 
-__global__ void k_begin(Ctl* ctl, int64_t* pc) {
-  if (ctl->done) return;
+// True in every thread of the last of `total` workgroups to get here (each
+// calls it once, after its last global update; `which`: the ticket).  Every
+// wave waits until its updates have been performed (the barrier alone does
+// not wait for global memory); what the other workgroups added with atomics
+// is then read with atomics (now()), so no cache is flushed or invalidated.
+__device__ inline bool last_workgroup(const PassArgs& a, int which, int32_t total) {
+  __shared__ int32_t s_last;
+  int32_t* ticket =
+      reinterpret_cast<int32_t*>(a.pc + (kPassCounters + which) * kCounterStride);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    s_last = atomicAdd(ticket, 1) == total - 1;
+    if (s_last) atomicExch(ticket, 0);
+  }
+  __syncthreads();
+  return s_last;
+}
+
+template <typename T>
+__device__ inline T now(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The pass's counters folded into the control block (one thread).
+__device__ inline void pass_begin(const PassArgs& a) {
+  Ctl* ctl = a.ctl;
   int64_t c[kPassCounters];
 #pragma unroll
   for (int j = 0; j < kPassCounters; ++j) {
-    c[j] = pc[j * kCounterStride];
-    pc[j * kCounterStride] = 0;
+    c[j] = a.pc[j * kCounterStride];
+    a.pc[j * kCounterStride] = 0;
   }
-  ctl->pass_evals = c[0];
   ctl->nprop = (int32_t)c[1];
   ctl->boundary += c[2];
   ctl->skipped += c[3];
@@ -1240,18 +1333,81 @@ __global__ void k_begin(Ctl* ctl, int64_t* pc) {
   // pass skips the tiled scorer and scores every vertex by the wave
   ctl->defer_all = (2 * c[4] > c[2] && c[0] > 12 * c[2]) ? 1 : 0;
   ctl->passes += 1;
-  ctl->evals += ctl->pass_evals;
-  ctl->pass_evals = 0;
+  ctl->evals += c[0];
   ctl->dS2 = 0;
   ctl->dN2 = 0;
-  if (ctl->nprop == 0) {
+  ctl->churn_max = 0;
+  if (c[1] == 0) {
     ctl->converged = 1;
     ctl->done = 1;
+    ctl->slots += 1;
     if (ctl->trace) {
       int64_t* r = ctl->trace + (int64_t)(ctl->passes - 1) * 4;
       r[0] = 0; r[1] = 0; r[2] = 0; r[3] = ctl->O;
     }
   }
+  if (!a.hflag) return;
+  // Hashed tables: before the batch is applied, rebuild the table from the
+  // partition (the counts are a function of C alone) if the keys the batch
+  // may add could take it beyond half full.  Keys: the batch adds at most k
+  // keys per proposal; the table holds 4 n k slots or more and at most n k
+  // live keys, so after a rebuild there is always room.  Rows: a proposal
+  // adds at most its vertex's distinct label ids, at most T0 in all, over at
+  // most T0 live rows, in more than 2 T0 rows.  The first pass's table is the
+  // one just built (no key without a count), so a rebuild would not change it.
+  const int64_t adds = a.t.rows ? now(&ctl->prop_rows) : (int64_t)a.k * c[1];
+  const bool need = c[1] > 0 && ctl->passes > 1 &&
+                    (int64_t)*a.t.hocc + adds > (int64_t)((a.t.hmask + 1) / 2);
+  *a.hflag = need ? 1 : 0;
+  if (need) *a.t.hocc = 0;
+}
+
+// Keep the applied batch if it lowered the objective, else fall back (one
+// thread).
+__device__ inline void pass_decide(Ctl* ctl) {
+  const int64_t dO = (int64_t)ctl->k * now(&ctl->dS2) - 2 * now(&ctl->dN2);
+  ctl->dS2 = 0;
+  ctl->dN2 = 0;
+  if (dO < 0) {
+    ctl->fallback = 0;
+    ctl->O += dO;
+    ctl->committed = ctl->nprop;
+  } else {
+    ctl->fallback = 1;
+    ctl->fallback_rounds += 1;
+    ctl->committed = 0;
+  }
+}
+
+// End of a slot (one thread): a batch that fell back goes on in the next
+// one, else the pass is accounted.
+__device__ inline void pass_end(Ctl* ctl) {
+  ctl->slots += 1;
+  if (ctl->fallback && !ctl->stage) {
+    ctl->stage = 1;
+    return;
+  }
+  ctl->stage = 0;
+  if (ctl->fallback) ctl->O += (int64_t)ctl->k * ctl->dS2 - 2 * ctl->dN2;
+  ctl->moves += ctl->committed;
+  if (ctl->trace) {
+    int64_t* r = ctl->trace + (int64_t)(ctl->passes - 1) * 4;
+    r[0] = ctl->nprop;
+    r[1] = ctl->committed;
+    r[2] = ctl->fallback;
+    r[3] = ctl->O;
+  }
+  ctl->last_moves = ctl->committed;
+  ctl->nprop = 0;
+  ctl->committed = 0;
+  ctl->fallback = 0;
+  ctl->heavy_count = 0;
+  ctl->rescore_count = 0;
+  ctl->plist_count = 0;
+  ctl->prop_rows = 0;
+  ctl->dS2 = 0;
+  ctl->dN2 = 0;
+  if (ctl->passes >= ctl->max_rounds) ctl->done = 1;
 }
 
 // Apply the move of v (from -> to) with sign d (+1 apply, -1 undo) to the
@@ -1278,314 +1434,14 @@ __device__ inline int64_t move_counts(const PassArgs& a, int64_t v, int32_t from
   return acc;
 }
 
-// ---------------------------------------------------------------------------
-// Apply every proposal with per-workgroup aggregation.  Updates are keyed by
-// table cell (sizes use keys cells + cluster) and summed in an LDS hash
-// before one global atomic per distinct key.  Once half the slots hold keys
-// the table takes no new ones (probe runs stay short when a workgroup sees
-// many distinct keys, as on a first pass): a key not in it, or that finds no
-// free slot within kHashProbe steps, goes straight to the global counter.
-// A net update d on a counter whose previous value is `old` changes its
-// square by 2 old d + d^2, so the flush measures the objective change
-// exactly, whichever updates of a key went where.
-// ---------------------------------------------------------------------------
-constexpr int kHashSlots = 4096;
-constexpr int kHashOpen = kHashSlots / 2;  // keys the table takes
-constexpr int kHashProbe = 32;
-
-// The changes of the sums of squares caused by one global update: the
-// contingency part (n) and the size part (s).  Returned by value: pointers
-// to the caller's accumulators would keep them in scratch memory.
-struct Sq2 {
-  int64_t n, s;
-};
-
-// Keys: [0, cells) table cells, [cells, cells + K0) cluster sizes,
-// [cells + K0, cells + 2 K0) per-cluster move counts (churn_w).
-__device__ __attribute__((always_inline)) inline Sq2 agg_add(int32_t* hkey, int32_t* hval,
-                                                           int32_t* fill, const PassArgs& a,
-                                                           int32_t* churn_w, int64_t key,
-                                                           int32_t d) {
-  const int32_t k32 = (int32_t)key;
-  uint32_t h = ((uint32_t)k32 * 2654435761u) >> 20;  // 12 bits: kHashSlots
-#pragma unroll 1
-  for (int q = 0; q < kHashProbe; ++q) {
-    int32_t cur = hkey[h];
-    if (cur == -1) {
-      if (*fill >= kHashOpen) break;  // the key is not in the table
-      cur = atomicCAS(&hkey[h], -1, k32);
-      if (cur == -1) {
-        atomicAdd(fill, 1);
-        cur = k32;
-      }
-    }
-    if (cur == k32) {
-      atomicAdd(&hval[h], d);
-      return Sq2{0, 0};
-    }
-    h = (h + 1) & (kHashSlots - 1);
-  }
-  if (key < a.cells) {
-    const int32_t old = atomicAdd(counter(a.t, (uint32_t)key), d);
-    return Sq2{2 * (int64_t)old * d + 1, 0};
-  }
-  if (key < a.cells + a.K0) {
-    const int32_t old = atomicAdd(&a.s[key - a.cells], d);
-    return Sq2{0, 2 * (int64_t)old * d + 1};
-  }
-  atomicAdd(&churn_w[key - a.cells - a.K0], d);
-  return Sq2{0, 0};
-}
-
-// The proposers of the pass, in plist (order irrelevant): one atomic per
-// chunk of V kBlock vertices.
-__global__ __launch_bounds__(kBlock) void k_props(PassArgs a) {
-  Ctl* ctl = a.ctl;
-  if (ctl->done) return;
-  __shared__ int32_t s_base;
-  constexpr int V = 4;
-  constexpr int64_t kChunk = (int64_t)V * kBlock;
-  const int t = threadIdx.x;
-  int64_t rows = 0;  // hashed rows: the rows the proposals can add
-  for (int64_t c0 = (int64_t)blockIdx.x * kChunk; c0 < a.n; c0 += (int64_t)gridDim.x * kChunk) {
-    bool pr[V];
-    int32_t mine = 0;
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-      const int64_t v = c0 + j * kBlock + t;
-      pr[j] = v < a.n && a.prop[v] >= 0;
-      mine += pr[j];
-      if (pr[j] && a.rdist) rows += a.rdist[v];
-    }
-    int32_t total;
-    int32_t off = block_exclusive_scan(mine, &total);
-    if (t == 0 && total) s_base = atomicAdd(&ctl->plist_count, total);
-    __syncthreads();
-    if (total) {
-      off += s_base;
-#pragma unroll
-      for (int j = 0; j < V; ++j)
-        if (pr[j]) a.plist[off++] = (int32_t)(c0 + j * kBlock + t);
-    }
-    __syncthreads();
-  }
-  if (a.rdist) {  // one atomic per workgroup
-    __shared__ int64_t s_rows[kBlock / 64];
-    rows = wave_sum64(rows);
-    if ((t & 63) == 0) s_rows[t >> 6] = rows;
-    __syncthreads();
-    if (t == 0) {
-      int64_t tot = 0;
-      for (int j = 0; j < kBlock / 64; ++j) tot += s_rows[j];
-      if (tot) atomicAdd((unsigned long long*)&ctl->prop_rows, (unsigned long long)tot);
-    }
-  }
-}
-
-__global__ __launch_bounds__(kBlock) void k_apply_all(PassArgs a) {
-  Ctl* ctl = a.ctl;
-  if (ctl->done) return;
-  const int64_t count = ctl->plist_count;
-  const int64_t active = gridDim.x;
-  __shared__ int32_t hkey[kHashSlots];
-  __shared__ int32_t hval[kHashSlots];
-  __shared__ int32_t fill;
-  for (int j = threadIdx.x; j < kHashSlots; j += kBlock) {
-    hkey[j] = -1;
-    hval[j] = 0;
-  }
-  if (threadIdx.x == 0) fill = 0;
-  __syncthreads();
-  const int lane = threadIdx.x & 63;
-  const int64_t wave = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / 64;
-  int64_t dn2 = 0, ds2 = 0;
-  int32_t claimed = 0;
-  // moves per cluster, read by the next pass's scorer (counted over every
-  // proposal: a fallback pass commits fewer, so the count is an upper bound)
-  int32_t* churn_w = a.churn ? a.churn + (int64_t)(ctl->passes & 1) * a.K0 : nullptr;
-  // the wave serves the proposals of its 64 vertices four at a time, one
-  // per group of 16 lanes, the lanes of a group spread over the partitions
-  constexpr int kApplyLanes = 16;
-  const int grp = lane / kApplyLanes, gl = lane % kApplyLanes;
-  // the listed proposers, 64 at a time per wave of the active workgroups
-  const int64_t nact = active * (kBlock / 64);
-  for (int64_t e0 = wave * 64; e0 < count; e0 += nact * 64) {
-    const int64_t e = e0 + lane;
-    const int32_t vl = e < count ? a.plist[e] : 0;
-    const int32_t p = e < count ? a.prop[vl] : kNone;
-    uint64_t mask = __ballot(p >= 0);
-    while (mask) {
-      uint64_t m = mask;  // this group's proposal: the grp-th selected entry
-      for (int q = 0; q < grp; ++q) m &= m - 1;
-      const int b = m ? __ffsll((unsigned long long)m) - 1 : -1;
-      for (int q = 0; q < 64 / kApplyLanes; ++q) mask &= mask - 1;
-      const int32_t to = __shfl(p, b < 0 ? 0 : b, 64);
-      const int64_t w = __shfl(vl, b < 0 ? 0 : b, 64);
-      if (b < 0) continue;
-      const int32_t from = a.C[w];
-      const int32_t* row = a.Lvm + w * a.k;
-      for (int i = gl; i < a.k; i += kApplyLanes) {
-        const int32_t l = row[i];
-        const Sq2 up =
-            agg_add(hkey, hval, &fill, a, churn_w, cell_upd(a.t, i, to, l, claimed), +1);
-        const Sq2 dn =
-            agg_add(hkey, hval, &fill, a, churn_w, cell_upd(a.t, i, from, l, claimed), -1);
-        dn2 += up.n + dn.n;
-      }
-      if (gl == 0) {
-        const Sq2 up = agg_add(hkey, hval, &fill, a, churn_w, a.cells + to, +1);
-        const Sq2 dn = agg_add(hkey, hval, &fill, a, churn_w, a.cells + from, -1);
-        ds2 += up.s + dn.s;
-      } else if (gl == 1 && churn_w) {
-        agg_add(hkey, hval, &fill, a, churn_w, a.cells + a.K0 + to, +1);
-        agg_add(hkey, hval, &fill, a, churn_w, a.cells + a.K0 + from, +1);
-      }
-    }
-  }
-  __syncthreads();
-  for (int j = threadIdx.x; j < kHashSlots; j += kBlock) {
-    const int32_t key = hkey[j], d = hval[j];
-    if (key < 0 || d == 0) continue;
-    if (key < a.cells) {
-      const int32_t old = atomicAdd(counter(a.t, (uint32_t)key), d);
-      dn2 += 2 * (int64_t)old * d + (int64_t)d * d;
-    } else if (key < a.cells + a.K0) {
-      const int32_t old = atomicAdd(&a.s[key - a.cells], d);
-      ds2 += 2 * (int64_t)old * d + (int64_t)d * d;
-    } else {
-      atomicAdd(&churn_w[key - a.cells - a.K0], d);
-    }
-  }
-  if (a.t.hashed) flush_claims(a.t, claimed);
-  dn2 = wave_sum64(dn2);
-  ds2 = wave_sum64(ds2);
-  if (lane == 0) {
-    if (dn2) atomicAdd((unsigned long long*)&ctl->dN2, (unsigned long long)dn2);
-    if (ds2) atomicAdd((unsigned long long*)&ctl->dS2, (unsigned long long)ds2);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Batch apply for dense tables whose per-partition slice fits in LDS.  The
-// grid is (slices, k): workgroup (p, i) takes slice p of the listed
-// proposals and histograms partition i's count changes in LDS, +1 at
-// (to, l) and -1 at (from, l) with l the mover's label in partition i; then
-// it adds every nonzero change to the table with one atomic, whose returned
-// value gives the cell's exact share of the change of the sum of squares
-// (2 old d + d^2 for each addition, which sums to the exact change whatever
-// the order).  The workgroups of partition 0 do the same for the cluster
-// sizes and count the moves per cluster (churn).  Late passes, whose few
-// proposals mostly move between the same clusters, run one slice: each
-// counter then receives one atomic.
-// ---------------------------------------------------------------------------
-constexpr int kDeltaPerSlice = 2048;  // proposals per slice of the list
-constexpr int kDeltaUnroll = 4;
-
-template <bool IL>
-__global__ __launch_bounds__(kBlock) void k_apply_delta(PassArgs a) {
-  extern __shared__ int32_t sh[];
-  Ctl* ctl = a.ctl;
-  if (ctl->done) return;
-  const int64_t count = ctl->plist_count;
-  const int64_t active = min((int64_t)gridDim.x,
-                             max((int64_t)1, (count + kDeltaPerSlice - 1) / kDeltaPerSlice));
-  const int p = blockIdx.x, i = blockIdx.y, t = threadIdx.x;
-  if (p >= active || count == 0) return;
-  const int32_t k = a.k, K0 = a.K0;
-  const int32_t Li = IL ? a.t.Lmax : a.t.L[i];
-  const int32_t cells = K0 * Li;  // fits in LDS (checked by the host)
-  const bool sizes = i == 0;
-  int32_t* hd = sh;
-  int32_t* hs = sh + cells;
-  int32_t* hc = hs + K0;
-  const int32_t zero_len = sizes ? cells + 2 * K0 : cells;
-  for (int32_t j = t; j < zero_len; j += kBlock) sh[j] = 0;
-  __syncthreads();
-  const int64_t per = (count + active - 1) / active;
-  const int64_t eb = (int64_t)p * per, ee = min(count, eb + per);
-  for (int64_t e0 = eb + t; e0 < ee; e0 += (int64_t)kDeltaUnroll * kBlock) {
-    int32_t vv[kDeltaUnroll], to[kDeltaUnroll], fr[kDeltaUnroll], lb[kDeltaUnroll];
-#pragma unroll
-    for (int q = 0; q < kDeltaUnroll; ++q) {
-      const int64_t e = e0 + (int64_t)q * kBlock;
-      vv[q] = e < ee ? a.plist[e] : -1;
-    }
-#pragma unroll
-    for (int q = 0; q < kDeltaUnroll; ++q) {
-      if (vv[q] < 0) continue;
-      to[q] = a.prop[vv[q]];
-      fr[q] = a.C[vv[q]];
-      lb[q] = a.Lvm[(int64_t)vv[q] * k + i];
-    }
-#pragma unroll
-    for (int q = 0; q < kDeltaUnroll; ++q) {
-      if (vv[q] < 0) continue;
-      atomicAdd(&hd[to[q] * Li + lb[q]], 1);
-      atomicAdd(&hd[fr[q] * Li + lb[q]], -1);
-      if (sizes) {
-        atomicAdd(&hs[to[q]], 1);
-        atomicAdd(&hs[fr[q]], -1);
-        atomicAdd(&hc[to[q]], 1);
-        atomicAdd(&hc[fr[q]], 1);
-      }
-    }
-  }
-  __syncthreads();
-  int64_t dn2 = 0, ds2 = 0;
-  const int64_t toff = IL ? 0 : a.t.toff[i];
-  for (int32_t j0 = t; j0 < cells; j0 += kDeltaUnroll * kBlock) {
-    int32_t d[kDeltaUnroll], old[kDeltaUnroll];
-#pragma unroll
-    for (int q = 0; q < kDeltaUnroll; ++q) {
-      const int32_t j = j0 + q * kBlock;
-      d[q] = j < cells ? hd[j] : 0;
-      old[q] = 0;
-      if (d[q]) {
-        const int32_t x = j / Li, l = j - x * Li;
-        const uint32_t c = IL ? ((uint32_t)x * (uint32_t)Li + (uint32_t)l) * (uint32_t)k + i
-                              : (uint32_t)toff + (uint32_t)j;
-        old[q] = atomicAdd(&a.t.N[c], d[q]);
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < kDeltaUnroll; ++q)
-      dn2 += 2 * (int64_t)old[q] * d[q] + (int64_t)d[q] * d[q];
-  }
-  if (sizes) {
-    int32_t* churn_w = a.churn ? a.churn + (int64_t)(ctl->passes & 1) * K0 : nullptr;
-    for (int32_t x = t; x < K0; x += kBlock) {
-      const int32_t d = hs[x];
-      if (d) {
-        const int32_t old = atomicAdd(&a.s[x], d);
-        ds2 += 2 * (int64_t)old * d + (int64_t)d * d;
-      }
-      if (churn_w && hc[x]) atomicAdd(&churn_w[x], hc[x]);
-    }
-  }
-  dn2 = wave_sum64(dn2);
-  ds2 = wave_sum64(ds2);
-  __shared__ int64_t red[2][kBlock / 64];
-  if ((t & 63) == 0) {
-    red[0][t >> 6] = dn2;
-    red[1][t >> 6] = ds2;
-  }
-  __syncthreads();
-  if (t == 0) {
-    int64_t n2 = 0, s2 = 0;
-#pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) {
-      n2 += red[0][w];
-      s2 += red[1][w];
-    }
-    if (n2) atomicAdd((unsigned long long*)&ctl->dN2, (unsigned long long)n2);
-    if (s2) atomicAdd((unsigned long long*)&ctl->dS2, (unsigned long long)s2);
-  }
-}
-
 // Vertex w moved: it and its out-neighbours (its in-neighbours, the graph
 // being symmetric) recompute their candidate sets next pass.
 __device__ inline void mark_dirty(const PassArgs& a, int64_t w, int lane) {
   if (!a.dirty) return;
+  if (a.moved) {  // looked up by k_pull
+    if (lane == 0) atomicOr(&a.moved[w >> 5], 1u << (w & 31));
+    return;
+  }
   if (lane == 0) a.dirty[w] = 1;
   const int64_t b = a.row_ptr[w], e = a.row_ptr[w + 1];
   for (int64_t p = b + lane; p < e; p += 64) a.dirty[a.col[p]] = 1;
@@ -1601,17 +1457,13 @@ __device__ inline void relabel_in_arcs(const PassArgs& a, int64_t w, int32_t c, 
 // The apply-type kernels walk the vertices 64 at a time per wave: one
 // coalesced load of the proposals, a ballot, then the wave serves each
 // selected vertex with its lanes spread over the partitions.
-enum ApplyMode { kApplyAll = 0, kCommitOrElect = 1, kFallbackCommit = 2, kFallbackFinish = 3 };
+enum ApplyMode { kCommitOrElect = 1, kFallbackCommit = 2, kFallbackFinish = 3 };
 
 template <int MODE>
-__global__ __launch_bounds__(kBlock) void k_apply(PassArgs a) {
+__device__ inline void apply_walk(const PassArgs& a, int64_t wave, int64_t nwaves) {
   Ctl* ctl = a.ctl;
-  if (ctl->done) return;
-  if ((MODE == kFallbackCommit || MODE == kFallbackFinish) && !ctl->fallback) return;
   const bool fb = ctl->fallback;
   const int lane = threadIdx.x & 63;
-  const int64_t wave = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / 64;
-  const int64_t nwaves = ((int64_t)gridDim.x * kBlock) / 64;
   int64_t dn2 = 0, ds2 = 0;
   int32_t committed = 0;
   for (int64_t v0 = wave * 64; v0 < a.n; v0 += nwaves * 64) {
@@ -1627,9 +1479,7 @@ __global__ __launch_bounds__(kBlock) void k_apply(PassArgs a) {
       const int64_t w = v0 + b;
       const int32_t pw = __shfl(p, b, 64);
       const int32_t from = a.C[w];
-      if (MODE == kApplyAll) {
-        dn2 += move_counts(a, w, from, pw, +1, lane, &ds2);
-      } else if (MODE == kCommitOrElect) {
+      if (MODE == kCommitOrElect) {
         if (!fb) {
           if (lane == 0) {
             a.C[w] = pw;
@@ -1671,7 +1521,7 @@ __global__ __launch_bounds__(kBlock) void k_apply(PassArgs a) {
       }
     }
   }
-  if (MODE == kApplyAll || MODE == kFallbackCommit) {
+  if (MODE == kFallbackCommit) {
     dn2 = wave_sum64(dn2);
     ds2 = wave_sum64(ds2);
     committed = wave_sum32(committed);
@@ -1683,26 +1533,334 @@ __global__ __launch_bounds__(kBlock) void k_apply(PassArgs a) {
   }
 }
 
-// Hashed tables: before the batch is applied, rebuild the table from the
-// partition (the counts are a function of C alone) if the keys the batch may
-// add could take it beyond half full.  Keys: the batch adds at most k keys
-// per proposal; the table holds 4 n k slots or more and at most n k live
-// keys, so after a rebuild there is always room.  Rows: a proposal adds at
-// most its vertex's distinct label ids, at most T0 in all, over at most T0
-// live rows, in more than 2 T0 rows.  The first pass's table is the one
-// just built (no key without a count), so a rebuild would not change it.
-__global__ void k_hash_guard(PassArgs a, int64_t limit) {
+// ---------------------------------------------------------------------------
+// Apply every proposal with per-workgroup aggregation.  Updates are keyed by
+// table cell (sizes use keys cells + cluster) and summed in an LDS hash
+// before one global atomic per distinct key.  Once half the slots hold keys
+// the table takes no new ones (probe runs stay short when a workgroup sees
+// many distinct keys, as on a first pass): a key not in it, or that finds no
+// free slot within kHashProbe steps, goes straight to the global counter.
+// A net update d on a counter whose previous value is `old` changes its
+// square by 2 old d + d^2, so the flush measures the objective change
+// exactly, whichever updates of a key went where.
+// ---------------------------------------------------------------------------
+constexpr int kHashSlots = 4096;
+constexpr int kHashOpen = kHashSlots / 2;  // keys the table takes
+constexpr int kHashProbe = 32;
+
+// The changes of the sums of squares caused by one global update: the
+// contingency part (n) and the size part (s).  Returned by value: pointers
+// to the caller's accumulators would keep them in scratch memory.
+struct Sq2 {
+  int64_t n, s;
+  int32_t churn;  // a cluster's move count after the update, else 0
+};
+
+// Keys: [0, cells) table cells, [cells, cells + K0) cluster sizes,
+// [cells + K0, cells + 2 K0) per-cluster move counts (churn_w).
+__device__ __attribute__((always_inline)) inline Sq2 agg_add(int32_t* hkey, int32_t* hval,
+                                                           int32_t* fill, bool direct,
+                                                           const PassArgs& a, int32_t* churn_w,
+                                                           int64_t key, int32_t d) {
+  const int32_t k32 = (int32_t)key;
+  uint32_t h = ((uint32_t)k32 * 2654435761u) >> 20;  // 12 bits: kHashSlots
+  const int probes = direct ? 0 : kHashProbe;
+#pragma unroll 1
+  for (int q = 0; q < probes; ++q) {
+    int32_t cur = hkey[h];
+    if (cur == -1) {
+      if (*fill >= kHashOpen) break;  // the key is not in the table
+      cur = atomicCAS(&hkey[h], -1, k32);
+      if (cur == -1) {
+        atomicAdd(fill, 1);
+        cur = k32;
+      }
+    }
+    if (cur == k32) {
+      atomicAdd(&hval[h], d);
+      return Sq2{0, 0, 0};
+    }
+    h = (h + 1) & (kHashSlots - 1);
+  }
+  if (key < a.cells) {
+    const int32_t old = atomicAdd(counter(a.t, (uint32_t)key), d);
+    return Sq2{2 * (int64_t)old * d + 1, 0, 0};
+  }
+  if (key < a.cells + a.K0) {
+    const int32_t old = atomicAdd(&a.s[key - a.cells], d);
+    return Sq2{0, 2 * (int64_t)old * d + 1, 0};
+  }
+  return Sq2{0, 0, atomicAdd(&churn_w[key - a.cells - a.K0], d) + d};
+}
+
+// The proposers of the pass, in plist (order irrelevant): one atomic per
+// chunk of V kBlock vertices.
+__global__ __launch_bounds__(kBlock) void k_props(PassArgs a) {
   Ctl* ctl = a.ctl;
-  if (ctl->done) {
-    *a.hflag = 0;
+  if (ctl->done || ctl->stage) {
+    if (a.hflag && blockIdx.x == 0 && threadIdx.x == 0) *a.hflag = 0;
     return;
   }
-  // keys the batch may add: k a proposal, or for hashed rows the distinct
-  // label ids of the proposers (the rows a move can add)
-  const int64_t adds = a.t.rows ? ctl->prop_rows : (int64_t)a.k * ctl->nprop;
-  const bool need = ctl->passes > 1 && (int64_t)*a.t.hocc + adds > limit;
-  *a.hflag = need ? 1 : 0;
-  if (need) *a.t.hocc = 0;
+  __shared__ int32_t s_base;
+  constexpr int V = 4;
+  constexpr int64_t kChunk = (int64_t)V * kBlock;
+  const int t = threadIdx.x;
+  int64_t rows = 0;  // hashed rows: the rows the proposals can add
+  for (int64_t c0 = (int64_t)blockIdx.x * kChunk; c0 < a.n; c0 += (int64_t)gridDim.x * kChunk) {
+    bool pr[V];
+    int32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      const int64_t v = c0 + j * kBlock + t;
+      pr[j] = v < a.n && a.prop[v] >= 0;
+      mine += pr[j];
+      if (pr[j] && a.rdist) rows += a.rdist[v];
+    }
+    int32_t total;
+    int32_t off = block_exclusive_scan(mine, &total);
+    if (t == 0 && total) s_base = atomicAdd(&ctl->plist_count, total);
+    __syncthreads();
+    if (total) {
+      off += s_base;
+#pragma unroll
+      for (int j = 0; j < V; ++j)
+        if (pr[j]) a.plist[off++] = (int32_t)(c0 + j * kBlock + t);
+    }
+    __syncthreads();
+  }
+  if (a.rdist) {  // one atomic per workgroup
+    __shared__ int64_t s_rows[kBlock / 64];
+    rows = wave_sum64(rows);
+    if ((t & 63) == 0) s_rows[t >> 6] = rows;
+    __syncthreads();
+    if (t == 0) {
+      int64_t tot = 0;
+      for (int j = 0; j < kBlock / 64; ++j) tot += s_rows[j];
+      if (tot) atomicAdd((unsigned long long*)&ctl->prop_rows, (unsigned long long)tot);
+    }
+  }
+  if (last_workgroup(a, 0, (int32_t)gridDim.x) && t == 0) pass_begin(a);
+}
+
+__global__ __launch_bounds__(kBlock) void k_apply_all(PassArgs a) {
+  Ctl* ctl = a.ctl;
+  if (ctl->done || ctl->stage) return;
+  const int lane = threadIdx.x & 63;
+  __shared__ int32_t hkey[kHashSlots];
+  __shared__ int32_t hval[kHashSlots];
+  __shared__ int32_t fill;
+  // the workgroup's share of the listed proposals: one per group of 16
+  // lanes at least, the lanes of a group spread over the partitions
+  constexpr int kApplyLanes = 16, kGroups = kBlock / kApplyLanes;
+  const int64_t count = ctl->plist_count;
+  const int64_t per = max((int64_t)kGroups, (count + gridDim.x - 1) / gridDim.x);
+  const int64_t eb = blockIdx.x * per, ee = min(count, eb + per);
+  if (eb < ee) {
+    // one proposal a group: little to merge, the updates go straight to the
+    // counters
+    const bool direct = per == kGroups;
+    if (!direct)
+      for (int j = threadIdx.x; j < kHashSlots; j += kBlock) {
+        hkey[j] = -1;
+        hval[j] = 0;
+      }
+    if (threadIdx.x == 0) fill = 0;
+    __syncthreads();
+    int64_t dn2 = 0, ds2 = 0;
+    int32_t claimed = 0, cmax = 0;
+    // moves per cluster, read by the next pass's scorer (counted over every
+    // proposal: a fallback pass commits fewer, so the count is an upper bound)
+    int32_t* churn_w = a.churn ? a.churn + (int64_t)(ctl->passes & 1) * a.K0 : nullptr;
+    const int gl = lane % kApplyLanes;
+    for (int64_t e = eb + threadIdx.x / kApplyLanes; e < ee; e += kGroups) {
+      const int64_t w = a.plist[e];
+      const int32_t to = a.prop[w], from = a.C[w];
+      const int32_t* row = a.Lvm + w * a.k;
+      for (int i = gl; i < a.k; i += kApplyLanes) {
+        const int32_t l = row[i];
+        const Sq2 up =
+            agg_add(hkey, hval, &fill, direct, a, churn_w, cell_upd(a.t, i, to, l, claimed), +1);
+        const Sq2 dn =
+            agg_add(hkey, hval, &fill, direct, a, churn_w, cell_upd(a.t, i, from, l, claimed), -1);
+        dn2 += up.n + dn.n;
+      }
+      if (gl == 0) {
+        const Sq2 up = agg_add(hkey, hval, &fill, direct, a, churn_w, a.cells + to, +1);
+        const Sq2 dn = agg_add(hkey, hval, &fill, direct, a, churn_w, a.cells + from, -1);
+        ds2 += up.s + dn.s;
+      } else if (gl == 1 && churn_w) {
+        cmax = max(cmax, agg_add(hkey, hval, &fill, direct, a, churn_w, a.cells + a.K0 + to, +1).churn);
+        cmax = max(cmax, agg_add(hkey, hval, &fill, direct, a, churn_w, a.cells + a.K0 + from, +1).churn);
+      }
+    }
+    __syncthreads();
+    for (int j = threadIdx.x; j < kHashSlots && !direct; j += kBlock) {
+      const int32_t key = hkey[j], d = hval[j];
+      if (key < 0 || d == 0) continue;
+      if (key < a.cells) {
+        const int32_t old = atomicAdd(counter(a.t, (uint32_t)key), d);
+        dn2 += 2 * (int64_t)old * d + (int64_t)d * d;
+      } else if (key < a.cells + a.K0) {
+        const int32_t old = atomicAdd(&a.s[key - a.cells], d);
+        ds2 += 2 * (int64_t)old * d + (int64_t)d * d;
+      } else {
+        cmax = max(cmax, atomicAdd(&churn_w[key - a.cells - a.K0], d) + d);
+      }
+    }
+    if (a.t.hashed) flush_claims(a.t, claimed);
+    dn2 = wave_sum64(dn2);
+    ds2 = wave_sum64(ds2);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) cmax = max(cmax, __shfl_xor(cmax, o, 64));
+    if (lane == 0) {
+      if (dn2) atomicAdd((unsigned long long*)&ctl->dN2, (unsigned long long)dn2);
+      if (ds2) atomicAdd((unsigned long long*)&ctl->dS2, (unsigned long long)ds2);
+      if (cmax) atomicMax(&ctl->churn_max, cmax);
+    }
+  }
+  if (last_workgroup(a, 1, (int32_t)gridDim.x) && threadIdx.x == 0) pass_decide(ctl);
+}
+
+// ---------------------------------------------------------------------------
+// Batch apply for dense tables whose per-partition slice fits in LDS.  The
+// grid is (slices, k): workgroup (p, i) takes slice p of the listed
+// proposals and histograms partition i's count changes in LDS, +1 at
+// (to, l) and -1 at (from, l) with l the mover's label in partition i; then
+// it adds every nonzero change to the table with one atomic, whose returned
+// value gives the cell's exact share of the change of the sum of squares
+// (2 old d + d^2 for each addition, which sums to the exact change whatever
+// the order).  The workgroups of partition 0 do the same for the cluster
+// sizes and count the moves per cluster (churn).  Late passes, whose few
+// proposals mostly move between the same clusters, run one slice: each
+// counter then receives one atomic.
+// ---------------------------------------------------------------------------
+constexpr int kDeltaPerSlice = 2048;  // proposals per slice of the list
+constexpr int kDeltaUnroll = 4;
+
+template <bool IL>
+__global__ __launch_bounds__(kBlock) void k_apply_delta(PassArgs a) {
+  extern __shared__ int32_t sh[];
+  Ctl* ctl = a.ctl;
+  if (ctl->done || ctl->stage) return;
+  const int p = blockIdx.x, i = blockIdx.y, t = threadIdx.x;
+  const int64_t count = ctl->plist_count;
+  const int64_t active = min((int64_t)gridDim.x,
+                             max((int64_t)1, (count + kDeltaPerSlice - 1) / kDeltaPerSlice));
+  if (p >= active) return;
+  const int32_t k = a.k, K0 = a.K0;
+  const int32_t Li = IL ? a.t.Lmax : a.t.L[i];
+  const int32_t cells = K0 * Li;  // fits in LDS (checked by the host)
+  const bool sizes = i == 0;
+  int32_t* hd = sh;
+  int32_t* hs = sh + cells;
+  int32_t* hc = hs + K0;
+  const int32_t zero_len = sizes ? cells + 2 * K0 : cells;
+  for (int32_t j = t; j < zero_len; j += kBlock) sh[j] = 0;
+  __syncthreads();
+  const int64_t per = (count + active - 1) / active;
+  const int64_t eb = (int64_t)p * per, ee = min(count, eb + per);
+  for (int64_t e0 = eb + t; e0 < ee; e0 += (int64_t)kDeltaUnroll * kBlock) {
+    int32_t vv[kDeltaUnroll], to[kDeltaUnroll], fr[kDeltaUnroll], lb[kDeltaUnroll];
+#pragma unroll
+    for (int q = 0; q < kDeltaUnroll; ++q) {
+      const int64_t e = e0 + (int64_t)q * kBlock;
+      vv[q] = e < ee ? a.plist[e] : -1;
+    }
+#pragma unroll
+    for (int q = 0; q < kDeltaUnroll; ++q) {
+      if (vv[q] < 0) continue;
+      to[q] = a.prop[vv[q]];
+      fr[q] = a.C[vv[q]];
+      lb[q] = a.Lvm[(int64_t)vv[q] * k + i];
+    }
+#pragma unroll
+    for (int q = 0; q < kDeltaUnroll; ++q) {
+      if (vv[q] < 0) continue;
+      atomicAdd(&hd[to[q] * Li + lb[q]], 1);
+      atomicAdd(&hd[fr[q] * Li + lb[q]], -1);
+      if (sizes) {
+        atomicAdd(&hs[to[q]], 1);
+        atomicAdd(&hs[fr[q]], -1);
+        atomicAdd(&hc[to[q]], 1);
+        atomicAdd(&hc[fr[q]], 1);
+      }
+    }
+  }
+  __syncthreads();
+  int64_t dn2 = 0, ds2 = 0;
+  int32_t cmax = 0;
+  const int64_t toff = IL ? 0 : a.t.toff[i];
+  for (int32_t j0 = t; j0 < cells; j0 += kDeltaUnroll * kBlock) {
+    int32_t d[kDeltaUnroll], old[kDeltaUnroll];
+#pragma unroll
+    for (int q = 0; q < kDeltaUnroll; ++q) {
+      const int32_t j = j0 + q * kBlock;
+      d[q] = j < cells ? hd[j] : 0;
+      old[q] = 0;
+      if (d[q]) {
+        const int32_t x = j / Li, l = j - x * Li;
+        const uint32_t c = IL ? ((uint32_t)x * (uint32_t)Li + (uint32_t)l) * (uint32_t)k + i
+                              : (uint32_t)toff + (uint32_t)j;
+        old[q] = atomicAdd(&a.t.N[c], d[q]);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kDeltaUnroll; ++q)
+      dn2 += 2 * (int64_t)old[q] * d[q] + (int64_t)d[q] * d[q];
+  }
+  if (sizes) {
+    int32_t* churn_w = a.churn ? a.churn + (int64_t)(ctl->passes & 1) * K0 : nullptr;
+    for (int32_t x = t; x < K0; x += kBlock) {
+      const int32_t d = hs[x];
+      if (d) {
+        const int32_t old = atomicAdd(&a.s[x], d);
+        ds2 += 2 * (int64_t)old * d + (int64_t)d * d;
+      }
+      if (churn_w && hc[x]) cmax = max(cmax, atomicAdd(&churn_w[x], hc[x]) + hc[x]);
+    }
+  }
+  if (sizes && a.churn) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) cmax = max(cmax, __shfl_xor(cmax, o, 64));
+    if ((t & 63) == 0 && cmax) atomicMax(&ctl->churn_max, cmax);
+  }
+  dn2 = wave_sum64(dn2);
+  ds2 = wave_sum64(ds2);
+  __shared__ int64_t red[2][kBlock / 64];
+  if ((t & 63) == 0) {
+    red[0][t >> 6] = dn2;
+    red[1][t >> 6] = ds2;
+  }
+  __syncthreads();
+  if (t == 0) {
+    int64_t n2 = 0, s2 = 0;
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; ++w) {
+      n2 += red[0][w];
+      s2 += red[1][w];
+    }
+    if (n2) atomicAdd((unsigned long long*)&ctl->dN2, (unsigned long long)n2);
+    if (s2) atomicAdd((unsigned long long*)&ctl->dS2, (unsigned long long)s2);
+  }
+  if (last_workgroup(a, 1, (int32_t)active * a.k) && t == 0) pass_decide(ctl);
+}
+
+// The second slot's apply (a kernel of its own: inside the apply kernels its
+// registers cost them a third of their speed).
+__global__ __launch_bounds__(kBlock) void k_fallback(PassArgs a) {
+  if (a.ctl->done || !a.ctl->stage) return;
+  apply_walk<kFallbackCommit>(a, ((int64_t)blockIdx.x * kBlock + threadIdx.x) / 64,
+                              ((int64_t)gridDim.x * kBlock) / 64);
+}
+
+__global__ __launch_bounds__(kBlock) void k_commit(PassArgs a) {
+  Ctl* ctl = a.ctl;
+  if (ctl->done) return;
+  const int64_t wave = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / 64;
+  const int64_t nwaves = ((int64_t)gridDim.x * kBlock) / 64;
+  if (ctl->stage) apply_walk<kFallbackFinish>(a, wave, nwaves);
+  else apply_walk<kCommitOrElect>(a, wave, nwaves);
+  if (last_workgroup(a, 2, (int32_t)gridDim.x) && threadIdx.x == 0) pass_end(ctl);
 }
 
 __global__ __launch_bounds__(kBlock) void k_hash_reset(PassArgs a) {
@@ -1755,51 +1913,13 @@ __global__ __launch_bounds__(kBlock) void k_member_fill(PassArgs a) {
   }
 }
 
-__global__ void k_decide(Ctl* ctl) {
-  if (ctl->done) return;
-  const int64_t dO = (int64_t)ctl->k * ctl->dS2 - 2 * ctl->dN2;
-  ctl->dS2 = 0;
-  ctl->dN2 = 0;
-  if (dO < 0) {
-    ctl->fallback = 0;
-    ctl->O += dO;
-    ctl->committed = ctl->nprop;
-  } else {
-    ctl->fallback = 1;
-    ctl->fallback_rounds += 1;
-    ctl->committed = 0;
-  }
-}
-
-__global__ void k_end(Ctl* ctl) {
-  if (ctl->done) return;
-  if (ctl->fallback) ctl->O += (int64_t)ctl->k * ctl->dS2 - 2 * ctl->dN2;
-  ctl->moves += ctl->committed;
-  if (ctl->trace) {
-    int64_t* r = ctl->trace + (int64_t)(ctl->passes - 1) * 4;
-    r[0] = ctl->nprop;
-    r[1] = ctl->committed;
-    r[2] = ctl->fallback;
-    r[3] = ctl->O;
-  }
-  ctl->nprop = 0;
-  ctl->committed = 0;
-  ctl->fallback = 0;
-  ctl->heavy_count = 0;
-  ctl->rescore_count = 0;
-  ctl->plist_count = 0;
-  ctl->prop_rows = 0;
-  ctl->dS2 = 0;
-  ctl->dN2 = 0;
-  if (ctl->passes >= ctl->max_rounds) ctl->done = 1;
-}
-
-__global__ void k_ctl_init(Ctl* ctl, const int64_t* acc, int32_t k, int32_t max_rounds,
+__global__ void k_ctl_init(Ctl* ctl, const int64_t* acc, int32_t n, int32_t k, int32_t max_rounds,
                            int64_t* trace) {
   Ctl c = {};
   c.k = k;
   c.max_rounds = max_rounds;
   c.trace = trace;
+  c.last_moves = n;
   c.O = (int64_t)k * acc[0] + acc[1] - 2 * acc[2];
   *ctl = c;
 }
@@ -1844,9 +1964,9 @@ bool score_lanes_ok(int lanes) {
   return lanes == 0 || lanes == 4 || lanes == 8 || lanes == 16 || lanes == 32 || lanes == 64;
 }
 
-void launch_ctl_init(Ctl* ctl, const int64_t* acc, int32_t k, int32_t max_rounds,
+void launch_ctl_init(Ctl* ctl, const int64_t* acc, int64_t n, int32_t k, int32_t max_rounds,
                      int64_t* trace, hipStream_t st) {
-  k_ctl_init<<<1, 1, 0, st>>>(ctl, acc, k, max_rounds, trace);
+  k_ctl_init<<<1, 1, 0, st>>>(ctl, acc, (int32_t)n, k, max_rounds, trace);
 }
 
 void enqueue_pass(const PassArgs& a, int lanes, int grid_score, int grid_apply, hipStream_t st,
@@ -1859,7 +1979,12 @@ void enqueue_pass(const PassArgs& a, int lanes, int grid_score, int grid_apply, 
   if (score_begin) (void)hipEventRecord(score_begin, st);
   switch (lanes) {
     case 0:
-      if (a.st) k_status<<<grid_apply, kBlock, 0, st>>>(a);
+      if (a.moved)
+        k_pull<<<(int)std::min<int64_t>((a.n * 8 + kBlock - 1) / kBlock, a.tile_grid), kBlock, 0,
+                 st>>>(a);
+      // one vertex a thread until that fills the chip
+      if (a.st && a.n <= kSmallTileMax) k_status<1><<<grid_apply, kBlock, 0, st>>>(a);
+      else if (a.st) k_status<4><<<grid_apply, kBlock, 0, st>>>(a);
       if (a.t.hashed) launch_tile<kHashed>(a, grid_score, st);
       else if (a.t.interleaved) launch_tile<kInterleaved>(a, grid_score, st);
       else launch_tile<kBlocked>(a, grid_score, st);
@@ -1873,10 +1998,8 @@ void enqueue_pass(const PassArgs& a, int lanes, int grid_score, int grid_apply, 
     default: launch_score<64>(a, grid_score, st); break;
   }
   if (score_end) (void)hipEventRecord(score_end, st);
-  k_begin<<<1, 1, 0, st>>>(a.ctl, a.pc);
   k_props<<<grid_apply, kBlock, 0, st>>>(a);
   if (a.t.hashed) {
-    k_hash_guard<<<1, 1, 0, st>>>(a, (int64_t)((a.t.hmask + 1) / 2));
     k_hash_reset<<<grid_apply, kBlock, 0, st>>>(a);
     k_hash_refill<<<grid_apply, kBlock, 0, st>>>(a);
   }
@@ -1887,11 +2010,8 @@ void enqueue_pass(const PassArgs& a, int lanes, int grid_score, int grid_apply, 
   } else {
     k_apply_all<<<grid_apply, kBlock, 0, st>>>(a);
   }
-  k_decide<<<1, 1, 0, st>>>(a.ctl);
-  k_apply<kCommitOrElect><<<grid_apply, kBlock, 0, st>>>(a);
-  k_apply<kFallbackCommit><<<grid_apply, kBlock, 0, st>>>(a);
-  k_apply<kFallbackFinish><<<grid_apply, kBlock, 0, st>>>(a);
-  k_end<<<1, 1, 0, st>>>(a.ctl);
+  k_fallback<<<grid_apply, kBlock, 0, st>>>(a);
+  k_commit<<<grid_apply, kBlock, 0, st>>>(a);
 }
 
 }  // namespace mcc

@@ -1,0 +1,103 @@
+"""Decisions carried over between passes (candidate sets, skipped vertices)
+with and without the symmetric flag, on graphs that are not symmetric, and
+vertices with more candidates than a cache, a lane group or a key set holds:
+the whole trace against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+KEYS = ("passes", "converged", "fallback_rounds", "clusters", "moves", "candidate_evals",
+        "objective_init", "objective")
+
+
+@pytest.fixture(scope="module")
+def mcc():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2408_11331_amd as m
+    m.lib()
+    oracle.build(force=False)
+    return m
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def check(mcc, row_ptr, col, labels, init, flags=0, max_rounds=0):
+    out, st, tr = mcc.consensus(dev(row_ptr), dev(col), dev(labels),
+                                None if init is None else dev(init), flags=flags, trace=True,
+                                max_rounds=max_rounds)
+    eo, est, et = oracle.consensus(row_ptr, col, labels, init, trace=True, max_rounds=max_rounds)
+    assert np.array_equal(out.cpu().numpy(), eo)
+    assert [tuple(t) for t in et][:st["passes"]] == tr
+    for key in KEYS:
+        assert st[key] == est[key], key
+    return st
+
+
+def noisy(n, k, groups, rng):
+    base = np.arange(n) * groups // n
+    labels = np.tile(base, (k, 1))
+    noise = rng.random((k, n)) < 0.3
+    labels[noise] = rng.integers(0, groups, int(noise.sum()))
+    return labels.astype(np.int32)
+
+
+@pytest.mark.parametrize("start", ["clusters", "singletons"])
+@pytest.mark.parametrize("n,k", [(700, 5), (3001, 33), (20000, 12)])
+def test_asymmetric_graph(mcc, n, k, start):
+    print(f"[gpu-case] carry asymmetric n={n} k={k} {start}", flush=True)
+    rng = np.random.default_rng(n)
+    u, v = rng.integers(0, n, 6 * n), rng.integers(0, n, 6 * n)
+    near = rng.random(6 * n) < 0.7
+    v[near] = (u[near] + rng.integers(1, 9, int(near.sum()))) % n
+    rp, col = synth.graph.csr_from_edges(n, u, v)
+    keep = rng.random(col.size) < 0.5  # arcs without their reverse
+    src = np.repeat(np.arange(n), np.diff(rp))[keep]
+    rp = np.concatenate([[0], np.cumsum(np.bincount(src, minlength=n))]).astype(np.int64)
+    col = col[keep]
+    labels = noisy(n, k, n // 50 + 2, rng)
+    init = rng.integers(0, n // 4, n).astype(np.int32) if start == "clusters" else None
+    check(mcc, rp, col, labels, init)
+
+
+@pytest.mark.parametrize("symmetric", [False, True])
+@pytest.mark.parametrize("hashed", [False, True])
+def test_hubs(mcc, symmetric, hashed):
+    # degrees at the edges of the cached sets (16), the lists (16 lanes x 8
+    # arcs), the sets of a wave (128, 256) and its arc registers (512)
+    print(f"[gpu-case] carry hubs symmetric={symmetric} hashed={hashed}", flush=True)
+    rng = np.random.default_rng(3)
+    n, k = 4000, 9
+    degrees = [15, 16, 17, 127, 128, 129, 130, 254, 255, 256, 257, 300, 511, 512, 513, 900]
+    u, v = [np.arange(n - 1)], [np.arange(1, n)]
+    for j, d in enumerate(degrees):
+        u.append(np.full(d, j * 200))
+        v.append(1000 + rng.choice(2900, d, replace=False))
+    rp, col = synth.graph.csr_from_edges(n, np.concatenate(u), np.concatenate(v))
+    labels = noisy(n, k, 60, rng)
+    init = (np.arange(n) // 2 * 2).astype(np.int32)  # neighbours in many clusters
+    flags = (mcc.MCC_F_SYMMETRIC if symmetric else 0) | (mcc.MCC_F_HASH_TABLES if hashed else 0)
+    check(mcc, rp, col, labels, init, flags)
+
+
+@pytest.mark.parametrize("symmetric", [False, True])
+def test_many_candidates_many_partitions(mcc, symmetric):
+    # from singletons with degree 30 the first passes go to the wave scorer
+    # as a whole; with more than 64 partitions it keeps nothing
+    print(f"[gpu-case] carry k=70 singletons symmetric={symmetric}", flush=True)
+    for k in (64, 70):
+        rng = np.random.default_rng(k)
+        n = 2000
+        u, v = rng.integers(0, n, 15 * n), rng.integers(0, n, 15 * n)
+        near = rng.random(15 * n) < 0.6
+        v[near] = (u[near] + rng.integers(1, 30, int(near.sum()))) % n
+        rp, col = synth.graph.csr_from_edges(n, u, v)
+        check(mcc, rp, col, noisy(n, k, 30, rng), None,
+              mcc.MCC_F_SYMMETRIC if symmetric else 0)
