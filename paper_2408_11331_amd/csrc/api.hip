@@ -733,10 +733,10 @@ int translate(const std::exception_ptr& ep) {
   }
 }
 
-bool labels_ok(const int32_t* const* labels, int32_t k) {
+bool labels_ok(const int32_t* const* labels, int32_t k, VisibleRanges& vis) {
   if (!labels) return false;
   for (int i = 0; i < k; ++i)
-    if (!device_visible(labels[i])) return false;
+    if (!vis.check(labels[i])) return false;
   return true;
 }
 
@@ -806,20 +806,58 @@ int64_t multi_table_bound(int64_t n, int32_t k) {
 int64_t multi_bound(int64_t vertices, int64_t count, int64_t label_ptrs, int64_t table) {
   const int64_t small = 24 * (vertices + 64 * count) + count * ((int64_t)sizeof(MultiInst) +
                         (int64_t)sizeof(MultiCtl) + 12 * kMultiClusters + 4 * 256) +
-                        label_ptrs * 24 + (vertices / 256 + count) * 16;
+                        label_ptrs * 40 + (vertices / 256 + count) * 32;
   return 2 * (small + table) + ((int64_t)16 << 20);
 }
 
-// One wave: the instances probs[ids[j]], results in res[ids[j]].  Instances
-// the kernels do not take are left with their ranges known.
-void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>& ids,
-                int32_t max_rounds, bool literal, hipStream_t st, MultiResult* res,
-                int64_t* dtrace = nullptr) {
+// Host arrays gathered for one upload: a copy from pageable memory costs
+// several microseconds of host time however small it is.
+class Upload {
+ public:
+  template <class T>
+  size_t put(const std::vector<T>& v) {
+    const size_t at = (data_.size() + 15) & ~(size_t)15;
+    data_.resize(at + v.size() * sizeof(T));
+    if (!v.empty()) memcpy(data_.data() + at, v.data(), v.size() * sizeof(T));
+    return at;
+  }
+  // Overwrites an array put before.
+  template <class T>
+  void set(size_t at, const std::vector<T>& v) {
+    if (!v.empty()) memcpy(data_.data() + at, v.data(), v.size() * sizeof(T));
+  }
+  int64_t size() const { return (int64_t)data_.size(); }
+  // Copies the gathered arrays to d, in stream order.
+  void send_to(Arena& ar, unsigned char* d, hipStream_t st) const {
+    h2d(d, ar.host(data_), (int64_t)data_.size(), st);
+  }
+  // The same into room of their own.
+  unsigned char* send(Arena& ar, hipStream_t st) const {
+    unsigned char* d = ar.get<unsigned char>(size());
+    send_to(ar, d, st);
+    return d;
+  }
+
+ private:
+  std::vector<unsigned char> data_;
+};
+
+// Device state of a wave's instances, their ranges known and on the host.
+struct MultiSet {
+  std::vector<MultiInst> inst;
+  std::vector<MultiCtl> ctl;
+  MultiArgs a{};
+};
+
+// The ranges of the instances probs[ids[j]] (K0, lmax and err of ctl[j]); the
+// device copies of the instances and counters are taken with room for them.
+void multi_ranges(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>& ids,
+                  int32_t max_rounds, bool literal, bool passes, hipStream_t st, MultiSet* S) {
   const int32_t count = (int32_t)ids.size();
-  std::vector<MultiInst> hi(count);
+  S->inst.resize(count);
+  S->ctl.resize(count);
   std::vector<const int32_t*> ptrs;
   std::vector<MultiItem> labels;
-  std::vector<MultiCtl> hc(count);
   std::vector<int64_t> voff(count + 1, 0);
   int64_t n_max = 1;
   for (int32_t j = 0; j < count; ++j) {
@@ -831,20 +869,21 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
     n_max = std::max<int64_t>(n_max, p.g.n);
     // state only where the kernels may take the instance
     voff[j + 1] = voff[j] + (p.g.n <= kMultiVertices ? (p.g.n + 63) & ~(int64_t)63 : 0);
-    hc[j].lmax = -1;
+    S->ctl[j].lmax = -1;
   }
-  const int32_t** dptrs = ar.get<const int32_t*>((int64_t)ptrs.size());
-  h2d(dptrs, ar.host(ptrs), (int64_t)ptrs.size(), st);
-  MultiItem* dlabels = ar.get<MultiItem>((int64_t)labels.size());
-  h2d(dlabels, ar.host(labels), (int64_t)labels.size(), st);
   uint16_t* C = ar.get<uint16_t>(voff[count]);
   int32_t* rawid = ar.get<int32_t>(voff[count]);
-  int2* plist = ar.get<int2>(voff[count]);
-  int64_t* dprop = ar.get<int64_t>(voff[count]);
+  int2* plist = passes ? ar.get<int2>(voff[count]) : nullptr;
+  int64_t* dprop = passes ? ar.get<int64_t>(voff[count]) : nullptr;
+  Upload up;
+  const size_t at_ptrs = up.put(ptrs), at_labels = up.put(labels), at_ctl = up.put(S->ctl),
+               at_inst = up.put(S->inst);
+  unsigned char* d = ar.get<unsigned char>(up.size());
+  const int32_t* const* dptrs = reinterpret_cast<const int32_t* const*>(d + at_ptrs);
   int64_t lo = 0;
   for (int32_t j = 0; j < count; ++j) {
     const mcc_problem& p = probs[ids[j]];
-    MultiInst& m = hi[j];
+    MultiInst& m = S->inst[j];
     m.n = p.g.n;
     m.row_ptr = p.g.row_ptr;
     m.col = p.g.col;
@@ -855,23 +894,36 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
     m.k = p.k;
     m.C = C + voff[j];
     m.rawid = rawid + voff[j];
-    m.plist = plist + voff[j];
-    m.dprop = dprop + voff[j];
+    if (passes) {
+      m.plist = plist + voff[j];
+      m.dprop = dprop + voff[j];
+    }
   }
-  MultiInst* dinst = ar.get<MultiInst>(count);
-  MultiCtl* dctl = ar.get<MultiCtl>(count);
-  h2d(dinst, ar.host(hi), count, st);
-  h2d(dctl, ar.host(hc), count, st);
-  MultiArgs a{};
-  a.inst = dinst;
-  a.ctl = dctl;
-  a.count = count;
-  a.max_rounds = max_rounds;
-  a.literal = literal ? 1 : 0;
-  a.trace = dtrace;
-  launch_multi_ranges(a, dlabels, (int32_t)labels.size(), n_max, st);
-  d2h(hc.data(), dctl, count, st);
+  up.set(at_inst, S->inst);
+  up.send_to(ar, d, st);
+  S->a.inst = reinterpret_cast<const MultiInst*>(d + at_inst);
+  S->a.ctl = reinterpret_cast<MultiCtl*>(d + at_ctl);
+  S->a.count = count;
+  S->a.max_rounds = max_rounds;
+  S->a.literal = literal ? 1 : 0;
+  launch_multi_ranges(S->a, reinterpret_cast<const MultiItem*>(d + at_labels),
+                      (int32_t)labels.size(), n_max, st);
+  d2h(S->ctl.data(), S->a.ctl, count, st);
   sync(st);
+}
+
+// One wave: the instances probs[ids[j]], results in res[ids[j]].  Instances
+// the kernels do not take are left with their ranges known.
+void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>& ids,
+                int32_t max_rounds, bool literal, hipStream_t st, MultiResult* res,
+                int64_t* dtrace = nullptr) {
+  const int32_t count = (int32_t)ids.size();
+  MultiSet set;
+  multi_ranges(ar, probs, ids, max_rounds, literal, true, st, &set);
+  std::vector<MultiInst>& hi = set.inst;
+  std::vector<MultiCtl>& hc = set.ctl;
+  MultiArgs& a = set.a;
+  a.trace = dtrace;
 
   // the instances the kernels take, narrow and wide counts apart, as far as
   // the wave's table budget goes (at least one)
@@ -911,7 +963,6 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
       hi[j].owner = owner + sat[j];
       hi[j].N = N + tat[j];
     }
-  h2d(dinst, ar.host(hi), count, st);
 
   // Work lists of the live instances: partitions in two classes of slice
   // size (the LDS of build and apply is sized to the class), tiles, and the
@@ -923,9 +974,8 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
     int32_t cells[2] = {1, 1};
     int words[kMultiModes] = {};
     size_t slice[kMultiModes] = {}, table[kMultiModes] = {};
-    MultiItem* dparts[2] = {nullptr, nullptr};
-    MultiItem* dtiles[kMultiModes] = {};
-    int32_t* dids = nullptr;
+    size_t at_parts[2] = {}, at_tiles[kMultiModes] = {}, at_ids = 0;  // in the upload
+    const unsigned char* dev = nullptr;
   } W[2];
   int64_t total_n = 0;
   for (auto& l : live)
@@ -933,13 +983,8 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
   // tiles of 1024 read the table less often; 256 when those would leave
   // compute units without a tile
   const int tile = total_n >= (int64_t)1024 * 2 * device_sms() ? 1024 : 256;
-  // (the lists only shrink from one call to the next, so their device arrays
-  // are taken once)
   auto fill = [&](int w) {
     Lists x;
-    for (int c = 0; c < 2; ++c) x.dparts[c] = W[w].dparts[c];
-    for (int q = 0; q < kMultiModes; ++q) x.dtiles[q] = W[w].dtiles[q];
-    x.dids = W[w].dids;
     const size_t tsz = w ? 4 : 2;
     for (int32_t j : live[w]) {
       const MultiInst& m = hi[j];
@@ -954,22 +999,30 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
       x.slice[q] = std::max(x.slice[q], (size_t)m.cs * tsz);
       x.table[q] = std::max(x.table[q], (size_t)m.cs * tsz * (size_t)m.k);
     }
-    auto up = [&](auto*& d, const auto& v) {
-      using T = std::remove_reference_t<decltype(*d)>;
-      if (v.empty()) return;
-      if (!d) d = ar.get<T>((int64_t)v.size());
-      h2d(d, ar.host(v), (int64_t)v.size(), st);
-    };
-    for (int c = 0; c < 2; ++c) up(x.dparts[c], x.parts[c]);
-    for (int q = 0; q < kMultiModes; ++q) up(x.dtiles[q], x.tiles[q]);
-    up(x.dids, x.ids);
     W[w] = x;
   };
+  auto put = [&](int w, Upload& up) {
+    Lists& x = W[w];
+    for (int c = 0; c < 2; ++c) x.at_parts[c] = up.put(x.parts[c]);
+    for (int q = 0; q < kMultiModes; ++q) x.at_tiles[q] = up.put(x.tiles[q]);
+    x.at_ids = up.put(x.ids);
+  };
+  {  // the instances and the lists in one upload
+    Upload up;
+    up.put(hi);
+    for (int w = 0; w < 2; ++w) {
+      if (live[w].empty()) continue;
+      fill(w);
+      put(w, up);
+    }
+    const unsigned char* d = up.send(ar, st);
+    a.inst = reinterpret_cast<const MultiInst*>(d);
+    for (int w = 0; w < 2; ++w) W[w].dev = d;
+  }
+  auto items = [&](int w, size_t at) { return reinterpret_cast<const MultiItem*>(W[w].dev + at); };
   for (int w = 0; w < 2; ++w) {
-    if (live[w].empty()) continue;
-    fill(w);
     for (int c = 0; c < 2; ++c)
-      launch_multi_build(a, W[w].dparts[c], (int32_t)W[w].parts[c].size(), w != 0, W[w].cells[c],
+      launch_multi_build(a, items(w, W[w].at_parts[c]), (int32_t)W[w].parts[c].size(), w != 0, W[w].cells[c],
                          st);
   }
   int enqueued = 0, chunk = 2;
@@ -986,15 +1039,17 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
           const size_t room = tile == 256 ? (16 << 10) : (64 << 10);
           const size_t buf =
               md == kMultiDirect ? 0 : std::max(x.slice[md], std::min(x.table[md], room));
-          launch_multi_score(a, x.dtiles[md], (int32_t)x.tiles[md].size(), w != 0, md, tile,
+          launch_multi_score(a, items(w, x.at_tiles[md]), (int32_t)x.tiles[md].size(), w != 0, md, tile,
                              x.words[md], buf, st);
         }
         for (int c = 0; c < 2; ++c)
-          launch_multi_apply(a, x.dparts[c], (int32_t)x.parts[c].size(), w != 0, x.cells[c], st);
-        launch_multi_commit(a, x.dids, (int32_t)x.ids.size(), w != 0, st);
+          launch_multi_apply(a, items(w, x.at_parts[c]), (int32_t)x.parts[c].size(), w != 0,
+                             x.cells[c], st);
+        launch_multi_commit(a, reinterpret_cast<const int32_t*>(x.dev + x.at_ids),
+                            (int32_t)x.ids.size(), w != 0, st);
       }
     enqueued += todo;
-    d2h(hc.data(), dctl, count, st);
+    d2h(hc.data(), a.ctl, count, st);
     sync(st);
     bool any = false;
     for (int w = 0; w < 2; ++w) {  // the instances still running
@@ -1010,6 +1065,11 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
           }
         live[w] = rest;
         fill(w);
+        if (!rest.empty()) {
+          Upload up;
+          put(w, up);
+          W[w].dev = up.send(ar, st);
+        }
       }
     }
     if (!any) break;
@@ -1020,6 +1080,42 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
       res[ids[j]].solved = true;
       res[ids[j]].ctl = hc[j];
     }
+}
+
+// The table of one small instance with few clusters (`init` against k
+// partitions): the objective without any pass, for the evaluation calls.
+// False when the kernels do not take it (an id outside [0, n) among the
+// reasons) and nothing was computed.
+bool multi_table(Arena& ar, const int32_t* const* labels, int32_t k, int64_t n,
+                 const int32_t* init, hipStream_t st, MultiSet* S) {
+  if (n > kMultiVertices || k > 256) return false;
+  mcc_problem one{};
+  one.g.n = n;
+  one.labels = labels;
+  one.k = k;
+  one.init = init;
+  multi_ranges(ar, &one, {0}, 1, false, false, st, S);
+  MultiInst& m = S->inst[0];
+  const int64_t Ls = (int64_t)S->ctl[0].lmax + 1;
+  if (S->ctl[0].err || !multi_fits(n, S->ctl[0].K0, Ls)) return false;
+  m.K0 = S->ctl[0].K0;
+  m.Ls = (int32_t)Ls;
+  m.rs = multi_row(n, m.K0);
+  m.cs = m.rs * m.Ls;
+  m.s = ar.get<int32_t>(m.K0);
+  m.owner = ar.get<uint64_t>(m.K0);
+  m.N = ar.get<unsigned char>(multi_table_bytes(n, k, m.K0, m.Ls));
+  std::vector<MultiItem> parts;
+  for (int32_t i = 0; i < k; ++i) parts.push_back({0, i});
+  Upload up;
+  up.put(S->inst);
+  const size_t at = up.put(parts);
+  const unsigned char* d = up.send(ar, st);
+  S->a.inst = reinterpret_cast<const MultiInst*>(d);
+  launch_multi_build(S->a, reinterpret_cast<const MultiItem*>(d + at), k, n >= (1 << 15),
+                     m.K0 * m.Ls, st);
+  d2h(S->ctl.data(), S->a.ctl, 1, st);
+  return true;
 }
 
 void multi_stats(const MultiCtl& c, mcc_stats* o) {
@@ -1076,8 +1172,9 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     }
     return MCC_OK;
   }
-  if (!device_visible(g->row_ptr) || (g->nnz > 0 && !device_visible(g->col)) ||
-      !device_visible(out) || (init && !device_visible(init)) || !labels_ok(labels, k))
+  VisibleRanges vis;
+  if (!vis.check(g->row_ptr) || (g->nnz > 0 && !vis.check(g->col)) || !vis.check(out) ||
+      (init && !vis.check(init)) || !labels_ok(labels, k, vis))
     return MCC_EINVAL;
 
   hipStream_t st = stats ? (hipStream_t)stats->stream : nullptr;
@@ -1085,19 +1182,19 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
   if (noalloc && (uint64_t)(4 * n * (int64_t)k + 48 * n) > kScratchBytes) return MCC_ESCRATCH;
   try {
     Arena ar(st, noalloc ? scratch_address() : nullptr, kScratchBytes);
-    hipEvent_t e0, e1, e2, e3;
-    HIPCK(hipEventCreate(&e0));
-    HIPCK(hipEventCreate(&e1));
-    HIPCK(hipEventCreate(&e2));
-    HIPCK(hipEventCreate(&e3));
-    struct Ev {
-      hipEvent_t* e;
-      ~Ev() {
-        for (int j = 0; j < 4; ++j) (void)hipEventDestroy(e[j]);
+    struct Events {
+      std::vector<hipEvent_t> e;
+      hipEvent_t make() {
+        hipEvent_t x;
+        HIPCK(hipEventCreate(&x));
+        e.push_back(x);
+        return x;
       }
-    };
-    hipEvent_t evs[4] = {e0, e1, e2, e3};
-    Ev guard{evs};
+      ~Events() {
+        for (hipEvent_t x : e) (void)hipEventDestroy(x);
+      }
+    } events;
+    const hipEvent_t e0 = events.make(), e3 = events.make();
     HIPCK(hipEventRecord(e0, st));
 
     // a small instance with few clusters: the level-by-level kernels, three
@@ -1129,6 +1226,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
       ar.rewind(before);  // the scratch array holds what it held without the attempt
     }
 
+    const hipEvent_t e1 = events.make(), e2 = events.make();
     std::vector<const int32_t*> hptrs(labels, labels + k);
     Solve S;
     build_solve(ar, hptrs, n, init, true, (flags & MCC_F_VALIDATE) ? g : nullptr, &S, st,
@@ -1367,10 +1465,17 @@ int mcc_objective(const int32_t* c, const int32_t* const* labels, int32_t k, int
     *result = 0;
     return MCC_OK;
   }
-  if (!device_visible(c) || !labels_ok(labels, k)) return MCC_EINVAL;
+  VisibleRanges vis;
+  if (!vis.check(c) || !labels_ok(labels, k, vis)) return MCC_EINVAL;
   hipStream_t st = (hipStream_t)stream;
   try {
     Arena ar(st);
+    MultiSet small;
+    if (multi_table(ar, labels, k, n, c, st, &small)) {
+      sync(st);
+      *result = small.ctl[0].O;
+      return MCC_OK;
+    }
     std::vector<const int32_t*> hptrs(labels, labels + k);
     Solve S;
     build_solve(ar, hptrs, n, c, false, nullptr, &S, st);
@@ -1394,6 +1499,12 @@ int mcc_mirkin(const int32_t* a, const int32_t* b, int64_t n, int64_t* result, v
   hipStream_t st = (hipStream_t)stream;
   try {
     Arena ar(st);
+    MultiSet small;
+    if (multi_table(ar, &b, 1, n, a, st, &small)) {
+      sync(st);
+      *result = small.ctl[0].O;
+      return MCC_OK;
+    }
     // dense ids of a (in [0, n)) serve as the consensus, b as the single
     // partition: the objective with k = 1 is Mirkin(a, b)
     std::vector<const int32_t*> pa{a};
@@ -1432,6 +1543,16 @@ int mcc_canonicalize(const int32_t* in, int32_t* out, int64_t n, int32_t* cluste
   hipStream_t st = (hipStream_t)stream;
   try {
     Arena ar(st);
+    if (n <= kMultiCanon) {
+      int32_t* dtotal = ar.get<int32_t>(1);
+      launch_multi_canonical(in, n, out, dtotal, st);
+      int32_t total = 0;
+      d2h(&total, dtotal, 1, st);
+      sync(st);
+      if (total < 0) return MCC_EINVAL;
+      if (clusters) *clusters = total;
+      return MCC_OK;
+    }
     int32_t* err = ar.get<int32_t>(1);
     launch_fill_i32(err, 1, 0, st);
     int32_t* cflags = ar.get<int32_t>(n + 1);
@@ -2086,6 +2207,30 @@ int mcc_compare(const int32_t* a, const int32_t* b, int64_t n, mcc_comparison* r
   hipStream_t st = (hipStream_t)stream;
   try {
     Arena ar(st);
+    auto finish = [&](int64_t mirkin, int64_t rowmax, int64_t colmax, double cells, double rows,
+                      double cols, int32_t ka, int32_t kb) {
+      r->mirkin = mirkin;
+      r->split_join_ab = n - rowmax;
+      r->split_join_ba = n - colmax;
+      r->split_join = r->split_join_ab + r->split_join_ba;
+      r->vi = (rows + cols - 2.0 * cells) / (double)n;
+      r->rand = n > 1 ? (double)r->mirkin / ((double)n * (double)(n - 1)) : 0.0;
+      r->clusters_a = ka;
+      r->clusters_b = kb;
+    };
+    MultiSet small;
+    if (multi_table(ar, &b, 1, n, a, st, &small)) {
+      MultiCompare* dc = ar.get<MultiCompare>(1);
+      launch_multi_compare(small.a, dc, st);
+      MultiCompare c;
+      d2h(&c, dc, 1, st);
+      sync(st);
+      if (c.labels == small.inst[0].Ls) {  // else labels with gaps: dense ids, below
+        finish(small.ctl[0].O, c.rowmax, c.colmax, c.cells, c.rows, c.cols, small.inst[0].K0,
+               c.labels);
+        return MCC_OK;
+      }
+    }
     // the table of (cluster of a, label of b): dense ids of a as the
     // consensus, b as the one partition
     std::vector<const int32_t*> pa{a};
@@ -2129,14 +2274,7 @@ int mcc_compare(const int32_t* a, const int32_t* b, int64_t n, mcc_comparison* r
     d2h(ms, maxsum, 2, st);
     d2h(hs, sums, 3, st);
     sync(st);
-    r->mirkin = acc[0] + acc[1] - 2 * acc[2];
-    r->split_join_ab = n - ms[0];
-    r->split_join_ba = n - ms[1];
-    r->split_join = r->split_join_ab + r->split_join_ba;
-    r->vi = (hs[1] + hs[2] - 2.0 * hs[0]) / (double)n;
-    r->rand = n > 1 ? (double)r->mirkin / ((double)n * (double)(n - 1)) : 0.0;
-    r->clusters_a = K0;
-    r->clusters_b = Lb;
+    finish(acc[0] + acc[1] - 2 * acc[2], ms[0], ms[1], hs[0], hs[1], hs[2], K0, Lb);
     return MCC_OK;
   } catch (...) {
     return translate(std::current_exception());
@@ -2148,8 +2286,9 @@ int mcc_split_join_matrix(const int32_t* const* labels, int32_t k, int64_t n, in
   if (!dist || !labels || k < 1 || n < 0 || (int64_t)k * n >= ((int64_t)1 << 31))
     return MCC_EINVAL;
   memset(dist, 0, sizeof(int64_t) * (size_t)k * (size_t)k);
-  if (n == 0 || k == 1) return labels_ok(labels, k) ? MCC_OK : MCC_EINVAL;
-  if (!labels_ok(labels, k)) return MCC_EINVAL;
+  VisibleRanges vis;
+  if (n == 0 || k == 1) return labels_ok(labels, k, vis) ? MCC_OK : MCC_EINVAL;
+  if (!labels_ok(labels, k, vis)) return MCC_EINVAL;
   hipStream_t st = (hipStream_t)stream;
   try {
     Arena ar(st);

@@ -70,6 +70,23 @@ struct MultiArgs {
   int64_t* trace;       // device int64[4 * max_rounds] of a lone instance, or null
 };
 
+// Comparison of the clusters of a lone instance with its one partition, from
+// its table (the statistics mcc_compare reports, and the distinct labels).
+struct MultiCompare {
+  int64_t rowmax, colmax;  // sums of the rows' and the columns' largest counts
+  double cells, rows, cols;  // sums of c ln c over the cells, clusters, labels
+  int32_t labels;            // labels that occur
+  int32_t pad;
+};
+void launch_multi_compare(const MultiArgs& a, MultiCompare* out, hipStream_t st);
+
+// First-occurrence relabelling of up to kMultiCanon ids in [0, n) by one
+// workgroup; *total: the distinct ids, or -1 if one lies outside [0, n) (then
+// nothing is written).
+constexpr int64_t kMultiCanon = 16384;
+void launch_multi_canonical(const int32_t* in, int64_t n, int32_t* out, int32_t* total,
+                            hipStream_t st);
+
 // Dynamic LDS of the scorer: offsets, clusters, masks of `words` words a
 // vertex, cluster sizes, and the slice buffer.
 size_t multi_score_lds(int tile, int words, size_t slice_bytes);

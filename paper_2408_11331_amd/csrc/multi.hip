@@ -764,7 +764,132 @@ __global__ __launch_bounds__(kLeader) void k_multi_commit(MultiArgs a, const int
   }
 }
 
+// ---------------------------------------------------------------------------
+// Evaluation of one small partition.
+// ---------------------------------------------------------------------------
+__device__ inline double xlogx(int32_t c) { return c > 0 ? (double)c * log((double)c) : 0.0; }
+
+// Sum over a workgroup of kBlock threads as the comparison kernels take it
+// (the order fixes the bits of a floating-point sum).
+__device__ inline double block_total(double x, double* part) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = x;
+  __syncthreads();
+  double t = 0;
+#pragma unroll
+  for (int j = 0; j < kBlock / 64; ++j) t += part[j];
+  __syncthreads();
+  return t;
+}
+
+// sum over j < len of f(j) in the order of a grid of len / (4 kBlock)
+// workgroups striding over len, their sums then added up by one workgroup:
+// the same bits as the general comparison gives
+template <typename F>
+__device__ inline double grid_order_sum(int64_t len, F&& f, double* part) {
+  const int t = threadIdx.x;
+  const int nb = (int)max((int64_t)1, min((int64_t)2048, (len + 4 * kBlock - 1) / (4 * kBlock)));
+  double mine = 0.0;  // thread t adds the sums of the grid's workgroups t, t + kBlock, ...
+  for (int b = 0; b < nb; ++b) {
+    double acc = 0.0;
+    for (int64_t j = (int64_t)b * kBlock + t; j < len; j += (int64_t)nb * kBlock) acc += f(j);
+    acc = block_total(acc, part);
+    if (b % kBlock == t) mine += acc;
+  }
+  return block_total(mine, part);
+}
+
+__global__ __launch_bounds__(kBlock) void k_multi_compare(MultiArgs a, MultiCompare* out) {
+  __shared__ double part[kBlock / 64];
+  extern __shared__ int32_t s_col[];  // Ls sums
+  const MultiInst& m = a.inst[0];
+  const int t = threadIdx.x;
+  const int32_t K0 = m.K0, Ls = m.Ls, rs = m.rs;
+  const bool wide = m.n >= (1 << 15);
+  auto at = [&](int32_t x, int32_t l) -> int32_t {
+    return wide ? static_cast<const int32_t*>(m.N)[l * rs + x]
+                : (int32_t)static_cast<const int16_t*>(m.N)[l * rs + x];
+  };
+  int64_t rowmax = 0, colmax = 0;
+  for (int32_t x = t; x < K0; x += kBlock) {
+    int32_t best = 0;
+    for (int32_t l = 0; l < Ls; ++l) best = max(best, at(x, l));
+    rowmax += best;
+  }
+  int32_t labels = 0;
+  for (int32_t l = t; l < Ls; l += kBlock) {
+    int32_t best = 0, sum = 0;
+    for (int32_t x = 0; x < K0; ++x) {
+      const int32_t c = at(x, l);
+      best = max(best, c);
+      sum += c;
+    }
+    colmax += best;
+    s_col[l] = sum;
+    labels += sum > 0;
+  }
+  __syncthreads();
+  rowmax = wg_sum<kBlock>(rowmax);
+  colmax = wg_sum<kBlock>(colmax);
+  labels = wg_sum<kBlock>(labels);
+  const double cells = grid_order_sum(
+      (int64_t)K0 * Ls,
+      [&](int64_t j) {
+        const int32_t x = (int32_t)(j / Ls);
+        return xlogx(at(x, (int32_t)(j - (int64_t)x * Ls)));
+      },
+      part);
+  const double rows = grid_order_sum(K0, [&](int64_t x) { return xlogx(m.s[x]); }, part);
+  const double cols = grid_order_sum(Ls, [&](int64_t l) { return xlogx(s_col[l]); }, part);
+  if (t == 0) *out = MultiCompare{rowmax, colmax, cells, rows, cols, labels, 0};
+}
+
+// The smallest vertex of every id is found in LDS; then the vertices are
+// walked in order, those that are the first of their id counted by a scan,
+// and an id's entry becomes the complement of its rank (negative, so that it
+// is no vertex).
+__global__ __launch_bounds__(kLeader) void k_multi_canonical(const int32_t* in, int32_t n,
+                                                             int32_t* out, int32_t* total) {
+  extern __shared__ int32_t first[];  // n
+  const int t = threadIdx.x;
+  for (int32_t x = t; x < n; x += kLeader) first[x] = 0x7fffffff;
+  __syncthreads();
+  bool bad = false;
+  for (int32_t v = t; v < n; v += kLeader) {
+    const int32_t x = in[v];
+    if (x < 0 || x >= n) bad = true;
+    else if (first[x] > v) atomicMin(&first[x], v);
+  }
+  if (__syncthreads_or(bad)) {
+    if (t == 0) *total = -1;
+    return;
+  }
+  int32_t seen = 0;
+  for (int32_t v0 = 0; v0 < n; v0 += kLeader) {
+    const int32_t v = v0 + t, x = v < n ? in[v] : 0;
+    const bool lead = v < n && first[x] == v;
+    int32_t tot;
+    const int32_t e = wg_excl_scan<kLeader>(lead ? 1 : 0, &tot);
+    if (lead) first[x] = ~(seen + e);
+    seen += tot;
+    __syncthreads();
+  }
+  for (int32_t v = t; v < n; v += kLeader) out[v] = ~first[in[v]];
+  if (t == 0) *total = seen;
+}
+
 }  // namespace
+
+void launch_multi_compare(const MultiArgs& a, MultiCompare* out, hipStream_t st) {
+  k_multi_compare<<<1, kBlock, 4 * (size_t)kMultiCells, st>>>(a, out);
+}
+
+void launch_multi_canonical(const int32_t* in, int64_t n, int32_t* out, int32_t* total,
+                            hipStream_t st) {
+  k_multi_canonical<<<1, kLeader, 4 * (size_t)n, st>>>(in, (int32_t)n, out, total);
+}
 
 size_t multi_score_lds(int tile, int words, size_t slice_bytes) {
   return 4 * (size_t)(tile + 4) + 4 * (size_t)kMultiClusters + 4 * (size_t)words * tile +
