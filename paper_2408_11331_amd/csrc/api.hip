@@ -362,6 +362,11 @@ constexpr int32_t kAlignMaxClusters = 1 << 16;
 // blocked one, so it needs K0 k <= 2 sum_i L_i (not so from singletons).
 constexpr int64_t kDenseAlignedMax = (int64_t)1 << 30;
 
+// Largest table a hashed solve is moved to (densify_pays).
+int64_t densify_cells(int64_t n, int32_t k) {
+  return std::max<int64_t>((int64_t)1 << 24, 2 * n * (int64_t)k);
+}
+
 int64_t dense_cells_max(int64_t n, int32_t k, int64_t K0, int64_t sumL, bool want_rows) {
   int64_t lim = std::max<int64_t>((int64_t)1 << 24, 16 * n * (int64_t)k);
   if (want_rows && K0 <= kAlignMaxClusters && K0 * k <= 2 * sumL)
@@ -1134,6 +1139,15 @@ void multi_stats(const MultiCtl& c, mcc_stats* o) {
 
 namespace {
 
+// Whether a solve that started from hashed tables goes on with a dense one
+// for the K1 clusters that still have members: at most a quarter of the
+// present ones, and a table of at most twice the n k labels (or 2^24 counts).
+bool densify_pays(int64_t n, int32_t k, int64_t K0, int64_t K1, int64_t Lmax) {
+  const int64_t cells = K1 * Lmax * k;
+  return K1 > 0 && 4 * K1 <= K0 && K1 <= kAlignMaxClusters && cells <= densify_cells(n, k) &&
+         cells + 2 * K1 < ((int64_t)1 << 31);
+}
+
 // Workspace of the candidate sets carried over between passes.
 int64_t carry_bytes(int64_t n, int64_t K0) {
   return 4 * (5 * n + n * kCacheCand + 2 * K0 + (n + 31) / 32) + 8 * 256;
@@ -1237,7 +1251,10 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     int64_t* dtrace = nullptr;
     if (flags & MCC_F_TRACE) dtrace = ar.get<int64_t>((int64_t)max_rounds * 4);
     Ctl* ctl = ar.get<Ctl>(1);
-    launch_ctl_init(ctl, S.acc, n, k, max_rounds, dtrace, st);
+    // from singletons every neighbour is a candidate: with more than 32 on
+    // average the first pass's tiles would walk their arcs only to defer them
+    launch_ctl_init(ctl, S.acc, n, k, max_rounds, dtrace,
+                    S.t.hashed && S.K0 == n && g->nnz > 32 * n, st);
     uint64_t* owner = ar.get<uint64_t>(S.K0);
     launch_fill_u64(owner, S.K0, ~0ull, st);
     int32_t* prop = ar.get<int32_t>(n);
@@ -1266,13 +1283,15 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     a.ctl = ctl;
     a.pc = ar.get<int64_t>((kPassCounters + kTickets) * kCounterStride);
     a.plist = ar.get<int32_t>(n);
-    if (!S.t.hashed) {  // histogram apply when a partition's slice fits in LDS
+    // histogram apply when a partition's slice of a dense table fits in LDS
+    auto set_delta = [&]() {
       const int64_t slice = (int64_t)S.K0 * S.maxL + 2 * (int64_t)S.K0;
       if (4 * slice <= kDeltaLdsMax) {
         a.delta_lds = (int32_t)(4 * slice);
         a.delta_slices = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, n / 2048));
       }
-    }
+    };
+    if (!S.t.hashed) set_delta();
     launch_fill_u64(reinterpret_cast<uint64_t*>(a.pc), (kPassCounters + kTickets) * kCounterStride,
                     0ull, st);
     a.n = n;
@@ -1312,6 +1331,16 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
       a.members = ar.get<int32_t>(n);
       a.mscan_tmp = ar.get<int32_t>(scan_tmp_elems(S.K0));
       a.msum_max = S.t.rows ? kRowsMemberMax : kMemberSumMax;
+      const int32_t width = S.maxL <= 256 ? 1 : (S.maxL <= 65536 ? 2 : 0);
+      const int64_t stride = (width * (int64_t)k + 15) & ~(int64_t)15;
+      if (width && ar.fits(n * stride + 256)) {
+        uint8_t* Lc = ar.get<uint8_t>(n * stride);
+        launch_compact_rows(S.Lvm, n, k, width, (int32_t)stride, Lc, st);
+        a.Lc = Lc;
+        a.lc_stride = (int32_t)stride;
+        a.lc_width = width;
+        a.msum_max = kMemberSumMax;
+      }
     }
     a.cn_bytes = S.K0 <= 256 ? 1 : (S.K0 <= 65536 ? 2 : 4);
     if (a.cn_bytes == 4) {
@@ -1369,11 +1398,58 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     HIPCK(hipEventRecord(e1, st));
     Ctl hc;
     memset(&hc, 0, sizeof hc);
-    // slots are enqueued ahead in growing chunks; a pass takes one, or two
-    // when it falls back
-    int chunk = 2;
-    for (int64_t enqueued = 0; enqueued < 2 * (int64_t)max_rounds; enqueued += chunk) {
-      if (enqueued) chunk = std::min(chunk * 2, 16);
+    // A solve that starts from hashed tables (many clusters) goes on with a
+    // dense one once few clusters are left, and with a smaller one when fewer
+    // are: the counts are those of the same partition, and the new indexes
+    // keep the order of the old ones, so no decision changes.  (2 M kNN
+    // vertices from singletons: 50 000 clusters after four passes, 180 after
+    // eight; LFR 100 k: 700 after four.)
+    const bool shrinks = S.t.hashed && !(flags & (MCC_F_HASH_TABLES | MCC_F_HASH_ROWS |
+                                                  MCC_F_HASH_KEYS | MCC_F_ARC_CACHE));
+    int32_t* const cmap = a.mstart;
+    int32_t* const live = a.mcnt;
+    int32_t* const scan_tmp = a.mscan_tmp;
+    auto shrink = [&](int32_t K1) {
+      Tables to{};
+      to.Lmax = S.maxL;
+      to.k = k;
+      to.interleaved = 1;
+      to.L = S.t.L;  // bounds of the label ids, unchanged
+      const int64_t cells = (int64_t)K1 * to.Lmax * k;
+      if (!ar.fits(4 * cells + 16 * (int64_t)K1 + 2 * n + 8 * 256)) return;
+      to.N = ar.get<int32_t>(cells);
+      launch_fill_i32(to.N, cells, 0, st);
+      launch_densify(a.t, cmap, a.s, a.K0, to, st);
+      int32_t* s2 = ar.get<int32_t>(K1);
+      int32_t* raw2 = ar.get<int32_t>(K1);
+      int32_t* churn2 = a.churn ? ar.get<int32_t>(2 * (int64_t)K1) : nullptr;
+      launch_compact_clusters(cmap, a.K0, a.s, S.rawid, a.churn, K1, s2, raw2, churn2, st);
+      const int32_t bytes = K1 <= 256 ? 1 : 2;
+      void* Cn = ar.get<uint8_t>(n * bytes);
+      launch_remap(cmap, n, a.C, Cn, bytes, a.cnum, a.ccache, kCacheCand, st);
+      a.t = to;
+      a.s = s2;
+      S.rawid = raw2;
+      S.s = s2;
+      S.K0 = a.K0 = K1;
+      a.churn = churn2;
+      a.Cn = Cn;
+      a.cn_bytes = bytes;
+      a.cells = cells;
+      a.hflag = nullptr;
+      a.rdist = nullptr;
+      a.mstart = a.mcnt = a.members = a.mscan_tmp = nullptr;
+      a.Lc = nullptr;
+      set_delta();
+    };
+    // slots are enqueued ahead in growing chunks (a pass takes one, or two
+    // when it falls back), while clusters may vanish fast one by one
+    int chunk = shrinks ? 1 : 2;
+    int64_t enqueued = 0;
+    Ctl last{};
+    for (int round = 0; enqueued < 2 * (int64_t)max_rounds; ++round) {
+      if (round && (!shrinks || round >= 8)) chunk = std::min(chunk * 2, 16);
+      enqueued += chunk;
       for (int j = 0; j < chunk; ++j) {
         hipEvent_t b = nullptr, e = nullptr;
         if (profile) {
@@ -1384,16 +1460,27 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
         }
         enqueue_pass(a, lanes, grid_score, grid_apply, st, b, e);
       }
+      int32_t K1 = 0;
+      if (shrinks) {
+        launch_live(a.s, a.K0, live, st);
+        launch_scan(live, cmap, a.K0, scan_tmp, st);
+        d2h(&K1, cmap + a.K0, 1, st);
+      }
       d2h(&hc, ctl, 1, st);
       sync(st);
       if (hc.done) break;
+      // tiles of 128 hold 16 candidates a vertex, of 64 twice as many
+      const int64_t bnd = hc.boundary - last.boundary;
+      if (bnd > 0) a.tile_small = hc.evals - last.evals > 12 * bnd ? 1 : 0;
+      last = hc;
+      if (shrinks && !hc.stage && densify_pays(n, k, a.K0, K1, S.maxL)) shrink(K1);
     }
     HIPCK(hipEventRecord(e2, st));
 
     launch_finish(S.C, S.rawid, n, out, st);
     int32_t* ncl = ar.get<int32_t>(1);
     launch_fill_i32(ncl, 1, 0, st);
-    launch_count_nonzero(S.s, S.K0, ncl, st);
+    launch_count_nonzero(a.s, S.K0, ncl, st);
     int32_t clusters = 0;
     d2h(&clusters, ncl, 1, st);
     d2h(&hc, ctl, 1, st);
@@ -2566,6 +2653,11 @@ int mcc_workspace_bound(int64_t n, int64_t nnz, int32_t k, int64_t max_label, in
     while (((int64_t)1 << bits) < 4 * nk) ++bits;
     add(8 * (k + 1)); add(16 * ((int64_t)1 << bits)); add(8); add(4 * sumL);
     add(4 * (K0 + 1)); add(4 * K0); add(4 * n); add(4 * (scan_tmp_elems(K0) + 1));
+    add(n * ((2 * (int64_t)k + 15) & ~(int64_t)15));  // compact label rows
+    if (!(flags & (MCC_F_HASH_TABLES | MCC_F_HASH_ROWS | MCC_F_HASH_KEYS | MCC_F_ARC_CACHE)))
+      for (int j = 0; j < 8; ++j) {  // smaller and smaller dense tables (each a quarter)
+        add(4 * (densify_cells(n, k) >> (2 * j))); add(2 * n); add(16 * K0 >> (2 * j));
+      }
     // alignment to partition 0 for the row layout (its table is at most the
     // key table unless forced) and its label ids (at most L0 + L_i a partition)
     const int64_t L0 = std::min<int64_t>(max_label + 1, kAlignMaxClusters);

@@ -332,6 +332,23 @@ void launch_row_distinct(const int32_t* Lvm, int64_t n, int32_t k, uint8_t* rdis
 // Hashed rows: the counts of C from the vertex-major label rows.
 void launch_build_rows(const int32_t* C, const int32_t* Lvm, int64_t n, int32_t k, Tables t,
                        hipStream_t st);
+// Label rows of `width`-byte ids, `stride` bytes apart (see PassArgs).
+void launch_compact_rows(const int32_t* Lvm, int64_t n, int32_t k, int32_t width, int32_t stride,
+                         uint8_t* Lc, hipStream_t st);
+// Fewer clusters: flags[x] = 1 where cluster x has members (its scan is the
+// order-preserving new index cmap); sizes, raw ids and move counts moved to
+// their new places; cluster ids of the vertices (and their narrow copy, of
+// `bytes` bytes, or null) and of the cached candidates rewritten.
+void launch_live(const int32_t* s, int64_t K0, int32_t* flags, hipStream_t st);
+void launch_compact_clusters(const int32_t* cmap, int64_t K0, const int32_t* s,
+                             const int32_t* rawid, const int32_t* churn, int32_t K1, int32_t* s2,
+                             int32_t* rawid2, int32_t* churn2, hipStream_t st);
+void launch_remap(const int32_t* cmap, int64_t n, int32_t* C, void* Cn, int32_t bytes,
+                  const int32_t* cnum, int32_t* ccache, int32_t cache, hipStream_t st);
+// The counts of table t moved to the (zeroed) interleaved table `to`, whose
+// clusters are cmap's new indexes and whose label ids are t's.
+void launch_densify(const Tables& t, const int32_t* cmap, const int32_t* s, int64_t K0,
+                    const Tables& to, hipStream_t st);
 // In-arc lists: in_ptr (exclusive scan of in-degrees, n + 1) and in_pos
 // (arc positions grouped by head vertex); ac[j] = C[col[j]].
 void launch_in_degree(const int32_t* col, int64_t nnz, int32_t* indeg, hipStream_t st);
@@ -413,6 +430,12 @@ struct PassArgs {
                       // kMemberSumMax): a member row costs two or three
                       // lines, a key table's probes k lines, a row table's
                       // a few
+  // Label rows of 1- or 2-byte ids (where the ids fit), lc_stride bytes apart
+  // (a multiple of 16, the rest of a row zero): a member row is one 64-byte
+  // line for up to 64 partitions of at most 256 ids.  Null: read Lvm.
+  const uint8_t* Lc;
+  int32_t lc_stride;
+  int32_t lc_width;
   int32_t K0;
   // Narrow copy of C (uint8 when K0 <= 256, uint16 when K0 <= 65536, else
   // C itself) for the per-arc cluster gathers: a few MiB stay resident in
@@ -473,7 +496,7 @@ struct PassArgs {
   int32_t delta_lds;
   int32_t delta_slices;
   int32_t tile_grid;    // most workgroups of the tiled scorer
-  int32_t pad4;
+  int32_t tile_small;   // 1: tiles of 64 (the last pass had many candidates a vertex)
 };
 
 constexpr int kDeltaLdsMax = 48 << 10;
@@ -557,7 +580,8 @@ bool score_lanes_ok(int lanes);
 // kernel on the same stream.
 void enqueue_pass(const PassArgs& a, int lanes, int grid_score, int grid_apply, hipStream_t st,
                   hipEvent_t score_begin = nullptr, hipEvent_t score_end = nullptr);
+// defer_all: the first pass is left to the wave-per-vertex scorer.
 void launch_ctl_init(Ctl* ctl, const int64_t* acc, int64_t n, int32_t k, int32_t max_rounds,
-                     int64_t* trace, hipStream_t st);
+                     int64_t* trace, bool defer_all, hipStream_t st);
 
 }  // namespace mcc

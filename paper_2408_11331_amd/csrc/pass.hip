@@ -121,9 +121,24 @@ __device__ inline void flush_counts(const PassArgs& a, int64_t evals, int64_t np
 // smallest id without any sort.
 // ---------------------------------------------------------------------------
 constexpr int kMaxLdsPart = 256;  // partitions whose table geometry sits in LDS
-constexpr int kTileCandAvg = 8;   // candidates per vertex the tiled scorer's key set holds
+constexpr int kTileCandAvg = 24;  // candidates per vertex that fit the key sets of 64-vertex tiles
 constexpr int kCandSetBits = 8;   // deferred vertex: LDS set of its candidate clusters
 constexpr int kCandSet = 1 << kCandSetBits;
+
+// Ids that agree in 16 bytes of two compact label rows: zero bytes (halves)
+// of the exclusive or.
+__device__ inline int32_t zeros8(uint32_t x) {
+  return __popc(~((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) | 0x7f7f7f7fu));
+}
+__device__ inline int32_t zeros16(uint32_t x) {
+  return __popc(~((((x & 0x7fff7fffu) + 0x7fff7fffu) | x) | 0x7fff7fffu));
+}
+__device__ inline int32_t agree8(const uint4& a, const uint4& b) {
+  return zeros8(a.x ^ b.x) + zeros8(a.y ^ b.y) + zeros8(a.z ^ b.z) + zeros8(a.w ^ b.w);
+}
+__device__ inline int32_t agree16(const uint4& a, const uint4& b) {
+  return zeros16(a.x ^ b.x) + zeros16(a.y ^ b.y) + zeros16(a.z ^ b.z) + zeros16(a.w ^ b.w);
+}
 
 template <int G, bool LIST>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_score(PassArgs a) {
@@ -420,7 +435,45 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
             int32_t* vrow = s_vrow[w];  // the vertex's row, read by every pair
             vrow[lane] = lane < k ? row[lane] : 0;
             __builtin_amdgcn_wave_barrier();
-            if ((k & 1) == 0) {  // rows 8-byte aligned: two partitions a load
+            if (a.Lc) {  // compact rows: four lanes read 64 bytes of a member's row
+              const uint4* L4 = reinterpret_cast<const uint4*>(a.Lc);
+              const int q4 = a.lc_stride >> 4;  // 16-byte words a row
+              const bool bytes = a.lc_width == 1;
+              const int32_t pad = (a.lc_stride / a.lc_width) - k;  // zeros that agree
+              constexpr int E = 4;
+              for (int32_t p0 = 0; p0 < P; p0 += 16 * E) {
+                int32_t its[E], us[E], sums[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                  const int32_t p = p0 + 16 * e + pq;
+                  its[e] = -1;
+                  us[e] = 0;
+                  sums[e] = 0;
+                  if (p < P) {
+                    const int it = item_of(p);
+                    its[e] = it;
+                    const int32_t ms = imst[it];
+                    us[e] = ms < 0 ? ~ms : a.members[ms + (p - ioff[it])];
+                  }
+                }
+                for (int c = li; c < q4; c += 4) {
+                  const uint4 o = L4[v * q4 + c];
+                  uint4 r[E];
+#pragma unroll
+                  for (int e = 0; e < E; ++e)
+                    r[e] = its[e] >= 0 ? L4[(int64_t)us[e] * q4 + c] : o;
+#pragma unroll
+                  for (int e = 0; e < E; ++e)
+                    sums[e] += bytes ? agree8(r[e], o) : agree16(r[e], o);
+                }
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                  sums[e] += __shfl_xor(sums[e], 1, 4);
+                  sums[e] += __shfl_xor(sums[e], 2, 4);
+                  if (li == 0 && its[e] >= 0) atomicAdd(&isum[its[e]], sums[e] - pad);
+                }
+              }
+            } else if ((k & 1) == 0) {  // rows 8-byte aligned: two partitions a load
               const int h = k >> 1;
               const int2* vl = reinterpret_cast<const int2*>(vrow);
               for (int32_t p0 = 0; p0 < P; p0 += 32) {
@@ -685,7 +738,8 @@ void k_score_tile(PassArgs a) {
   if (a.ctl->done || a.ctl->stage) return;
   constexpr int kPairMax = kSetSlots + TV;  // every candidate plus one own pair per vertex
   constexpr int kProbeRegs = NR > 0 ? NR : 1;       // labels per lane when k <= 16 NR
-  constexpr int kProbeBatch = NR > 2 || NR == 0 || TK == kHashed ? 4 : 8;  // pairs in flight
+  // pairs in flight (hashed lookups hold more registers a pair)
+  constexpr int kProbeBatch = TK == kHashed ? (NR > 2 ? 2 : 4) : (NR > 2 || NR == 0 ? 4 : 8);
   __shared__ int32_t s_off[TV + 1];
   __shared__ int32_t s_c[TV];
   __shared__ int32_t s_nc[TV];    // candidates of each vertex
@@ -693,6 +747,7 @@ void k_score_tile(PassArgs a) {
   __shared__ int32_t s_cur[TV];   // fill cursor of the vertex's run
   __shared__ int32_t s_clean[TV]; // 1: candidate set taken from the cache
   __shared__ int32_t s_np;            // pairs that fit the pair arrays
+  __shared__ int32_t s_nq;            // hashed tables: pairs left for the table
   __shared__ int32_t s_set[kSetSlots];
   __shared__ int32_t s_cl[kPairMax];   // pair keys (vertex << 24 | cluster), run per vertex
   __shared__ int32_t s_S[kPairMax];    // agreement sum of each pair
@@ -876,12 +931,60 @@ void k_score_tile(PassArgs a) {
         a.cnum[v] = nc;
       }
     }
+    // Hashed tables with compact rows: clusters of up to msum_max members are
+    // scored from their members' rows, four lanes a pair and four members at
+    // a time (a 64-byte line each, against about ten lines of a table lookup);
+    // the pairs of the others are listed (in the key set, which is done with)
+    // for the probes below.
+    int nprobe = npairs;
+    uint16_t* plist = reinterpret_cast<uint16_t*>(s_set);
+    const bool by_rows = TK == kHashed && a.Lc != nullptr;
+    if (by_rows) {
+      if (t == 0) s_nq = 0;
+      __syncthreads();
+      const uint4* L4 = reinterpret_cast<const uint4*>(a.Lc);
+      const int q4 = a.lc_stride >> 4, li = t & 3;
+      const bool bytes = a.lc_width == 1;
+      const int32_t pad = a.lc_stride / a.lc_width - k;  // zeros that agree
+      for (int p = t >> 2; p < npairs; p += kBlock / 4) {
+        const int32_t key = s_cl[p], x = key & 0xffffff;
+        const int64_t v = v0 + (int)((uint32_t)key >> 24);
+        const int32_t cnt = a.s[x];
+        if (cnt > a.msum_max) {
+          if (li == 0) plist[atomicAdd(&s_nq, 1)] = (uint16_t)p;
+          continue;
+        }
+        const int32_t b = a.mstart[x];
+        int32_t sum = 0;
+        for (int32_t m = 0; m < cnt; m += 4) {
+          const int32_t mid = m + li < cnt ? a.members[b + m + li] : -1;
+          int32_t u[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) u[j] = __shfl(mid, j, 4);
+          for (int c = li; c < q4; c += 4) {
+            const uint4 o = L4[v * q4 + c];
+            uint4 r[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) r[j] = L4[(int64_t)max(u[j], 0) * q4 + c];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (u[j] >= 0) sum += bytes ? agree8(r[j], o) : agree16(r[j], o);
+          }
+        }
+        sum += __shfl_xor(sum, 1, 4);
+        sum += __shfl_xor(sum, 2, 4);
+        if (li == 0) s_S[p] = sum - cnt * pad;
+      }
+      __syncthreads();
+      nprobe = s_nq;
+    }
     constexpr int kStride = (kBlock / kProbeLanes) * kProbeBatch;
+    auto pair_of = [&](int p) { return by_rows ? (int)plist[p] : p; };
     auto pair_at = [&](int p, int32_t& x, uint32_t& row) {
       x = -1;
       row = 0;
-      if (p < npairs) {
-        const int32_t key = s_cl[p];
+      if (p < nprobe) {
+        const int32_t key = s_cl[pair_of(p)];
         x = key & 0xffffff;
         row = (uint32_t)(v0 + (int)((uint32_t)key >> 24)) * (uint32_t)k;
       }
@@ -912,7 +1015,7 @@ void k_score_tile(PassArgs a) {
 #pragma unroll
       for (int q = 0; q < kProbeBatch; ++q) pair_at(p0 + q, xs[q], vs[q]);
       load_rows(xs, vs, lab);
-      for (; p0 < npairs; p0 += kStride) {
+      for (; p0 < nprobe; p0 += kStride) {
         int32_t xn[kProbeBatch], labn[kProbeBatch][kProbeRegs];
         uint32_t vn[kProbeBatch];
 #pragma unroll
@@ -922,7 +1025,7 @@ void k_score_tile(PassArgs a) {
 #pragma unroll
         for (int q = 0; q < kProbeBatch; ++q) {
           int32_t sum = 0;
-          if (TK == kHashed && xs[q] >= 0 && a.members && a.s[xs[q]] <= a.msum_max) {
+          if (TK == kHashed && !by_rows && xs[q] >= 0 && a.s[xs[q]] <= a.msum_max) {
             const int32_t cnt = a.s[xs[q]];  // <= kProbeLanes: one member id per lane
             const int32_t mid = lane < cnt ? a.members[a.mstart[xs[q]] + lane] : 0;
             for (int32_t m = 0; m < cnt; ++m) {
@@ -945,7 +1048,7 @@ void k_score_tile(PassArgs a) {
 #pragma unroll
         for (int q = 0; q < kProbeBatch; ++q) {
           const int32_t sq = group_sum<kProbeLanes>(sums[q]);
-          if (lane == 0 && xs[q] >= 0) s_S[p0 + q] = sq;
+          if (lane == 0 && xs[q] >= 0) s_S[pair_of(p0 + q)] = sq;
         }
 #pragma unroll
         for (int q = 0; q < kProbeBatch; ++q) {
@@ -956,7 +1059,7 @@ void k_score_tile(PassArgs a) {
         }
       }
     } else {
-      for (int p0 = g * kProbeBatch; p0 < npairs; p0 += kStride) {
+      for (int p0 = g * kProbeBatch; p0 < nprobe; p0 += kStride) {
 #pragma unroll
         for (int q = 0; q < kProbeBatch; ++q) {
           int32_t x;
@@ -965,7 +1068,7 @@ void k_score_tile(PassArgs a) {
           int32_t sum = 0;
           if (x >= 0) {
             const int32_t* row = a.Lvm + ro;
-            if (TK == kHashed && a.members && a.s[x] <= a.msum_max) {
+            if (TK == kHashed && !by_rows && a.s[x] <= a.msum_max) {
               const int32_t cnt = a.s[x];
               const int32_t mid = lane < cnt ? a.members[a.mstart[x] + lane] : 0;
               for (int32_t m = 0; m < cnt; ++m) {
@@ -977,7 +1080,7 @@ void k_score_tile(PassArgs a) {
             }
           }
           const int32_t sq = group_sum<kProbeLanes>(sum);
-          if (lane == 0 && x >= 0) s_S[p0 + q] = sq;
+          if (lane == 0 && x >= 0) s_S[pair_of(p0 + q)] = sq;
         }
       }
     }
@@ -1014,19 +1117,14 @@ void k_score_tile(PassArgs a) {
 // ---------------------------------------------------------------------------
 // Dirty marks where the graph is not known to be symmetric: eight lanes a
 // vertex look up whether it or one of its neighbours moved in the previous
-// pass (a bit a vertex: 125 KiB for 1 M vertices).  Where more than an eighth
-// of the vertices moved nearly all are dirty, and all are marked unread.
+// pass (a bit a vertex: 125 KiB for 1 M vertices), unless more than an eighth
+// of the vertices moved.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void k_pull(PassArgs a) {
   const Ctl* ctl = a.ctl;
   if (ctl->done || ctl->stage) return;
   const int64_t n = a.n;
-  if ((int64_t)ctl->last_moves * 8 > n) {
-    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n;
-         v += (int64_t)gridDim.x * kBlock)
-      a.dirty[v] = 1;
-    return;
-  }
+  if ((int64_t)ctl->last_moves * 8 > n) return;  // k_status takes all as dirty
   constexpr int G = 8;
   const int lane = threadIdx.x & (G - 1);
   const int64_t ngroups = (int64_t)gridDim.x * kBlock / G;
@@ -1062,6 +1160,7 @@ __global__ __launch_bounds__(kBlock) void k_status(PassArgs a) {
   const int32_t* churn = a.churn + (int64_t)par * a.K0;
   int32_t* next = a.churn + (int64_t)(par ^ 1) * a.K0;
   const int32_t churn_max = ctl->churn_max;
+  const bool all_dirty = (int64_t)ctl->last_moves * 8 > a.n;
   const int t = threadIdx.x;
   const int64_t t0 = (int64_t)blockIdx.x * kBlock + t, T = (int64_t)gridDim.x * kBlock;
   for (int64_t x = t0; x < a.K0; x += T) next[x] = 0;
@@ -1080,7 +1179,7 @@ __global__ __launch_bounds__(kBlock) void k_status(PassArgs a) {
       sl[j] = -1;
       cv[j] = 0;
       if (v < a.n) {
-        d[j] = a.dirty[v];
+        d[j] = all_dirty ? 1 : a.dirty[v];
         cn[j] = a.cnum[v];
         sl[j] = a.slack[v];
         cv[j] = a.C[v];
@@ -1331,7 +1430,7 @@ __device__ inline void pass_begin(const PassArgs& a) {
   // most boundary vertices had more candidates than the tiles hold, and
   // many on average (the counts fall fast once clusters merge): the next
   // pass skips the tiled scorer and scores every vertex by the wave
-  ctl->defer_all = (2 * c[4] > c[2] && c[0] > 12 * c[2]) ? 1 : 0;
+  ctl->defer_all = (2 * c[4] > c[2] && c[0] > kTileCandAvg * c[2]) ? 1 : 0;
   ctl->passes += 1;
   ctl->evals += c[0];
   ctl->dS2 = 0;
@@ -1349,7 +1448,9 @@ __device__ inline void pass_begin(const PassArgs& a) {
   if (!a.hflag) return;
   // Hashed tables: before the batch is applied, rebuild the table from the
   // partition (the counts are a function of C alone) if the keys the batch
-  // may add could take it beyond half full.  Keys: the batch adds at most k
+  // may add could take it beyond half full (rows: three quarters; the second
+  // pass of 2 M singletons then needs no rebuild, 4 ms, and few passes read a
+  // row table before a dense one takes over).  Keys: the batch adds at most k
   // keys per proposal; the table holds 4 n k slots or more and at most n k
   // live keys, so after a rebuild there is always room.  Rows: a proposal
   // adds at most its vertex's distinct label ids, at most T0 in all, over at
@@ -1357,7 +1458,8 @@ __device__ inline void pass_begin(const PassArgs& a) {
   // one just built (no key without a count), so a rebuild would not change it.
   const int64_t adds = a.t.rows ? now(&ctl->prop_rows) : (int64_t)a.k * c[1];
   const bool need = c[1] > 0 && ctl->passes > 1 &&
-                    (int64_t)*a.t.hocc + adds > (int64_t)((a.t.hmask + 1) / 2);
+                    (int64_t)*a.t.hocc + adds > (int64_t)(a.t.rows ? 3 * ((a.t.hmask + 1) / 4)
+                                                                 : (a.t.hmask + 1) / 2);
   *a.hflag = need ? 1 : 0;
   if (need) *a.t.hocc = 0;
 }
@@ -1434,14 +1536,22 @@ __device__ inline int64_t move_counts(const PassArgs& a, int64_t v, int32_t from
   return acc;
 }
 
+// More than an eighth of the vertices moved in the pass: nearly all are
+// dirty, so none is marked and the next pass takes all as dirty (2 M kNN
+// vertices that all moved: 0.85 ms of scattered marks).
+__device__ inline bool mass_move(const PassArgs& a) {
+  return (int64_t)a.ctl->committed * 8 > a.n;
+}
+
 // Vertex w moved: it and its out-neighbours (its in-neighbours, the graph
 // being symmetric) recompute their candidate sets next pass.
-__device__ inline void mark_dirty(const PassArgs& a, int64_t w, int lane) {
+__device__ inline void mark_dirty(const PassArgs& a, int64_t w, int lane, bool mass) {
   if (!a.dirty) return;
   if (a.moved) {  // looked up by k_pull
     if (lane == 0) atomicOr(&a.moved[w >> 5], 1u << (w & 31));
     return;
   }
+  if (mass) return;
   if (lane == 0) a.dirty[w] = 1;
   const int64_t b = a.row_ptr[w], e = a.row_ptr[w + 1];
   for (int64_t p = b + lane; p < e; p += 64) a.dirty[a.col[p]] = 1;
@@ -1462,7 +1572,7 @@ enum ApplyMode { kCommitOrElect = 1, kFallbackCommit = 2, kFallbackFinish = 3 };
 template <int MODE>
 __device__ inline void apply_walk(const PassArgs& a, int64_t wave, int64_t nwaves) {
   Ctl* ctl = a.ctl;
-  const bool fb = ctl->fallback;
+  const bool fb = ctl->fallback, mass = mass_move(a);
   const int lane = threadIdx.x & 63;
   int64_t dn2 = 0, ds2 = 0;
   int32_t committed = 0;
@@ -1486,7 +1596,7 @@ __device__ inline void apply_walk(const PassArgs& a, int64_t wave, int64_t nwave
             cn_store(a, w, pw);
           }
           relabel_in_arcs(a, w, pw, lane);
-          mark_dirty(a, w, lane);
+          mark_dirty(a, w, lane, mass);
         } else {
           move_counts(a, w, from, pw, -1, lane, &ds2);  // undo the batch
           if (lane == 0) {
@@ -1516,7 +1626,7 @@ __device__ inline void apply_walk(const PassArgs& a, int64_t wave, int64_t nwave
         }
         if (pw >= 0) {
           relabel_in_arcs(a, w, pw, lane);
-          mark_dirty(a, w, lane);
+          mark_dirty(a, w, lane, mass);
         }
       }
     }
@@ -1559,14 +1669,13 @@ struct Sq2 {
 // Keys: [0, cells) table cells, [cells, cells + K0) cluster sizes,
 // [cells + K0, cells + 2 K0) per-cluster move counts (churn_w).
 __device__ __attribute__((always_inline)) inline Sq2 agg_add(int32_t* hkey, int32_t* hval,
-                                                           int32_t* fill, bool direct,
-                                                           const PassArgs& a, int32_t* churn_w,
-                                                           int64_t key, int32_t d) {
+                                                           int32_t* fill, const PassArgs& a,
+                                                           int32_t* churn_w, int64_t key,
+                                                           int32_t d) {
   const int32_t k32 = (int32_t)key;
   uint32_t h = ((uint32_t)k32 * 2654435761u) >> 20;  // 12 bits: kHashSlots
-  const int probes = direct ? 0 : kHashProbe;
 #pragma unroll 1
-  for (int q = 0; q < probes; ++q) {
+  for (int q = 0; q < kHashProbe; ++q) {
     int32_t cur = hkey[h];
     if (cur == -1) {
       if (*fill >= kHashOpen) break;  // the key is not in the table
@@ -1649,21 +1758,19 @@ __global__ __launch_bounds__(kBlock) void k_apply_all(PassArgs a) {
   __shared__ int32_t hkey[kHashSlots];
   __shared__ int32_t hval[kHashSlots];
   __shared__ int32_t fill;
-  // the workgroup's share of the listed proposals: one per group of 16
-  // lanes at least, the lanes of a group spread over the partitions
+  // the workgroup's share of the listed proposals: one per group of 16 lanes
+  // at least (late passes move vertices between few clusters: updates merged
+  // in LDS spare the counters they share), the lanes of a group spread over
+  // the partitions
   constexpr int kApplyLanes = 16, kGroups = kBlock / kApplyLanes;
   const int64_t count = ctl->plist_count;
   const int64_t per = max((int64_t)kGroups, (count + gridDim.x - 1) / gridDim.x);
   const int64_t eb = blockIdx.x * per, ee = min(count, eb + per);
   if (eb < ee) {
-    // one proposal a group: little to merge, the updates go straight to the
-    // counters
-    const bool direct = per == kGroups;
-    if (!direct)
-      for (int j = threadIdx.x; j < kHashSlots; j += kBlock) {
-        hkey[j] = -1;
-        hval[j] = 0;
-      }
+    for (int j = threadIdx.x; j < kHashSlots; j += kBlock) {
+      hkey[j] = -1;
+      hval[j] = 0;
+    }
     if (threadIdx.x == 0) fill = 0;
     __syncthreads();
     int64_t dn2 = 0, ds2 = 0;
@@ -1679,22 +1786,22 @@ __global__ __launch_bounds__(kBlock) void k_apply_all(PassArgs a) {
       for (int i = gl; i < a.k; i += kApplyLanes) {
         const int32_t l = row[i];
         const Sq2 up =
-            agg_add(hkey, hval, &fill, direct, a, churn_w, cell_upd(a.t, i, to, l, claimed), +1);
+            agg_add(hkey, hval, &fill, a, churn_w, cell_upd(a.t, i, to, l, claimed), +1);
         const Sq2 dn =
-            agg_add(hkey, hval, &fill, direct, a, churn_w, cell_upd(a.t, i, from, l, claimed), -1);
+            agg_add(hkey, hval, &fill, a, churn_w, cell_upd(a.t, i, from, l, claimed), -1);
         dn2 += up.n + dn.n;
       }
       if (gl == 0) {
-        const Sq2 up = agg_add(hkey, hval, &fill, direct, a, churn_w, a.cells + to, +1);
-        const Sq2 dn = agg_add(hkey, hval, &fill, direct, a, churn_w, a.cells + from, -1);
+        const Sq2 up = agg_add(hkey, hval, &fill, a, churn_w, a.cells + to, +1);
+        const Sq2 dn = agg_add(hkey, hval, &fill, a, churn_w, a.cells + from, -1);
         ds2 += up.s + dn.s;
       } else if (gl == 1 && churn_w) {
-        cmax = max(cmax, agg_add(hkey, hval, &fill, direct, a, churn_w, a.cells + a.K0 + to, +1).churn);
-        cmax = max(cmax, agg_add(hkey, hval, &fill, direct, a, churn_w, a.cells + a.K0 + from, +1).churn);
+        cmax = max(cmax, agg_add(hkey, hval, &fill, a, churn_w, a.cells + a.K0 + to, +1).churn);
+        cmax = max(cmax, agg_add(hkey, hval, &fill, a, churn_w, a.cells + a.K0 + from, +1).churn);
       }
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < kHashSlots && !direct; j += kBlock) {
+    for (int j = threadIdx.x; j < kHashSlots; j += kBlock) {
       const int32_t key = hkey[j], d = hval[j];
       if (key < 0 || d == 0) continue;
       if (key < a.cells) {
@@ -1914,12 +2021,13 @@ __global__ __launch_bounds__(kBlock) void k_member_fill(PassArgs a) {
 }
 
 __global__ void k_ctl_init(Ctl* ctl, const int64_t* acc, int32_t n, int32_t k, int32_t max_rounds,
-                           int64_t* trace) {
+                           int64_t* trace, int32_t defer_all) {
   Ctl c = {};
   c.k = k;
   c.max_rounds = max_rounds;
   c.trace = trace;
   c.last_moves = n;
+  c.defer_all = defer_all;
   c.O = (int64_t)k * acc[0] + acc[1] - 2 * acc[2];
   *ctl = c;
 }
@@ -1948,7 +2056,9 @@ void launch_tile(const PassArgs& a, int grid, hipStream_t st) {
   // vertices, 51 clusters: 8.2 ms against 8.8 with 128), else 128, whose key
   // set holds 16 candidates a vertex (1 M LFR vertices, ten candidates each:
   // 49.6 ms against 51.4 with 256 and 54.7 with 64).
-  if (a.n <= kSmallTileMax) launch_tile_v<TK, 64>(a, st);
+  // Tiles of 64 also where the candidates are many: with hashed tables, whose
+  // starts have one for most arcs, and after a pass with more than twelve.
+  if (TK == kHashed || a.tile_small || a.n <= kSmallTileMax) launch_tile_v<TK, 64>(a, st);
   else if (a.K0 <= 256) launch_tile_v<TK, 256>(a, st);
   else launch_tile_v<TK, 128>(a, st);
   if (!a.st) return;
@@ -1965,8 +2075,8 @@ bool score_lanes_ok(int lanes) {
 }
 
 void launch_ctl_init(Ctl* ctl, const int64_t* acc, int64_t n, int32_t k, int32_t max_rounds,
-                     int64_t* trace, hipStream_t st) {
-  k_ctl_init<<<1, 1, 0, st>>>(ctl, acc, (int32_t)n, k, max_rounds, trace);
+                     int64_t* trace, bool defer_all, hipStream_t st) {
+  k_ctl_init<<<1, 1, 0, st>>>(ctl, acc, (int32_t)n, k, max_rounds, trace, defer_all ? 1 : 0);
 }
 
 void enqueue_pass(const PassArgs& a, int lanes, int grid_score, int grid_apply, hipStream_t st,

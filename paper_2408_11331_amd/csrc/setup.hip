@@ -475,25 +475,36 @@ __global__ __launch_bounds__(kBlock) void k_ref_labels(const int32_t* const* __r
 }
 
 // rdist[v] = distinct label ids in v's row (the rows of a hashed-rows table
-// v contributes to); *total += their sum.  k <= 64: a wave per vertex, lane
-// i holding partition i, the first lane of each id counted by a ballot;
-// else a thread per vertex.
+// v contributes to); *total += their sum.  Sixteen lanes a vertex, its labels
+// in registers, the smallest id left taken out until none is (KR labels a
+// lane: k <= 16 KR; 0: any k, a thread a vertex).
+template <int KR>
 __global__ __launch_bounds__(kBlock) void k_row_distinct(const int32_t* __restrict__ Lvm,
                                                          int64_t n, int32_t k,
                                                          uint8_t* __restrict__ rdist,
                                                          int64_t* __restrict__ total) {
   int64_t s = 0;
-  if (k <= 64) {
-    const int lane = threadIdx.x & 63;
-    const int64_t nw = ((int64_t)gridDim.x * kBlock) >> 6;
-    for (int64_t v = gtid() >> 6; v < n; v += nw) {
-      const int32_t l = lane < k ? Lvm[v * k + lane] : -1;
-      bool first = lane < k;
-      for (int j = 0; j < k; ++j) {
-        const int32_t o = __shfl(l, j, 64);
-        if (j < lane && o == l) first = false;
+  if constexpr (KR > 0) {
+    constexpr int G = 16;
+    constexpr int32_t kNoId = 0x7fffffff;
+    const int lane = threadIdx.x & (G - 1);
+    const int64_t groups = gstride() / G;
+    for (int64_t v = gtid() / G; v < n; v += groups) {
+      int32_t l[KR];
+#pragma unroll
+      for (int q = 0; q < KR; ++q) l[q] = lane + G * q < k ? Lvm[v * k + lane + G * q] : kNoId;
+      int32_t d = 0;
+      for (;;) {
+        int32_t m = l[0];
+#pragma unroll
+        for (int q = 1; q < KR; ++q) m = min(m, l[q]);
+#pragma unroll
+        for (int o = G / 2; o > 0; o >>= 1) m = min(m, __shfl_xor(m, o, G));
+        if (m == kNoId) break;
+        ++d;
+#pragma unroll
+        for (int q = 0; q < KR; ++q) l[q] = l[q] == m ? kNoId : l[q];
       }
-      const int32_t d = (int32_t)__popcll(__ballot(first));
       if (lane == 0) {
         rdist[v] = (uint8_t)min(d, 255);
         s += d;
@@ -519,18 +530,42 @@ __global__ __launch_bounds__(kBlock) void k_row_distinct(const int32_t* __restri
 
 // Hashed rows from clusters of one vertex each (singletons): row (C[v], l)
 // belongs to v alone, so its counts are stored, 1 at the partitions where
-// v has label id l (the others stay at the zero they were filled with);
-// each cell is written by one thread
+// v has label id l (the others stay at the zero they were filled with).
+// Sixteen lanes a vertex, its labels in registers: the smallest id left is
+// claimed once and stored by the lanes that hold it, so that a vertex costs
+// a claim per distinct id (4.2 of 50 on the kNN workload) instead of a probe
+// per partition (2 M vertices: 5.2 ms).
+template <int KR>  // labels a lane: k <= 16 KR
 __global__ __launch_bounds__(kBlock) void k_build_rows_single(const int32_t* __restrict__ C,
                                                               const int32_t* __restrict__ Lvm,
                                                               int64_t n, int32_t k, Tables t) {
+  constexpr int G = 16;
+  constexpr int32_t kNoId = 0x7fffffff;
+  const int lane = threadIdx.x & (G - 1);
+  const int64_t groups = gstride() / G;
   int32_t claimed = 0;
-  const int64_t total = n * k;
-  for (int64_t j = gtid(); j < total; j += gstride()) {
-    const int64_t v = j / k;
-    const int i = (int)(j - v * k);
-    const uint32_t r = rslot(t, hkey(t, 0, C[v], Lvm[j]), claimed);
-    t.N[(uint64_t)r * (uint64_t)k + (uint64_t)i] = 1;
+  for (int64_t v = gtid() / G; v < n; v += groups) {
+    int32_t l[KR];
+#pragma unroll
+    for (int q = 0; q < KR; ++q) l[q] = lane + G * q < k ? Lvm[v * k + lane + G * q] : kNoId;
+    const int32_t c = C[v];
+    for (;;) {
+      int32_t m = l[0];
+#pragma unroll
+      for (int q = 1; q < KR; ++q) m = min(m, l[q]);
+#pragma unroll
+      for (int o = G / 2; o > 0; o >>= 1) m = min(m, __shfl_xor(m, o, G));
+      if (m == kNoId) break;
+      uint32_t r = 0;
+      if (lane == 0) r = rslot(t, hkey(t, 0, c, m), claimed);
+      r = (uint32_t)__shfl((int32_t)r, 0, G);
+#pragma unroll
+      for (int q = 0; q < KR; ++q)
+        if (l[q] == m) {
+          t.N[(uint64_t)r * (uint64_t)k + (uint64_t)(lane + G * q)] = 1;
+          l[q] = kNoId;
+        }
+    }
   }
   flush_claims(t, claimed);
 }
@@ -541,6 +576,110 @@ __global__ __launch_bounds__(kBlock) void k_build_rows(const int32_t* __restrict
                                                        const int32_t* __restrict__ Lvm, int64_t n,
                                                        int32_t k, Tables t) {
   flush_claims(t, rows_count(t, C, Lvm, n, k, gtid(), gstride()));
+}
+
+// One 32-bit word of compact label rows a thread (the rest of a row is zero).
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_compact_rows(const int32_t* __restrict__ Lvm,
+                                                         int64_t n, int32_t k, int32_t words,
+                                                         uint32_t* __restrict__ out) {
+  constexpr int E = 4 / (int)sizeof(T);
+  const int64_t total = n * words;
+  for (int64_t j = gtid(); j < total; j += gstride()) {
+    const int64_t v = j / words;
+    const int32_t i0 = (int32_t)(j - v * words) * E;
+    uint32_t x = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (i0 + e < k) x |= (uint32_t)Lvm[v * k + i0 + e] << (8 * (int)sizeof(T) * e);
+    out[j] = x;
+  }
+}
+
+// ---- fewer clusters ----------------------------------------------------------
+__global__ __launch_bounds__(kBlock) void k_live(const int32_t* __restrict__ s, int64_t K0,
+                                                 int32_t* __restrict__ flags) {
+  for (int64_t x = gtid(); x < K0; x += gstride()) flags[x] = s[x] > 0;
+}
+
+__global__ __launch_bounds__(kBlock) void k_compact_clusters(
+    const int32_t* __restrict__ cmap, int64_t K0, const int32_t* __restrict__ s,
+    const int32_t* __restrict__ rawid, const int32_t* __restrict__ churn, int32_t K1,
+    int32_t* __restrict__ s2, int32_t* __restrict__ rawid2, int32_t* __restrict__ churn2) {
+  for (int64_t x = gtid(); x < K0; x += gstride()) {
+    if (s[x] == 0) continue;
+    const int32_t y = cmap[x];
+    s2[y] = s[x];
+    rawid2[y] = rawid[x];
+    if (churn) {
+      churn2[y] = churn[x];
+      churn2[K1 + y] = churn[K0 + x];
+    }
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void k_remap(const int32_t* __restrict__ cmap, int64_t n,
+                                                  int32_t* __restrict__ C, void* __restrict__ Cn,
+                                                  int32_t bytes,
+                                                  const int32_t* __restrict__ cnum,
+                                                  int32_t* __restrict__ ccache, int32_t cache) {
+  for (int64_t v = gtid(); v < n; v += gstride()) {
+    const int32_t c = cmap[C[v]];
+    C[v] = c;
+    if (bytes == 1) ((uint8_t*)Cn)[v] = (uint8_t)c;
+    else if (bytes == 2) ((uint16_t*)Cn)[v] = (uint16_t)c;
+    if (!cnum) continue;
+    const int32_t m = cnum[v];
+    if (m > cache) continue;
+    for (int32_t j = 0; j < m; ++j) ccache[v * cache + j] = cmap[ccache[v * cache + j]];
+  }
+}
+
+// A row of k counts per (cluster, label id), copied by k threads: from the
+// hashed rows (every row in use, its key naming cluster and label id) or
+// from an interleaved table (the rows of the clusters that have members).
+__global__ __launch_bounds__(kBlock) void k_rows_densify(Tables t,
+                                                         const int32_t* __restrict__ cmap,
+                                                         const int32_t* __restrict__ s,
+                                                         int64_t rows, Tables to) {
+  const int32_t k = t.k;
+  const int lane = threadIdx.x & 15;
+  const int64_t groups = gstride() >> 4;
+  for (int64_t r = gtid() >> 4; r < rows; r += groups) {
+    int32_t x, l;
+    if (t.rows) {
+      const uint64_t key = t.rkeys[r];
+      if (key == kHashEmpty) continue;
+      x = (int32_t)(key >> 32);
+      l = (int32_t)(uint32_t)key;
+    } else {
+      x = (int32_t)(r / t.Lmax);
+      l = (int32_t)(r - (int64_t)x * t.Lmax);
+    }
+    if (s[x] == 0) continue;
+    const int64_t d = ((int64_t)cmap[x] * to.Lmax + l) * k;
+    for (int i = lane; i < k; i += 16) to.N[d + i] = t.N[r * k + i];
+  }
+}
+
+// The same from hashed keys, a thread a slot; the partition of a global
+// label id by a search of the offsets.
+__global__ __launch_bounds__(kBlock) void k_keys_densify(Tables t,
+                                                         const int32_t* __restrict__ cmap,
+                                                         Tables to) {
+  const uint4* H = reinterpret_cast<const uint4*>(t.N);
+  for (int64_t j = gtid(); j <= (int64_t)t.hmask; j += gstride()) {
+    const uint4 e = H[j];
+    if ((e.x == 0xffffffffu && e.y == 0xffffffffu) || e.z == 0) continue;
+    int lo = 0, hi = t.k - 1;  // the last partition that starts at or before the id
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (t.toff[mid] <= (int64_t)e.x) lo = mid;
+      else hi = mid - 1;
+    }
+    const int64_t l = (int64_t)e.x - t.toff[lo];
+    to.N[((int64_t)cmap[e.y] * to.Lmax + l) * t.k + lo] = (int32_t)e.z;
+  }
 }
 
 // hist[toff[i] + l] = |P_i l| (label ids in the hashed key space)
@@ -1032,13 +1171,60 @@ void launch_ref_labels(const int32_t* const* dlabels, const int64_t* loff, const
 
 void launch_row_distinct(const int32_t* Lvm, int64_t n, int32_t k, uint8_t* rdist, int64_t* total,
                          hipStream_t st) {
-  if (n > 0) k_row_distinct<<<grid_for(n, kBlock, 4096), kBlock, 0, st>>>(Lvm, n, k, rdist, total);
+  if (n <= 0) return;
+  const int g = grid_for(n * 16, kBlock, 4096);
+  if (k <= 16) k_row_distinct<1><<<g, kBlock, 0, st>>>(Lvm, n, k, rdist, total);
+  else if (k <= 32) k_row_distinct<2><<<g, kBlock, 0, st>>>(Lvm, n, k, rdist, total);
+  else if (k <= 64) k_row_distinct<4><<<g, kBlock, 0, st>>>(Lvm, n, k, rdist, total);
+  else k_row_distinct<0><<<grid_for(n, kBlock, 4096), kBlock, 0, st>>>(Lvm, n, k, rdist, total);
+}
+
+void launch_compact_rows(const int32_t* Lvm, int64_t n, int32_t k, int32_t width, int32_t stride,
+                         uint8_t* Lc, hipStream_t st) {
+  if (n <= 0) return;
+  const int32_t words = stride / 4;
+  const int g = grid_for(n * words, kBlock * 4, 8192);
+  uint32_t* out = reinterpret_cast<uint32_t*>(Lc);
+  if (width == 1) k_compact_rows<uint8_t><<<g, kBlock, 0, st>>>(Lvm, n, k, words, out);
+  else k_compact_rows<uint16_t><<<g, kBlock, 0, st>>>(Lvm, n, k, words, out);
+}
+
+void launch_live(const int32_t* s, int64_t K0, int32_t* flags, hipStream_t st) {
+  k_live<<<grid_for(K0, kBlock, 2048), kBlock, 0, st>>>(s, K0, flags);
+}
+
+void launch_compact_clusters(const int32_t* cmap, int64_t K0, const int32_t* s,
+                             const int32_t* rawid, const int32_t* churn, int32_t K1, int32_t* s2,
+                             int32_t* rawid2, int32_t* churn2, hipStream_t st) {
+  k_compact_clusters<<<grid_for(K0, kBlock, 2048), kBlock, 0, st>>>(cmap, K0, s, rawid, churn, K1,
+                                                                   s2, rawid2, churn2);
+}
+
+void launch_remap(const int32_t* cmap, int64_t n, int32_t* C, void* Cn, int32_t bytes,
+                  const int32_t* cnum, int32_t* ccache, int32_t cache, hipStream_t st) {
+  k_remap<<<grid_for(n, kBlock, 4096), kBlock, 0, st>>>(cmap, n, C, Cn, bytes, cnum, ccache,
+                                                       cache);
+}
+
+void launch_densify(const Tables& t, const int32_t* cmap, const int32_t* s, int64_t K0,
+                    const Tables& to, hipStream_t st) {
+  if (t.hashed && !t.rows) {
+    k_keys_densify<<<grid_for((int64_t)t.hmask + 1, kBlock * 4, 4096), kBlock, 0, st>>>(t, cmap,
+                                                                                     to);
+    return;
+  }
+  const int64_t rows = t.rows ? (int64_t)t.hmask + 1 : K0 * t.Lmax;
+  k_rows_densify<<<grid_for(rows * 16, kBlock * 4, 8192), kBlock, 0, st>>>(t, cmap, s, rows, to);
 }
 
 void launch_build_rows_single(const int32_t* C, const int32_t* Lvm, int64_t n, int32_t k,
                               Tables t, hipStream_t st) {
-  if (n > 0)
-    k_build_rows_single<<<grid_for(n * k, kBlock, 8192), kBlock, 0, st>>>(C, Lvm, n, k, t);
+  if (n <= 0) return;
+  const int g = grid_for(n * 16, kBlock, 8192);
+  if (k <= 16) k_build_rows_single<1><<<g, kBlock, 0, st>>>(C, Lvm, n, k, t);
+  else if (k <= 32) k_build_rows_single<2><<<g, kBlock, 0, st>>>(C, Lvm, n, k, t);
+  else if (k <= 64) k_build_rows_single<4><<<g, kBlock, 0, st>>>(C, Lvm, n, k, t);
+  else k_build_rows<<<grid_for(n * k, kBlock, 8192), kBlock, 0, st>>>(C, Lvm, n, k, t);
 }
 
 void launch_build_rows(const int32_t* C, const int32_t* Lvm, int64_t n, int32_t k, Tables t,

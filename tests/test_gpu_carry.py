@@ -29,11 +29,13 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
-def check(mcc, row_ptr, col, labels, init, flags=0, max_rounds=0):
+def check(mcc, row_ptr, col, labels, init, flags=0, max_rounds=0, want=None):
     out, st, tr = mcc.consensus(dev(row_ptr), dev(col), dev(labels),
                                 None if init is None else dev(init), flags=flags, trace=True,
                                 max_rounds=max_rounds)
-    eo, est, et = oracle.consensus(row_ptr, col, labels, init, trace=True, max_rounds=max_rounds)
+    if want is None:
+        want = oracle.consensus(row_ptr, col, labels, init, trace=True, max_rounds=max_rounds)
+    eo, est, et = want
     assert np.array_equal(out.cpu().numpy(), eo)
     assert [tuple(t) for t in et][:st["passes"]] == tr
     for key in KEYS:
@@ -101,3 +103,33 @@ def test_many_candidates_many_partitions(mcc, symmetric):
         rp, col = synth.graph.csr_from_edges(n, u, v)
         check(mcc, rp, col, noisy(n, k, 30, rng), None,
               mcc.MCC_F_SYMMETRIC if symmetric else 0)
+
+
+@pytest.mark.parametrize("k", [1, 16, 17, 32, 33, 64, 65])
+@pytest.mark.parametrize("ids", ["aligned", "mixed", "wide"])
+def test_fewer_clusters(mcc, k, ids):
+    """From singletons the tables start hashed and become dense once few
+    clusters are left; member rows of 1-byte ids (aligned labels: the row
+    table), and of 2-byte ids; labels a lane at its edges.  The forced hashed
+    layouts, which stay hashed, agree."""
+    print(f"[gpu-case] carry fewer clusters k={k} {ids}", flush=True)
+    rng = np.random.default_rng(k)
+    n = 9000
+    u, v = rng.integers(0, n, 9 * n), rng.integers(0, n, 9 * n)
+    near = rng.random(9 * n) < 0.8
+    v[near] = (u[near] + rng.integers(1, 20, int(near.sum()))) % n
+    rp, col = synth.graph.csr_from_edges(n, u, v)
+    groups = 240 if ids == "aligned" else 300
+    labels = noisy(n, k, groups, rng)
+    if ids != "aligned":  # label names of their own in every partition
+        for i in range(k):
+            labels[i] = rng.permutation(groups)[labels[i]]
+    if ids == "wide":  # ids beyond one byte and gaps
+        labels = labels * 7 + 3
+    want = oracle.consensus(rp, col, labels, None, trace=True, max_rounds=12)
+    for flags in (0, mcc.MCC_F_SYMMETRIC):
+        st = check(mcc, rp, col, labels, None, flags, 12, want)
+        # hashed where the dense cells would pass 2^24
+        assert (st["tables"] in (2, 3)) == (n * k * groups > 1 << 24)
+    for flags in (mcc.MCC_F_HASH_KEYS, mcc.MCC_F_HASH_ROWS):
+        check(mcc, rp, col, labels, None, flags | mcc.MCC_F_SYMMETRIC, 12, want)
