@@ -494,9 +494,11 @@ void align_to_reference(Arena& ar, Solve* S, int32_t maxL, int64_t sumL, int32_t
 // The full setup: compaction of labels and clusters, tables, initial
 // objective.  `init` null means singletons.  `want_rows` builds the
 // vertex-major label rows the passes read.  hash_mode: kHash* bits.
+// known_max >= 0: the inputs were found valid and no label exceeds it (the
+// first sweep over them and its synchronisation are left out).
 void build_solve(Arena& ar, const std::vector<const int32_t*>& hptrs, int64_t n,
                  const int32_t* init, bool want_rows, const mcc_csr* g_validate, Solve* S,
-                 hipStream_t st, uint32_t hash_mode = 0) {
+                 hipStream_t st, uint32_t hash_mode = 0, int64_t known_max = -1) {
   const int32_t k = (int32_t)hptrs.size();
   S->n = n;
   S->k = k;
@@ -512,10 +514,17 @@ void build_solve(Arena& ar, const std::vector<const int32_t*>& hptrs, int64_t n,
     launch_validate_csr(g_validate->row_ptr, g_validate->col, n, g_validate->nnz, err, st);
   int32_t herr = 0;
   std::vector<int32_t> maxlab;
-  compact_labels(ar, hptrs, n, &S->lab, err, st, &herr, &maxlab);
-  sync(st);
-  if (herr & kErrGraph) throw Status{MCC_EGRAPH};
-  if (herr & (kErrNegLabel | kErrInitRange)) throw Status{MCC_EINVAL};
+  if (known_max >= 0) {
+    maxlab.assign(k, (int32_t)known_max);
+    const int32_t** dl = ar.get<const int32_t*>(k);
+    h2d(dl, ar.host(hptrs), k, st);
+    S->lab.dlabels = dl;
+  } else {
+    compact_labels(ar, hptrs, n, &S->lab, err, st, &herr, &maxlab);
+    sync(st);
+    if (herr & kErrGraph) throw Status{MCC_EGRAPH};
+    if (herr & (kErrNegLabel | kErrInitRange)) throw Status{MCC_EINVAL};
+  }
   compact_labels_finish(ar, n, k, maxlab, &S->lab, st);
   int32_t* cmap = nullptr;
   if (init) {
@@ -1087,12 +1096,20 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
     }
 }
 
+// Largest label value a refused small instance may hand on as known_max: the
+// label flags are then sized to it for every partition.
+bool known_max_pays(int64_t lmax, int32_t k) {
+  return (lmax + 1) * k <= ((int64_t)1 << 22) && (lmax + 1) * k <= kMaxLabelFlags;
+}
+
 // The table of one small instance with few clusters (`init` against k
 // partitions): the objective without any pass, for the evaluation calls.
-// False when the kernels do not take it (an id outside [0, n) among the
-// reasons) and nothing was computed.
+// False when the kernels do not take it and nothing was computed; *known is
+// then the largest label if the inputs are valid (the ids of init lie in
+// [0, n), no label is negative), else -1.
 bool multi_table(Arena& ar, const int32_t* const* labels, int32_t k, int64_t n,
-                 const int32_t* init, hipStream_t st, MultiSet* S) {
+                 const int32_t* init, hipStream_t st, MultiSet* S, int64_t* known) {
+  *known = -1;
   if (n > kMultiVertices || k > 256) return false;
   mcc_problem one{};
   one.g.n = n;
@@ -1102,7 +1119,11 @@ bool multi_table(Arena& ar, const int32_t* const* labels, int32_t k, int64_t n,
   multi_ranges(ar, &one, {0}, 1, false, false, st, S);
   MultiInst& m = S->inst[0];
   const int64_t Ls = (int64_t)S->ctl[0].lmax + 1;
-  if (S->ctl[0].err || !multi_fits(n, S->ctl[0].K0, Ls)) return false;
+  if (S->ctl[0].err) return false;
+  if (!multi_fits(n, S->ctl[0].K0, Ls)) {
+    if (known_max_pays(S->ctl[0].lmax, k)) *known = S->ctl[0].lmax;
+    return false;
+  }
   m.K0 = S->ctl[0].K0;
   m.Ls = (int32_t)Ls;
   m.rs = multi_row(n, m.K0);
@@ -1212,7 +1233,8 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     HIPCK(hipEventRecord(e0, st));
 
     // a small instance with few clusters: the level-by-level kernels, three
-    // launches a pass instead of ten or more
+    // launches a pass instead of eight or more
+    int64_t known = -1;  // the largest label, once the inputs are known to be valid
     if (lanes_req == 0 && n <= kMultiVertices && k <= 256 && (init || n <= kMultiClusters) &&
         !(flags & ~(MCC_F_TRACE | MCC_F_LITERAL | MCC_F_SYMMETRIC))) {
       unsigned char* const before = ar.mark();
@@ -1238,6 +1260,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
         return MCC_OK;
       }
       ar.rewind(before);  // the scratch array holds what it held without the attempt
+      if (!noalloc && known_max_pays(r.Ls - 1, k)) known = r.Ls - 1;
     }
 
     const hipEvent_t e1 = events.make(), e2 = events.make();
@@ -1246,7 +1269,8 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     build_solve(ar, hptrs, n, init, true, (flags & MCC_F_VALIDATE) ? g : nullptr, &S, st,
                 ((flags & MCC_F_HASH_TABLES) ? kHashForce : 0u) |
                     ((flags & MCC_F_HASH_ROWS) ? kHashRows : 0u) |
-                    ((flags & MCC_F_HASH_KEYS) ? kHashKeys : 0u));
+                    ((flags & MCC_F_HASH_KEYS) ? kHashKeys : 0u),
+                known);
 
     int64_t* dtrace = nullptr;
     if (flags & MCC_F_TRACE) dtrace = ar.get<int64_t>((int64_t)max_rounds * 4);
@@ -1558,14 +1582,15 @@ int mcc_objective(const int32_t* c, const int32_t* const* labels, int32_t k, int
   try {
     Arena ar(st);
     MultiSet small;
-    if (multi_table(ar, labels, k, n, c, st, &small)) {
+    int64_t known = -1;
+    if (multi_table(ar, labels, k, n, c, st, &small, &known)) {
       sync(st);
       *result = small.ctl[0].O;
       return MCC_OK;
     }
     std::vector<const int32_t*> hptrs(labels, labels + k);
     Solve S;
-    build_solve(ar, hptrs, n, c, false, nullptr, &S, st);
+    build_solve(ar, hptrs, n, c, false, nullptr, &S, st, 0, known);
     int64_t acc[3];
     d2h(acc, S.acc, 3, st);
     sync(st);
@@ -1587,9 +1612,19 @@ int mcc_mirkin(const int32_t* a, const int32_t* b, int64_t n, int64_t* result, v
   try {
     Arena ar(st);
     MultiSet small;
-    if (multi_table(ar, &b, 1, n, a, st, &small)) {
+    int64_t known = -1;
+    if (multi_table(ar, &b, 1, n, a, st, &small, &known)) {
       sync(st);
       *result = small.ctl[0].O;
+      return MCC_OK;
+    }
+    if (known >= 0) {  // a's ids lie in [0, n): they serve as they are
+      Solve S;
+      build_solve(ar, {b}, n, a, false, nullptr, &S, st, 0, known);
+      int64_t acc[3];
+      d2h(acc, S.acc, 3, st);
+      sync(st);
+      *result = acc[0] + acc[1] - 2 * acc[2];
       return MCC_OK;
     }
     // dense ids of a (in [0, n)) serve as the consensus, b as the single
@@ -2306,7 +2341,8 @@ int mcc_compare(const int32_t* a, const int32_t* b, int64_t n, mcc_comparison* r
       r->clusters_b = kb;
     };
     MultiSet small;
-    if (multi_table(ar, &b, 1, n, a, st, &small)) {
+    int64_t known = -1;
+    if (multi_table(ar, &b, 1, n, a, st, &small, &known)) {
       MultiCompare* dc = ar.get<MultiCompare>(1);
       launch_multi_compare(small.a, dc, st);
       MultiCompare c;
@@ -2319,22 +2355,27 @@ int mcc_compare(const int32_t* a, const int32_t* b, int64_t n, mcc_comparison* r
       }
     }
     // the table of (cluster of a, label of b): dense ids of a as the
-    // consensus, b as the one partition
-    std::vector<const int32_t*> pa{a};
-    Compacted ca;
-    int32_t* err = ar.get<int32_t>(1);
-    launch_fill_i32(err, 1, 0, st);
-    int32_t herr = 0;
-    std::vector<int32_t> maxlab;
-    compact_labels(ar, pa, n, &ca, err, st, &herr, &maxlab);
-    sync(st);
-    if (herr & kErrNegLabel) return MCC_EINVAL;
-    compact_labels_finish(ar, n, 1, maxlab, &ca, st);
-    int32_t* da = ar.get<int32_t>(n);
-    launch_dense_map(a, n, ca.scan, da, st);
+    // consensus (a itself where its ids are known to lie in [0, n)), b as the
+    // one partition
+    const int32_t* da = a;
+    if (known < 0) {
+      std::vector<const int32_t*> pa{a};
+      Compacted ca;
+      int32_t* err = ar.get<int32_t>(1);
+      launch_fill_i32(err, 1, 0, st);
+      int32_t herr = 0;
+      std::vector<int32_t> maxlab;
+      compact_labels(ar, pa, n, &ca, err, st, &herr, &maxlab);
+      sync(st);
+      if (herr & kErrNegLabel) return MCC_EINVAL;
+      compact_labels_finish(ar, n, 1, maxlab, &ca, st);
+      int32_t* dense = ar.get<int32_t>(n);
+      launch_dense_map(a, n, ca.scan, dense, st);
+      da = dense;
+    }
     std::vector<const int32_t*> pb{b};
     Solve S;
-    build_solve(ar, pb, n, da, false, nullptr, &S, st);
+    build_solve(ar, pb, n, da, false, nullptr, &S, st, 0, known);
     const int32_t K0 = S.K0, Lb = S.lab.Lh[0];
     int32_t* rowmax = ar.get<int32_t>(K0);
     int32_t* colmax = ar.get<int32_t>(Lb);
