@@ -1382,8 +1382,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     // the arcs of a symmetric graph, else pulled (not beside the arc cache,
     // nor where the scratch array has no room for them).
     const bool push = (flags & MCC_F_SYMMETRIC) != 0;
-    if (lanes == 0 && (push || (!(flags & MCC_F_ARC_CACHE) &&
-                                ar.fits(carry_bytes(n, S.K0))))) {
+    if (lanes == 0 && (push || !(flags & MCC_F_ARC_CACHE)) && ar.fits(carry_bytes(n, S.K0))) {
       if (!push) {
         a.moved = ar.get<uint32_t>((n + 31) / 32);
         launch_fill_i32(reinterpret_cast<int32_t*>(a.moved), (n + 31) / 32, 0, st);

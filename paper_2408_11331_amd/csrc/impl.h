@@ -509,7 +509,11 @@ constexpr int kCounterStride = 64;  // int64 words between two counters
 // Candidate clusters cached per vertex.  An LFR vertex of degree 20 has ten
 // candidates: with room for 8, half of the vertices of 1 M were scored anew
 // in each of 36 passes (0.93 ms a pass where a hundred vertices moved).
-constexpr int kCacheCand = 16;
+// With room for 16, the twelfth of them with more were, by the largest move
+// count of all clusters (0.15 to 0.6 ms a pass).  Sets of up to kListLanes are
+// rescored from the cache, larger ones only bounded by it.
+constexpr int kCacheCand = 32;
+constexpr int kListLanes = 16;  // lanes a vertex of the list scorer
 
 // Compile-time variants: CN is the narrow copy's width in bytes (0: read the
 // per-arc cache), IL selects the interleaved table layout.

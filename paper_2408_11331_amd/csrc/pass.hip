@@ -140,7 +140,8 @@ __device__ inline int32_t agree16(const uint4& a, const uint4& b) {
   return zeros16(a.x ^ b.x) + zeros16(a.y ^ b.y) + zeros16(a.z ^ b.z) + zeros16(a.w ^ b.w);
 }
 
-template <int G, bool LIST>
+// MEM: hashed tables, whose small clusters are scored from member rows.
+template <int G, bool LIST, bool MEM>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_score(PassArgs a) {
   if (a.ctl->done || a.ctl->stage) return;
   // LIST: the vertices the tiled or list scorer deferred or, in a dense pass
@@ -160,10 +161,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
   // deferred-vertex scorer, per wave: items' first member pair, sums, member
   // list starts, clusters, and the items of clusters without member lists
   constexpr int kW = (LIST && G == 64) ? kBlock / 64 : 1;
-  constexpr int kI = (LIST && G == 64) ? 130 : 1;
+  constexpr int kI = (LIST && G == 64 && MEM) ? 130 : 1;
   __shared__ int32_t s_ioff[kW][kI], s_imst[kW][kI], s_iy[kW][kI], s_ilarge[kW][kI];
   __shared__ int32_t s_isum[kW][(LIST && G == 64) ? kCandSet + 2 : 1];
-  __shared__ __align__(8) int32_t s_vrow[kW][(LIST && G == 64) ? 64 : 2];
+  __shared__ __align__(8) int32_t s_vrow[kW][(LIST && G == 64 && MEM) ? 64 : 2];
   __shared__ int32_t s_cset[kW][(LIST && G == 64) ? kCandSet : 1];
   __shared__ int32_t s_cnb[kW][(LIST && G == 64) ? kCandSet : 1];  // a neighbour in the cluster
   __shared__ int32_t s_clist[kW][(LIST && G == 64) ? kCandSet : 1];
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
     // S_y(v) summed over the group's lanes
     auto agree = [&](int32_t y) -> int32_t {
       int32_t sum = 0;
-      if (a.members && a.s[y] <= a.msum_max) {
+      if (MEM && a.s[y] <= a.msum_max) {
         // S_y(v) = sum over members u of y of the partitions agreeing on u, v;
         // the member ids are read once, one per lane, and broadcast
         const int32_t cnt = a.s[y], b = a.mstart[y];
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
         int32_t nc = s_ccount[w];
         // more than 128 candidates (with member lists), or as many as the set
         // holds: the general path below
-        const bool many = a.members ? nc > 128 : nc >= kCandSet;
+        const bool many = MEM ? nc > 128 : nc >= kCandSet;
         int32_t cand_lo = kInf, cand_hi = kInf;
         if (!many) {
           int32_t mine = 0, keys[kCandSet / 64];
@@ -360,7 +361,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
           for (int q = 0; q < 4; ++q) lb[q] = sl + 16 * q < k ? row[sl + 16 * q] : 0;
           int32_t s_lo = 0, s_hi = 0, s_v = 0;
           const int nitems = nc + 1;  // item 0: the own cluster; item c + 1: candidate c
-          if (a.members) {
+          if constexpr (MEM) {
             // Small clusters (member lists) are scored by their members' label
             // rows, every member row of every small item in flight at once:
             // four lanes per (item, member) pair, sixteen pairs a step, the
@@ -542,10 +543,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
             s_hi = isum[65 + lane];
             __builtin_amdgcn_wave_barrier();
           } else {
-            // table probes, four items a step and group, the sums of a lane's
+            // table probes, eight items a step and group, the sums of a lane's
             // items kept in LDS (the latency of a probe, not the sums, is what
             // a step costs: a hub's forty candidates took ten dependent steps)
-            constexpr int D = 4;
+            constexpr int D = 8;
             int32_t* isum = s_isum[w];
             const int32_t* clist = s_clist[w];
             for (int j0 = 0; j0 < nitems; j0 += 4 * D) {
@@ -582,7 +583,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
               bx = xc;
             }
           };
-          if (a.members) {
+          if constexpr (MEM) {
             if (lane < nc) consider(cand_lo, s_lo);
             if (lane + 64 < nc) consider(cand_hi, s_hi);
           } else {
@@ -1196,7 +1197,7 @@ __global__ __launch_bounds__(kBlock) void k_status(PassArgs a) {
       if (known == 0) {
         a.prop[v] = kNone;
       } else if (known > 0) {
-        stv[j] = known <= kCacheCand ? known : 0;
+        stv[j] = known <= kListLanes ? known : 0;
         if (sl[j] >= 0) {
           // the candidates' largest move count, by the cheap bound first
           const int64_t own = churn[cv[j]];
@@ -1249,12 +1250,12 @@ __global__ __launch_bounds__(kBlock) void k_status(PassArgs a) {
 // List scorer: the vertices of the rescoring list, in passes where they are
 // few, kListLanes lanes per vertex.  A vertex's candidates come from its
 // cache or from its arcs (distinct neighbour clusters, in increasing id, one
-// per lane); its own cluster and the candidates are then probed four at a
-// time with every probe of the four issued together.  Vertices with more
-// candidates than lanes, a degree beyond the arc registers or k beyond the
-// label registers go to the deferred list (the wave-per-vertex scorer).
+// per lane); its own cluster and the candidates are then probed eight at a
+// time (four in hashed tables) with all their probes issued together.
+// Vertices with more candidates than lanes, a degree beyond the arc registers
+// or k beyond the label registers go to the deferred list (the
+// wave-per-vertex scorer).
 // ---------------------------------------------------------------------------
-constexpr int kListLanes = 16;
 
 template <int CN, int TK>
 __global__ __launch_bounds__(kBlock) void k_score_list(PassArgs a) {
@@ -1343,10 +1344,11 @@ __global__ __launch_bounds__(kBlock) void k_score_list(PassArgs a) {
     const int64_t scv = a.s[cv];
     int64_t s_own = 0, bd = 0;
     int32_t bx = kNone;
-    for (int i0 = 0; i0 <= nc; i0 += 4) {  // item 0: own cluster; item j: candidate j - 1
-      int32_t part[4], ys[4];
+    constexpr int D = TK == kHashed ? 4 : 8;  // items in flight
+    for (int i0 = 0; i0 <= nc; i0 += D) {  // item 0: own cluster; item j: candidate j - 1
+      int32_t part[D], ys[D];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < D; ++q) {
         const int it = i0 + q;
         const int32_t yc = __shfl(cand, it > 0 ? (it - 1) & (G - 1) : 0, G);
         ys[q] = it == 0 ? cv : (it <= nc ? yc : -1);
@@ -1360,7 +1362,7 @@ __global__ __launch_bounds__(kBlock) void k_score_list(PassArgs a) {
         }
       }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < D; ++q) {
         const int64_t sum = group_sum<G>(part[q]);
         if (ys[q] < 0) continue;
         if (i0 + q == 0) {
@@ -2034,7 +2036,8 @@ __global__ void k_ctl_init(Ctl* ctl, const int64_t* acc, int32_t n, int32_t k, i
 
 template <int G>
 void launch_score(const PassArgs& a, int grid, hipStream_t st) {
-  k_score<G, false><<<grid, kBlock, 0, st>>>(a);
+  if (a.members) k_score<G, false, true><<<grid, kBlock, 0, st>>>(a);
+  else k_score<G, false, false><<<grid, kBlock, 0, st>>>(a);
 }
 
 template <int TK, int TV>
@@ -2099,7 +2102,8 @@ void enqueue_pass(const PassArgs& a, int lanes, int grid_score, int grid_apply, 
       else if (a.t.interleaved) launch_tile<kInterleaved>(a, grid_score, st);
       else launch_tile<kBlocked>(a, grid_score, st);
       // deferred vertices: one per wave, as many waves as the chip holds
-      k_score<64, true><<<grid_score, kBlock, 0, st>>>(a);
+      if (a.members) k_score<64, true, true><<<grid_score, kBlock, 0, st>>>(a);
+      else k_score<64, true, false><<<grid_score, kBlock, 0, st>>>(a);
       break;
     case 4: launch_score<4>(a, grid_score, st); break;
     case 8: launch_score<8>(a, grid_score, st); break;

@@ -133,3 +133,21 @@ def test_fewer_clusters(mcc, k, ids):
         assert (st["tables"] in (2, 3)) == (n * k * groups > 1 << 24)
     for flags in (mcc.MCC_F_HASH_KEYS, mcc.MCC_F_HASH_ROWS):
         check(mcc, rp, col, labels, None, flags | mcc.MCC_F_SYMMETRIC, 12, want)
+
+
+@pytest.mark.parametrize("symmetric", [False, True])
+@pytest.mark.parametrize("k", [4, 20])
+def test_cached_sets(mcc, symmetric, k):
+    # candidate sets at the edges of a cache (32) and of a list's lanes (16):
+    # larger ones than the lanes are bounded by the cache, not rescored from it
+    print(f"[gpu-case] carry cached sets symmetric={symmetric} k={k}", flush=True)
+    rng = np.random.default_rng(k)
+    n, groups = 6000, 1500
+    u, v = [np.arange(n - 1)], [np.arange(1, n)]
+    for j in range(400):
+        u.append(np.full(14 + j % 21, 7 + 15 * j))  # degrees 14 to 34
+        v.append(rng.choice(n, 14 + j % 21, replace=False))
+    rp, col = synth.graph.csr_from_edges(n, np.concatenate(u), np.concatenate(v))
+    labels = noisy(n, k, groups, rng)
+    init = (np.arange(n) // 2 * 2).astype(np.int32)
+    check(mcc, rp, col, labels, init, mcc.MCC_F_SYMMETRIC if symmetric else 0)
