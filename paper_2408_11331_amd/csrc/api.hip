@@ -347,7 +347,13 @@ struct Solve {
   int64_t total = 0;       // table cells
   int64_t* acc = nullptr;  // sum s^2, sum |P_il|^2, sum N^2
   uint8_t* rdist = nullptr;  // hashed rows: distinct label ids per vertex
+  uint32_t* Lp = nullptr;    // label ids of four partitions a word (slice scorer)
 };
+
+// Workspace of the candidate sets carried over between passes.
+int64_t carry_bytes(int64_t n, int64_t K0) {
+  return 4 * (5 * n + n * kCacheCand + 2 * K0 + (n + 31) / 32) + 8 * 256;
+}
 
 // Largest cluster count for which labels are aligned to clusters.
 constexpr int32_t kAlignMaxClusters = 1 << 16;
@@ -498,7 +504,8 @@ void align_to_reference(Arena& ar, Solve* S, int32_t maxL, int64_t sumL, int32_t
 // first sweep over them and its synchronisation are left out).
 void build_solve(Arena& ar, const std::vector<const int32_t*>& hptrs, int64_t n,
                  const int32_t* init, bool want_rows, const mcc_csr* g_validate, Solve* S,
-                 hipStream_t st, uint32_t hash_mode = 0, int64_t known_max = -1) {
+                 hipStream_t st, uint32_t hash_mode = 0, int64_t known_max = -1,
+                 bool want_words = false) {
   const int32_t k = (int32_t)hptrs.size();
   S->n = n;
   S->k = k;
@@ -714,7 +721,15 @@ void build_solve(Arena& ar, const std::vector<const int32_t*>& hptrs, int64_t n,
   }
   if (want_rows) {
     S->Lvm = ar.get<int32_t>(n * k);
-    launch_label_transpose(S->lab.dlabels, k, n, S->lab.loff, S->lab.fmap, S->Lvm, st);
+    // label words for the slice scorer, where they leave room for the arrays
+    // that the solve still takes
+    PassArgs shape{};
+    const int64_t words = (int64_t)((k + 3) / 4) * n;
+    if (want_words && aligned && label_words_ok(k) && slice_shape(n, k, K0, S->maxL, &shape) &&
+        ar.fits(4 * words + 4 * (int64_t)k * shape.slice_cells + carry_bytes(n, K0) + 48 * n +
+                64 * (int64_t)K0 + 16 * (sumL + (int64_t)k * K0) + ((int64_t)1 << 20)))
+      S->Lp = ar.get<uint32_t>(words);
+    launch_label_transpose(S->lab.dlabels, k, n, S->lab.loff, S->lab.fmap, S->Lvm, st, S->Lp);
   }
   S->acc = ar.get<int64_t>(3);
   launch_fill_u64(reinterpret_cast<uint64_t*>(S->acc), 3, 0ull, st);
@@ -1172,11 +1187,6 @@ bool densify_pays(int64_t n, int32_t k, int64_t K0, int64_t K1, int64_t Lmax) {
          cells + 2 * K1 < ((int64_t)1 << 31);
 }
 
-// Workspace of the candidate sets carried over between passes.
-int64_t carry_bytes(int64_t n, int64_t K0) {
-  return 4 * (5 * n + n * kCacheCand + 2 * K0 + (n + 31) / 32) + 8 * 256;
-}
-
 // One solve.  noalloc: the workspace is the device's scratch array instead
 // of the cached chunks (nothing is allocated).
 int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
@@ -1273,7 +1283,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
                 ((flags & MCC_F_HASH_TABLES) ? kHashForce : 0u) |
                     ((flags & MCC_F_HASH_ROWS) ? kHashRows : 0u) |
                     ((flags & MCC_F_HASH_KEYS) ? kHashKeys : 0u),
-                known);
+                known, lanes_req == 0 && !(flags & MCC_F_ARC_CACHE));
 
     int64_t* dtrace = nullptr;
     if (flags & MCC_F_TRACE) dtrace = ar.get<int64_t>((int64_t)max_rounds * 4);
@@ -1369,6 +1379,11 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
         a.msum_max = kMemberSumMax;
       }
     }
+    if (S.Lp) {
+      (void)slice_shape(n, k, S.K0, S.maxL, &a);
+      a.Lp = S.Lp;
+      a.slices = ar.get<int32_t>((int64_t)k * a.slice_cells);
+    }
     a.cn_bytes = S.K0 <= 256 ? 1 : (S.K0 <= 65536 ? 2 : 4);
     if (a.cn_bytes == 4) {
       a.Cn = S.C;
@@ -1400,6 +1415,9 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
       a.st = ar.get<int32_t>(n);
       a.rlist = ar.get<int32_t>(n);
       a.sparse_max = (int32_t)std::max<int64_t>(1, n / 8);
+      // the slice scorer's tiles are listed vertices: it takes all but the
+      // passes that leave most compute units without one
+      if (a.Lp) a.sparse_max = std::min(a.sparse_max, kSliceListMax);
       // the cached candidate rows are read as 16-byte vectors
       launch_fill_i32(a.slack, n, -1, st);
       launch_fill_i32(a.churn, 2 * (int64_t)S.K0, 0, st);
@@ -2727,6 +2745,9 @@ int mcc_workspace_bound(int64_t n, int64_t nnz, int32_t k, int64_t max_label, in
     big += dbig;
   }
   add(4 * nk); add(24);  // label rows, objective sums
+  if (n >= kSliceVertices && !(flags & MCC_F_ARC_CACHE)) {  // slice scorer
+    add((nk + 3 * n)); add((int64_t)k * kSliceLds / 4);
+  }
   // per-pass state
   add(sizeof(Ctl)); add(8 * K0); add(4 * n); add(8 * n); add(4 * n); add(4 * n);
   add(8 * (kPassCounters + kTickets) * kCounterStride); add(2 * n); add(4); add(4);

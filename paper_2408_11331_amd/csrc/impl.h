@@ -268,7 +268,10 @@ void launch_label_ids(const int32_t* scan, const int64_t* loff, int32_t k, int64
                       int32_t* fmap, hipStream_t st);
 void launch_label_transpose(const int32_t* const* dlabels, int32_t k, int64_t n,
                             const int64_t* loff, const int32_t* fmap, int32_t* Lvm,
-                            hipStream_t st);
+                            hipStream_t st, uint32_t* Lp = nullptr);
+// Whether k partitions are transposed by tiles, which can also write the
+// label words of PassArgs::Lp.
+bool label_words_ok(int32_t k);
 // Label alignment from a blocked table: amap[poff[i] + l] = new id of dense
 // label l of partition i, L2[i] = new id bound of partition i.
 void launch_align(const Tables& blocked, int32_t k, int32_t K0, int32_t maxL,
@@ -495,11 +498,33 @@ struct PassArgs {
   // the proposal list; 0: the hashed aggregation (k_apply_all).
   int32_t delta_lds;
   int32_t delta_slices;
+  // Slice scorer (few clusters, many vertices): the label ids of four
+  // partitions a word (Lp[(i / 4) n + v], a byte each, zero past k), the
+  // dense table as one slice a partition (k_slices: count (l, x) of
+  // partition i at i slice_cells + l slice_row + x), and the LDS the scorer
+  // is launched with, slice_load slices of it at a time.  Null: the tiled
+  // scorer.
+  const uint32_t* Lp;
+  int32_t* slices;
+  int32_t slice_row;
+  int32_t slice_cells;
+  int32_t slice_load;
+  int32_t slice_lds;
   int32_t tile_grid;    // most workgroups of the tiled scorer
   int32_t tile_small;   // 1: tiles of 64 (the last pass had many candidates a vertex)
 };
 
 constexpr int kDeltaLdsMax = 48 << 10;
+
+// The slice scorer: a tile of 1024 vertices for each of 256 compute units at
+// the least, and half of a compute unit's LDS, so that two are resident.
+constexpr int64_t kSliceVertices = (int64_t)1 << 18;
+constexpr int kSliceLds = 80 << 10;
+constexpr int32_t kSliceListMax = 1 << 16;
+
+// Geometry of the slice scorer for K0 clusters and label ids below Lmax;
+// false where it does not apply (see launch_slices in pass.hip).
+bool slice_shape(int64_t n, int32_t k, int64_t K0, int64_t Lmax, PassArgs* a);
 
 constexpr int kPassCounters = 5;    // evaluations, proposals, boundary vertices, skipped,
                                     // boundary vertices with more candidates than a tile holds
@@ -553,10 +578,11 @@ __device__ inline void cn_store(const PassArgs& a, int64_t u, int32_t c) {
   else ((int32_t*)a.Cn)[u] = c;
 }
 
-// Exclusive scan of one value per thread over a kBlock-thread workgroup;
+// Exclusive scan of one value per thread over a workgroup of B threads;
 // *total receives the sum.  Contains barriers: call from all threads.
+template <int B = kBlock>
 __device__ inline int32_t block_exclusive_scan(int32_t x, int32_t* total) {
-  __shared__ int32_t wsum[kBlock / 64];
+  __shared__ int32_t wsum[B / 64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   int32_t v = x;
 #pragma unroll
@@ -568,7 +594,7 @@ __device__ inline int32_t block_exclusive_scan(int32_t x, int32_t* total) {
   __syncthreads();
   int32_t off = 0, tot = 0;
 #pragma unroll
-  for (int j = 0; j < kBlock / 64; ++j) {
+  for (int j = 0; j < B / 64; ++j) {
     if (j < w) off += wsum[j];
     tot += wsum[j];
   }

@@ -93,9 +93,10 @@ __device__ inline int32_t wave_sum32(int32_t x) {
 
 // Add the workgroup's totals of the pass counters (all threads call; one
 // atomic per counter and workgroup).
+template <int B = kBlock>
 __device__ inline void flush_counts(const PassArgs& a, int64_t evals, int64_t nprop,
                                     int64_t boundary, int64_t skipped, int64_t wide = 0) {
-  __shared__ int64_t red[kPassCounters][kBlock / 64];
+  __shared__ int64_t red[kPassCounters][B / 64];
   const int64_t v[kPassCounters] = {evals, nprop, boundary, skipped, wide};
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
@@ -107,7 +108,7 @@ __device__ inline void flush_counts(const PassArgs& a, int64_t evals, int64_t np
   if (threadIdx.x < kPassCounters) {
     int64_t tot = 0;
 #pragma unroll
-    for (int j = 0; j < kBlock / 64; ++j) tot += red[threadIdx.x][j];
+    for (int j = 0; j < B / 64; ++j) tot += red[threadIdx.x][j];
     if (tot) atomicAdd((unsigned long long*)&a.pc[threadIdx.x * kCounterStride],
                        (unsigned long long)tot);
   }
@@ -1116,6 +1117,276 @@ void k_score_tile(PassArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// Slice scorer: few clusters and many vertices, where four partitions'
+// slices of the table fit half of the LDS.  k_slices writes the interleaved
+// table as one slice a partition (half a megabyte for 51 clusters and 50
+// partitions); a workgroup scores a tile of 1024 vertices of the rescoring
+// list, one a thread:
+//  1. arcs, spread over all threads: the head's cluster sets a bit of the
+//     tail's mask (cached candidate sets set theirs without arcs);
+//  2. the vertices are put in order of their candidates;
+//  3. the agreement sums: two or more slices at a time in LDS, the counts of
+//     the own cluster and of up to 11 candidates a round added in registers,
+//     labels read as words of four partitions.  Vertices with more candidates
+//     take further rounds, or, where they are few in the tile, go to the
+//     wave-per-vertex scorer;
+//  4. the smallest (gain, cluster id).
+// The counts of a candidate come from LDS where the tiled scorer gathers them
+// from L2, sixteen lanes a pair.  Bound by latency, about 40 us a tile for
+// the arcs (columns from HBM, then clusters) and 55 us for the sums (label
+// words from HBM, slices from L2) with two workgroups a compute unit; LDS is
+// busy a fifth of the time.  2 M kNN vertices, 51 clusters, 50 partitions, a
+// pass over all of them 1.22 -> 0.56 ms, over half 0.66 -> 0.30, over a
+// twentieth 0.17 -> 0.10 (from the list scorer); the solve 7.4 -> 5.2 ms.
+// One workgroup a compute unit with all of its LDS: 0.68 ms; slices through
+// registers instead of straight to LDS: 0.59; eight lanes a vertex for the
+// arcs: 0.69.
+// ---------------------------------------------------------------------------
+constexpr int kSliceTile = 1024;
+constexpr int kSliceItems = 12;     // the own cluster and the candidates of a round
+constexpr int kSliceStatic = 1024;  // bytes of the kernel's own arrays, at most
+
+__global__ __launch_bounds__(kBlock) void k_slices(PassArgs a) {
+  const Ctl* ctl = a.ctl;
+  if (ctl->done || ctl->stage) return;
+  if (a.st && ctl->rescore_count <= a.sparse_max) return;
+  const int32_t k = a.k, Lmax = a.t.Lmax;
+  const int32_t cells = (int32_t)a.cells;
+  for (int32_t j = blockIdx.x * kBlock + threadIdx.x; j < cells; j += gridDim.x * kBlock) {
+    const int32_t row = j / k, i = j - row * k;
+    const int32_t x = row / Lmax, l = row - x * Lmax;
+    a.slices[(int64_t)i * a.slice_cells + l * a.slice_row + x] = a.t.N[j];
+  }
+}
+
+__global__ __launch_bounds__(kSliceTile) __attribute__((amdgpu_waves_per_eu(8, 8)))
+void k_score_slices(PassArgs a) {
+  constexpr int TB = kSliceTile, U = 8;
+  const Ctl* ctl = a.ctl;
+  if (ctl->done || ctl->stage) return;
+  if (a.st && ctl->rescore_count <= a.sparse_max) return;
+  if (ctl->defer_all) return;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int W = (a.K0 + 31) >> 5;
+  uint32_t* s_mask = reinterpret_cast<uint32_t*>(smem);               // W * TB
+  int32_t* s_sz = reinterpret_cast<int32_t*>(s_mask + W * TB);        // K0, to a multiple of 4
+  unsigned char* s_tab = reinterpret_cast<unsigned char*>(s_sz + ((a.K0 + 3) & ~3));
+  // until the slices take their place:
+  int32_t* s_off = reinterpret_cast<int32_t*>(s_tab);  // TB + 1: arcs to walk of the vertices before
+  int32_t* s_d = s_off + TB + 4;                       // TB: position of a vertex's arc j less j
+  uint8_t* s_c = reinterpret_cast<uint8_t*>(s_d + TB); // TB: clusters
+  int32_t* s_v = s_off;                                // TB + 1, after the arcs: vertices
+  int32_t* s_perm = s_d;                               // TB, after the arcs: their order
+  __shared__ int32_t s_hist[kSliceItems];
+  __shared__ int32_t s_more;
+  const int t = threadIdx.x;
+  const int32_t k = a.k, K0 = a.K0;
+  const int64_t n = a.n, v0 = (int64_t)blockIdx.x * TB;
+  // the vertices to rescore, in the order of their list unless that is all
+  const int64_t count = a.st ? ctl->rescore_count : n;
+  if (v0 >= count) return;
+  const int nv = (int)min((int64_t)TB, count - v0);
+  const int64_t v = t >= nv ? -1 : (count < n ? a.rlist[v0 + t] : v0 + t);
+  const int32_t cv = t < nv ? a.C[v] : 0;
+  // candidates that need not be found again (see k_score_tile)
+  int32_t cached = t < nv ? -1 : 0;
+  if (a.st && t < nv) {
+    const int32_t stv = a.st[v];
+    if (stv > 0) cached = stv;
+  }
+  s_c[t] = (uint8_t)cv;
+  for (int w = 0; w < W; ++w) s_mask[w * TB + t] = 0;
+  for (int j = 0; j < cached; j += 4) {
+    const int4 q = *reinterpret_cast<const int4*>(a.ccache + v * kCacheCand + j);
+    const int32_t x[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (j + r < cached) s_mask[(x[r] >> 5) * TB + t] |= 1u << (x[r] & 31);
+  }
+  for (int x = t; x < K0; x += TB) s_sz[x] = a.s[x];
+  if (t == 0) s_more = 0;
+  if (t < kSliceItems) s_hist[t] = 0;
+  int32_t beg = 0, deg = 0;
+  if (cached < 0) {
+    beg = (int32_t)a.row_ptr[v];
+    deg = (int32_t)a.row_ptr[v + 1] - beg;
+  }
+  int32_t A;
+  const int32_t off = block_exclusive_scan<TB>(deg, &A);
+  s_off[t] = off;
+  s_d[t] = beg - off;
+  if (t == 0) s_off[TB] = A;
+  __syncthreads();
+  const uint8_t* Cn = static_cast<const uint8_t*>(a.Cn);
+  for (int32_t j0 = t * U; j0 < A; j0 += TB * U) {
+    int lo = 0, hi = TB - 1;  // tail: the last vertex whose arcs start at or before j0
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (s_off[mid] <= j0) lo = mid;
+      else hi = mid - 1;
+    }
+    int tl[U];
+    int32_t hd[U], ch[U];
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      while (j0 + r < A && s_off[lo + 1] <= j0 + r) ++lo;
+      tl[r] = lo;
+      hd[r] = a.col[s_d[lo] + min(j0 + r, A - 1)];
+    }
+#pragma unroll
+    for (int r = 0; r < U; ++r) ch[r] = Cn[hd[r]];
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      const int32_t x = ch[r];
+      if (x == s_c[tl[r]]) continue;
+      uint32_t* w = &s_mask[(x >> 5) * TB + tl[r]];
+      const uint32_t b = 1u << (x & 31);
+      if (!(*w & b)) atomicOr(w, b);
+    }
+  }
+  __syncthreads();
+  int32_t nc = 0;
+  for (int w = 0; w < W; ++w) nc += __popc(s_mask[w * TB + t]);
+  // keep the sets found this pass
+  const bool found = a.dirty && t < nv && cached < 0;
+  if (found && nc <= kCacheCand) {
+    int j = 0;
+    for (int w = 0; w < W; ++w)
+      for (uint32_t b = s_mask[w * TB + t]; b; b &= b - 1)
+        a.ccache[v * kCacheCand + j++] = w * 32 + __ffs(b) - 1;
+  }
+  constexpr int kRound = kSliceItems - 1;
+  const uint64_t more = __ballot(nc > kRound);
+  if ((t & 63) == 0 && more) atomicAdd(&s_more, (int32_t)__popcll(more));
+  __syncthreads();
+  const bool def = nc > kRound && s_more <= TB / 16;
+  if (def) a.heavy[atomicAdd(&a.ctl->heavy_count, 1)] = (int32_t)v;
+  if (found) a.cnum[v] = def ? -1 : nc;
+  if (def && a.slack) a.slack[v] = -1;
+  const int32_t cnt = def ? 0 : nc;
+  if (t < nv && !def && cnt == 0) a.prop[v] = kNone;
+  // The threads take the vertices in order of their candidates, so that a
+  // wave's work is that of its vertices and not of the largest among 64.
+  const int32_t key = min(cnt, kRound);
+  const int32_t rank = atomicAdd(&s_hist[key], 1);
+  s_v[t] = (int32_t)v;
+  __syncthreads();
+  int32_t at = rank;
+  for (int j = 0; j < key; ++j) at += s_hist[j];
+  s_perm[at] = t;
+  __syncthreads();
+  const int p = s_perm[t];
+  const int64_t own = s_v[p];
+  const int32_t cu = s_c[p];
+  int32_t mine = 0;
+  for (int w = 0; w < W; ++w) mine += __popc(s_mask[w * TB + p]);
+  if (t < s_hist[0]) mine = 0;  // no candidate, or deferred
+  // ---- sums ----
+  int64_t bd = 0;
+  int32_t bx = kNone;
+  int cw = 0;               // the mask word the thread is at
+  uint32_t cb = s_mask[p];  // and its bits not taken yet
+  for (int32_t done = 0; __syncthreads_or(done < mine); done += kRound) {
+    const int32_t here = max(0, min(kRound, mine - done));
+    // byte offsets of the items in a row, two a register; the own cluster
+    // first, and in the places of the candidates that are not there
+    uint32_t xp[kSliceItems / 2];
+    int32_t S[kSliceItems];
+#pragma unroll
+    for (int c = 0; c < kSliceItems; ++c) {
+      uint32_t x = (uint32_t)cu;
+      if (c > 0 && c <= here) {
+        while (!cb) cb = s_mask[++cw * TB + p];
+        x = (uint32_t)(cw * 32 + __ffs(cb) - 1);
+        cb &= cb - 1;
+      }
+      S[c] = 0;
+      if (c & 1) xp[c >> 1] |= x << 18;
+      else xp[c >> 1] = x << 2;
+    }
+    const bool any = __any(here > 0);  // of the wave
+    const uint32_t step = (uint32_t)a.slice_cells * 4, rb = (uint32_t)a.slice_row * 4;
+    uint32_t lw = 0, ln = here ? a.Lp[own] : 0;
+    // Straight to LDS, the next slices while these are read: no registers,
+    // and one barrier a group of slices.
+    auto fetch = [&](int32_t i0, uint32_t buf) {
+      const int4* src = reinterpret_cast<const int4*>(a.slices + (int64_t)i0 * a.slice_cells);
+      const int32_t n16 = min(a.slice_load, k - i0) * a.slice_cells / 4;
+      const int w0 = __builtin_amdgcn_readfirstlane(t & ~63), lane = t & 63;
+      for (int32_t j = w0; j < n16; j += TB)
+        if (j + lane < n16)
+          __builtin_amdgcn_global_load_lds(
+              (const __attribute__((address_space(1))) void*)(src + j + lane),
+              (__attribute__((address_space(3))) void*)(s_tab + buf + 16 * j), 16, 0, 0);
+    };
+    const uint32_t half = (uint32_t)a.slice_load * step;
+    uint32_t buf = 0;
+    fetch(0, 0);
+    for (int32_t i0 = 0; i0 < k; i0 += a.slice_load, buf ^= half) {
+      const int32_t np = min(a.slice_load, k - i0);
+      // this wave's slices have arrived; after the barrier everyone's have,
+      // and the other half has been read
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      if (i0 + a.slice_load < k) fetch(i0 + a.slice_load, buf ^ half);
+      if (!any) continue;
+      for (int32_t g = 0; g < np; g += 2) {  // i0 + g is even
+        if (((i0 + g) & 3) == 0) {
+          lw = ln;
+          const int32_t nx = i0 + g + 4;
+          if (nx < k) ln = here ? a.Lp[(int64_t)(nx >> 2) * n + own] : 0;
+        }
+        const uint32_t l0 = lw & 255, l1 = (lw >> 8) & 255;
+        lw >>= 16;
+        if (!here) continue;
+        const bool two = g + 1 < np;
+        const uint32_t r0 = buf + g * step + l0 * rb, r1 = two ? r0 + step + (l1 - l0) * rb : r0;
+        const int32_t m1 = two ? -1 : 0;
+        // the offsets stay packed: unpacked ahead of the loop they would take
+        // the registers of the counts in flight
+#pragma unroll
+        for (int c = 0; c < kSliceItems / 2; ++c) asm("" : "+v"(xp[c]));
+#pragma unroll
+        for (int c = 0; c < kSliceItems; c += 4) {
+          if (c > here) break;
+          int32_t g0[4], g1[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const uint32_t x = (c + u) & 1 ? xp[(c + u) >> 1] >> 16 : xp[(c + u) >> 1] & 0xffff;
+            g0[u] = *reinterpret_cast<const int32_t*>(s_tab + (r0 + x));
+            g1[u] = *reinterpret_cast<const int32_t*>(s_tab + (r1 + x));
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) S[c + u] += g0[u] + (g1[u] & m1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    if (here) {
+      const int32_t szc = s_sz[cu];
+#pragma unroll
+      for (int c = 1; c < kSliceItems; ++c) {
+        if (c > here) break;
+        const int32_t x = (int32_t)(c & 1 ? xp[c >> 1] >> 18 : (xp[c >> 1] & 0xffff) >> 2);
+        int64_t d = 2 * ((int64_t)S[0] - S[c]) + (int64_t)k * ((int64_t)s_sz[x] - szc - 1);
+        if (a.literal) d += k;
+        if (bx == kNone || d < bd) {  // candidates come in increasing id
+          bd = d;
+          bx = x;
+        }
+      }
+    }
+  }
+  const bool move = bx != kNone && bd < 0;
+  if (mine > 0) {
+    a.prop[own] = move ? bx : kNone;
+    if (move) a.dprop[own] = bd;
+    if (a.slack) a.slack[own] = move ? -1 : (int32_t)min(bd, (int64_t)INT32_MAX);
+  }
+  flush_counts<TB>(a, mine, move ? 1 : 0, mine > 0 ? 1 : 0, 0, mine > kTileCandAvg ? 1 : 0);
+}
+
+// ---------------------------------------------------------------------------
 // Dirty marks where the graph is not known to be symmetric: eight lanes a
 // vertex look up whether it or one of its neighbours moved in the previous
 // pass (a bit a vertex: 125 KiB for 1 M vertices), unless more than an eighth
@@ -2051,6 +2322,15 @@ void launch_tile_v(const PassArgs& a, hipStream_t st) {
 }
 
 template <int TK>
+void launch_list(const PassArgs& a, int grid, hipStream_t st) {
+  if (!a.st) return;
+  if (a.ac) k_score_list<0, TK><<<grid, kBlock, 0, st>>>(a);
+  else if (a.cn_bytes == 1) k_score_list<1, TK><<<grid, kBlock, 0, st>>>(a);
+  else if (a.cn_bytes == 2) k_score_list<2, TK><<<grid, kBlock, 0, st>>>(a);
+  else k_score_list<4, TK><<<grid, kBlock, 0, st>>>(a);
+}
+
+template <int TK>
 void launch_tile(const PassArgs& a, int grid, hipStream_t st) {
   // Vertices a tile: up to 2^18 vertices, tiles of 64 (a launch of 256 would
   // leave compute units without a tile: 15 passes over 100 000 vertices of
@@ -2064,14 +2344,38 @@ void launch_tile(const PassArgs& a, int grid, hipStream_t st) {
   if (TK == kHashed || a.tile_small || a.n <= kSmallTileMax) launch_tile_v<TK, 64>(a, st);
   else if (a.K0 <= 256) launch_tile_v<TK, 256>(a, st);
   else launch_tile_v<TK, 128>(a, st);
-  if (!a.st) return;
-  if (a.ac) k_score_list<0, TK><<<grid, kBlock, 0, st>>>(a);
-  else if (a.cn_bytes == 1) k_score_list<1, TK><<<grid, kBlock, 0, st>>>(a);
-  else if (a.cn_bytes == 2) k_score_list<2, TK><<<grid, kBlock, 0, st>>>(a);
-  else k_score_list<4, TK><<<grid, kBlock, 0, st>>>(a);
+  launch_list<TK>(a, grid, st);
+}
+
+// Taken (slice_shape) from 2^18 vertices, a tile for every compute unit,
+// where two buffers of two slices fit beside the candidate masks in half of
+// the LDS (4480 cells for up to 64 clusters: 2 M vertices of 51 clusters and
+// 75 label ids), the ids fit a byte, and the labels were transposed by tiles.
+// Passes over up to 65536 vertices keep the list scorer: 21 us over 10 000,
+// 140 to 177 us over 100 000 to 250 000, which the slices take in 100 us.
+void launch_slices(const PassArgs& a, int grid, hipStream_t st) {
+  k_slices<<<(int)std::min<int64_t>((a.cells + kBlock - 1) / kBlock, 1024), kBlock, 0, st>>>(a);
+  k_score_slices<<<(unsigned)((a.n + kSliceTile - 1) / kSliceTile), kSliceTile, a.slice_lds,
+                   st>>>(a);
+  launch_list<kInterleaved>(a, grid, st);
 }
 
 }  // namespace
+
+bool slice_shape(int64_t n, int32_t k, int64_t K0, int64_t Lmax, PassArgs* a) {
+  if (n < kSliceVertices || K0 > 256 || Lmax > 256) return false;
+  const int64_t row = K0 | 1;  // odd: a label's rows spread over the banks
+  const int64_t cells = (row * Lmax + 3) & ~(int64_t)3;
+  const int64_t words = (K0 + 31) / 32;
+  const int64_t fixed = 4 * ((K0 + 3) & ~(int64_t)3) + 4 * words * kSliceTile;
+  int64_t load = std::min<int64_t>((kSliceLds - kSliceStatic - fixed) / (8 * cells), k + 1) & ~1;
+  if (load < 2) return false;
+  a->slice_row = (int32_t)row;
+  a->slice_cells = (int32_t)cells;
+  a->slice_load = (int32_t)load;
+  a->slice_lds = (int32_t)(fixed + std::max<int64_t>(8 * load * cells, 9 * kSliceTile + 16));
+  return true;
+}
 
 bool score_lanes_ok(int lanes) {
   return lanes == 0 || lanes == 4 || lanes == 8 || lanes == 16 || lanes == 32 || lanes == 64;
@@ -2098,7 +2402,8 @@ void enqueue_pass(const PassArgs& a, int lanes, int grid_score, int grid_apply, 
       // one vertex a thread until that fills the chip
       if (a.st && a.n <= kSmallTileMax) k_status<1><<<grid_apply, kBlock, 0, st>>>(a);
       else if (a.st) k_status<4><<<grid_apply, kBlock, 0, st>>>(a);
-      if (a.t.hashed) launch_tile<kHashed>(a, grid_score, st);
+      if (a.Lp) launch_slices(a, grid_score, st);
+      else if (a.t.hashed) launch_tile<kHashed>(a, grid_score, st);
       else if (a.t.interleaved) launch_tile<kInterleaved>(a, grid_score, st);
       else launch_tile<kBlocked>(a, grid_score, st);
       // deferred vertices: one per wave, as many waves as the chip holds

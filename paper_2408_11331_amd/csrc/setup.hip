@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kBlock) void k_fmap_update(const int32_t* __restric
 __global__ __launch_bounds__(kBlock) void k_label_transpose(
     const int32_t* const* __restrict__ labels, int32_t k, int64_t n,
     const int64_t* __restrict__ loff, const int32_t* __restrict__ fmap, int tv,
-    int32_t* __restrict__ Lvm) {
+    int32_t* __restrict__ Lvm, uint32_t* __restrict__ Lp) {
   extern __shared__ int32_t tile[];  // [k][tv + 1], then one spare word
   constexpr int kWaves = kBlock / 64, kInFlight = 8;
   const int64_t v0 = (int64_t)blockIdx.x * tv;
@@ -258,6 +258,17 @@ __global__ __launch_bounds__(kBlock) void k_label_transpose(
       i -= k;
       ++vv;
     }
+  }
+  if (!Lp) return;
+  // four partitions' ids a word, neighbouring vertices side by side
+  for (int f = threadIdx.x; f < ((k + 3) >> 2) * tv; f += kBlock) {
+    const int q = f / tv, w = f - q * tv;  // tv is a power of two
+    if (w >= rows) continue;
+    uint32_t word = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (4 * q + j < k) word |= (uint32_t)tile[(4 * q + j) * (tv + 1) + w] << (8 * j);
+    Lp[(int64_t)q * n + v0 + w] = word;
   }
 }
 
@@ -991,19 +1002,31 @@ void launch_align(const Tables& blocked, int32_t k, int32_t K0, int32_t maxL,
   k_align_assign<<<g, kBlock, 0, st>>>(blocked.L, K0, poff, home, extra, rank, amap, L2);
 }
 
-void launch_label_transpose(const int32_t* const* dlabels, int32_t k, int64_t n,
-                            const int64_t* loff, const int32_t* fmap, int32_t* Lvm,
-                            hipStream_t st) {
+namespace {
+
+// Vertices of a transposed tile; 0 where k partitions leave no useful one.
+int transpose_rows(int32_t k) {
   int tv = 256;
   while (tv > 16 && (int64_t)(tv + 1) * k * 4 + 4 > 32 * 1024) tv >>= 1;
-  if ((int64_t)(tv + 1) * k * 4 + 4 > 32 * 1024) {
+  return (int64_t)(tv + 1) * k * 4 + 4 > 32 * 1024 ? 0 : tv;
+}
+
+}  // namespace
+
+bool label_words_ok(int32_t k) { return transpose_rows(k) > 0; }
+
+void launch_label_transpose(const int32_t* const* dlabels, int32_t k, int64_t n,
+                            const int64_t* loff, const int32_t* fmap, int32_t* Lvm,
+                            hipStream_t st, uint32_t* Lp) {
+  const int tv = transpose_rows(k);
+  if (!tv) {
     k_label_transpose_direct<<<grid_for(n * k, kBlock, 8192), kBlock, 0, st>>>(dlabels, k, n,
                                                                               loff, fmap, Lvm);
     return;
   }
   size_t lds = ((size_t)(tv + 1) * k + 1) * sizeof(int32_t);
   int64_t nb = (n + tv - 1) / tv;
-  k_label_transpose<<<(unsigned)nb, kBlock, lds, st>>>(dlabels, k, n, loff, fmap, tv, Lvm);
+  k_label_transpose<<<(unsigned)nb, kBlock, lds, st>>>(dlabels, k, n, loff, fmap, tv, Lvm, Lp);
 }
 
 void launch_cluster_mark(const int32_t* init, int64_t n, int32_t* flags, int32_t* err,
