@@ -1470,7 +1470,12 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
       launch_compact_clusters(cmap, a.K0, a.s, S.rawid, a.churn, K1, s2, raw2, churn2, st);
       const int32_t bytes = K1 <= 256 ? 1 : 2;
       void* Cn = ar.get<uint8_t>(n * bytes);
-      launch_remap(cmap, n, a.C, Cn, bytes, a.cnum, a.ccache, kCacheCand, st);
+      // After a pass with many moves every vertex counts as dirty (k_status)
+      // and finds its candidates anew: the cached ones, up to 32 scattered
+      // lookups a vertex, stay as they are (2 M kNN vertices: 1.6 ms).
+      const bool all_dirty = (int64_t)hc.last_moves * 8 > n;
+      launch_remap(cmap, n, a.C, Cn, bytes, all_dirty ? nullptr : a.cnum, a.ccache, kCacheCand,
+                   st);
       a.t = to;
       a.s = s2;
       S.rawid = raw2;
