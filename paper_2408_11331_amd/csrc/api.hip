@@ -490,7 +490,8 @@ void align_to_reference(Arena& ar, Solve* S, int32_t maxL, int64_t sumL, int32_t
   int32_t* tmp = ar.get<int32_t>(scan_tmp_elems(sumL));
   int32_t* amap = ar.get<int32_t>(sumL);
   *L2 = ar.get<int32_t>(k);
-  launch_align(bt, k, L0, maxL, dpoff, sumL, win, home, key, extra, rank, tmp, amap, *L2, st);
+  launch_align(bt, Cref, S->lab.dlabels, S->lab.loff, S->lab.fmap, n, stride, toff[k], k, L0, maxL,
+               dpoff, sumL, win, home, key, extra, rank, tmp, amap, *L2, st);
   launch_fmap_update(S->lab.scan, S->lab.loff, dpoff, amap, k, S->lab.max_span, S->lab.fmap, st);
   L2h->assign(k, 0);
   d2h(L2h->data(), *L2, k, st);
@@ -688,7 +689,8 @@ void build_solve(Arena& ar, const std::vector<const int32_t*>& hptrs, int64_t n,
     int32_t* tmp = ar.get<int32_t>(scan_tmp_elems(sumL));
     int32_t* amap = ar.get<int32_t>(sumL);
     int32_t* L2 = ar.get<int32_t>(k);
-    launch_align(bt, k, K0, maxL, dpoff, sumL, win, home, key, extra, rank, tmp, amap, L2, st);
+    launch_align(bt, S->C, S->lab.dlabels, S->lab.loff, S->lab.fmap, n, stride, total, k, K0, maxL,
+                 dpoff, sumL, win, home, key, extra, rank, tmp, amap, L2, st);
     std::vector<int32_t> L2h(k, 0);
     d2h(L2h.data(), L2, k, st);
     sync(st);

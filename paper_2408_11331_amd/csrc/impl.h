@@ -274,7 +274,9 @@ void launch_label_transpose(const int32_t* const* dlabels, int32_t k, int64_t n,
 bool label_words_ok(int32_t k);
 // Label alignment from a blocked table: amap[poff[i] + l] = new id of dense
 // label l of partition i, L2[i] = new id bound of partition i.
-void launch_align(const Tables& blocked, int32_t k, int32_t K0, int32_t maxL,
+void launch_align(const Tables& blocked, const int32_t* C, const int32_t* const* dlabels,
+                  const int64_t* loff, const int32_t* fmap, int64_t n, int64_t stride,
+                  int64_t cells, int32_t k, int32_t K0, int32_t maxL,
                   const int64_t* poff, int64_t total_labels, uint64_t* win, int32_t* home,
                   uint64_t* key, int32_t* extra, int32_t* rank, int32_t* scan_tmp,
                   int32_t* amap, int32_t* L2, hipStream_t st);

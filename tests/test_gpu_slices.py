@@ -58,3 +58,29 @@ def test_many_vertices(mcc, symmetric, clusters, k, graph):
     assert np.array_equal(out.cpu().numpy(), eo)
     for key in ("passes", "clusters", "moves", "candidate_evals", "objective_init", "objective"):
         assert st[key] == est[key], key
+
+
+@pytest.mark.parametrize("n,groups,k", [(4000, 600, 1), (20000, 1900, 4), (600001, 4000, 3)])
+def test_many_clusters_aligned(mcc, n, groups, k):
+    """Tables far larger than the sample their labels are aligned from (all
+    vertices, or runs of 64): home clusters looked up by the sampled members;
+    labels that no sampled vertex has."""
+    print(f"[gpu-case] align n={n} groups={groups} k={k}", flush=True)
+    import torch
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    rng = np.random.default_rng(n)
+    u = rng.integers(0, n, 5 * n)
+    v = (u + rng.integers(1, 40, 5 * n)) % n
+    rp, col = synth.graph.csr_from_edges(n, u, v)
+    base = np.arange(n) * groups // n
+    labels = np.stack([rng.permutation(groups + 50)[
+        np.where(rng.random(n) < 0.2, rng.integers(0, groups + 50, n), base)]
+        for _ in range(k)]).astype(np.int32)
+    init = np.where(rng.random(n) < 0.2, rng.integers(0, groups, n), base).astype(np.int32)
+    out, st, tr = mcc.consensus(dev(rp), dev(col), dev(labels), dev(init), trace=True,
+                                max_rounds=4)
+    eo, est, et = oracle.consensus(rp, col, labels, init, trace=True, max_rounds=4)
+    assert st["tables"] == 1
+    assert [tuple(t) for t in et][:st["passes"]] == tr
+    assert np.array_equal(out.cpu().numpy(), eo)
+    assert st["objective"] == est["objective"] and st["objective_init"] == est["objective_init"]
