@@ -518,9 +518,9 @@ struct PassArgs {
 
 constexpr int kDeltaLdsMax = 48 << 10;
 
-// The slice scorer: a tile of 1024 vertices for each of 256 compute units at
+// The slice scorer: two tiles of 1024 vertices for each of 256 compute units at
 // the least, and half of a compute unit's LDS, so that two are resident.
-constexpr int64_t kSliceVertices = (int64_t)1 << 18;
+constexpr int64_t kSliceVertices = (int64_t)1 << 19;
 constexpr int kSliceLds = 80 << 10;
 constexpr int32_t kSliceListMax = 1 << 16;
 

@@ -12,9 +12,9 @@
 // sets, no alignment.
 //
 // Measured against one workgroup an instance (the persistent launch): 4096
-// SBM instances of 200 to 20 000 vertices 152 -> 30.5 ms, 24 of them
-// 48.4 -> 1.05 ms; against the general pass kernels, 1000 vertices alone
-// 0.55 -> 0.16 ms, 30 000 with 150 clusters 3.4 -> 2.5 ms.
+// SBM instances of 200 to 20 000 vertices 155 -> 30.5 ms, 24 of them
+// 48.4 -> 0.90 ms; against the general pass kernels, 1000 vertices alone
+// 0.55 -> 0.14 ms, 30 000 with 150 clusters 3.4 -> 2.5 ms.
 #include "multi.h"
 
 namespace mcc {

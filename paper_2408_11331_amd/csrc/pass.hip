@@ -2336,9 +2336,10 @@ void launch_tile(const PassArgs& a, int grid, hipStream_t st) {
   // leave compute units without a tile: 15 passes over 100 000 vertices of
   // an LFR graph 5.9 ms against 9.3, 24 over 30 000 3.5 against 7.9).  Above,
   // tiles of 256 where at most 256 clusters keep the candidates few (2 M kNN
-  // vertices, 51 clusters: 8.2 ms against 8.8 with 128), else 128, whose key
-  // set holds 16 candidates a vertex (1 M LFR vertices, ten candidates each:
-  // 49.6 ms against 51.4 with 256 and 54.7 with 64).
+  // vertices, 51 clusters, scored by tiles: 8.2 ms against 8.8 with 128), else
+  // 128, whose key set holds 16 candidates a vertex (1 M LFR vertices, ten
+  // candidates each, all passes dense: 49.6 ms against 51.4 with 256 and 54.7
+  // with 64).
   // Tiles of 64 also where the candidates are many: with hashed tables, whose
   // starts have one for most arcs, and after a pass with more than twelve.
   if (TK == kHashed || a.tile_small || a.n <= kSmallTileMax) launch_tile_v<TK, 64>(a, st);
@@ -2347,8 +2348,9 @@ void launch_tile(const PassArgs& a, int grid, hipStream_t st) {
   launch_list<TK>(a, grid, st);
 }
 
-// Taken (slice_shape) from 2^18 vertices, a tile for every compute unit,
-// where two buffers of two slices fit beside the candidate masks in half of
+// Taken (slice_shape) from 2^19 vertices, two tiles for every compute unit
+// (320 000 vertices, 42 partitions: 2.72 ms, 2.62 with tiles of 256; 530 000:
+// 2.98 against 3.18), where two buffers of two slices fit beside the candidate masks in half of
 // the LDS (4480 cells for up to 64 clusters: 2 M vertices of 51 clusters and
 // 75 label ids), the ids fit a byte, and the labels were transposed by tiles.
 // Passes over up to 65536 vertices keep the list scorer: 21 us over 10 000,
@@ -2417,7 +2419,12 @@ void enqueue_pass(const PassArgs& a, int lanes, int grid_score, int grid_apply, 
     default: launch_score<64>(a, grid_score, st); break;
   }
   if (score_end) (void)hipEventRecord(score_end, st);
-  k_props<<<grid_apply, kBlock, 0, st>>>(a);
+  // Two workgroups a compute unit: each takes a ticket at the end, one after
+  // another (300 000 vertices: 7 us with 512 workgroups, 12 with 1024).  The
+  // commit needs four where many of 2^20 vertices or more move (106 us against
+  // 137 for 290 000 moves of 2 M), below two (13 against 15 us).
+  const int grid_end = std::min(grid_apply, std::max(1, a.tile_grid / 4));
+  k_props<<<grid_end, kBlock, 0, st>>>(a);
   if (a.t.hashed) {
     k_hash_reset<<<grid_apply, kBlock, 0, st>>>(a);
     k_hash_refill<<<grid_apply, kBlock, 0, st>>>(a);
@@ -2430,7 +2437,7 @@ void enqueue_pass(const PassArgs& a, int lanes, int grid_score, int grid_apply, 
     k_apply_all<<<grid_apply, kBlock, 0, st>>>(a);
   }
   k_fallback<<<grid_apply, kBlock, 0, st>>>(a);
-  k_commit<<<grid_apply, kBlock, 0, st>>>(a);
+  k_commit<<<a.n < (1 << 20) ? grid_end : grid_apply, kBlock, 0, st>>>(a);
 }
 
 }  // namespace mcc

@@ -29,7 +29,7 @@ def test_many_vertices(mcc, symmetric, clusters, k, graph):
     print(f"[gpu-case] slices {clusters} {k} {graph} symmetric={symmetric}", flush=True)
     import torch
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
-    n = (1 << 18) + 777
+    n = (1 << 19) + 777
     rng = np.random.default_rng(clusters)
     m = 8 * n
     u = rng.integers(0, n, m)
