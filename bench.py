@@ -68,7 +68,7 @@ def gen_parallel(fn, items, workers=16):
 
 
 def bench_batch(args):
-    """Config sbm_batch: many SBM instances, one persistent launch, against
+    """Config sbm_batch: many SBM instances in one batched call, against
     solving them one at a time."""
     import numpy as np
     import torch
@@ -132,7 +132,7 @@ def bench_batch(args):
                 assert st[key] == rec[key], (rec["index"], key)
             checked += 1
         log(f"all {checked} batched solves equal the oracle's stored results")
-    # roofline of the persistent launch: each instance's passes times its
+    # roofline of the batched launches: each instance's passes times its
     # per-pass algorithmic bytes, over the launch's time on the stream
     alg = sum(st["passes"] * pass_bytes(i) for st, i in zip(stats, insts))
     launch_s = info["ms_total"] / 1e3
@@ -503,7 +503,8 @@ def main():
             "trace": [list(r) for r in trace],
         },
         "roofline": {
-            "kernel": "k_score_tile (with the deferred-vertex k_score of the same pass)",
+            "kernel": "the scoring kernels of a pass (k_score_slices or k_score_tile, k_score_list, "
+                      "deferred k_score)",
             "bound": "hbm",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
