@@ -836,7 +836,7 @@ int64_t multi_table_bound(int64_t n, int32_t k) {
 // ends, plus a chunk).
 int64_t multi_bound(int64_t vertices, int64_t count, int64_t label_ptrs, int64_t table) {
   const int64_t small = 24 * (vertices + 64 * count) + count * ((int64_t)sizeof(MultiInst) +
-                        (int64_t)sizeof(MultiCtl) + 12 * kMultiClusters + 4 * 256) +
+                        (int64_t)sizeof(MultiCtl) + 4 * kMultiClusters + 4 * 256) +
                         label_ptrs * 40 + (vertices / 256 + count) * 32;
   return 2 * (small + table) + ((int64_t)16 << 20);
 }
@@ -986,12 +986,10 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
   }
   if (live[0].empty() && live[1].empty()) return;
   int32_t* s = ar.get<int32_t>(soff);
-  uint64_t* owner = ar.get<uint64_t>(soff);
   unsigned char* N = ar.get<unsigned char>(toff);
   for (auto& l : live)
     for (int32_t j : l) {
       hi[j].s = s + sat[j];
-      hi[j].owner = owner + sat[j];
       hi[j].N = N + tat[j];
     }
 
@@ -1059,10 +1057,12 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
       launch_multi_build(a, items(w, W[w].at_parts[c]), (int32_t)W[w].parts[c].size(), w != 0, W[w].cells[c],
                          st);
   }
-  int enqueued = 0, chunk = 2;
-  while (enqueued < max_rounds) {
-    const int todo = std::min(chunk, max_rounds - enqueued);
-    for (int q = 0; q < todo; ++q)
+  // slots are enqueued ahead in growing chunks; a pass takes one, or two when
+  // it falls back
+  int64_t enqueued = 0;
+  int chunk = 2;
+  while (enqueued < 2 * (int64_t)max_rounds) {
+    for (int q = 0; q < chunk; ++q)
       for (int w = 0; w < 2; ++w) {
         const Lists& x = W[w];
         if (x.ids.empty()) continue;
@@ -1081,9 +1081,9 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
           launch_multi_apply(a, items(w, x.at_parts[c]), (int32_t)x.parts[c].size(), w != 0,
                              x.cells[c], st);
         launch_multi_commit(a, reinterpret_cast<const int32_t*>(x.dev + x.at_ids),
-                            (int32_t)x.ids.size(), w != 0, st);
+                            (int32_t)x.ids.size(), st);
       }
-    enqueued += todo;
+    enqueued += chunk;
     d2h(hc.data(), a.ctl, count, st);
     sync(st);
     bool any = false;
@@ -1150,7 +1150,6 @@ bool multi_table(Arena& ar, const int32_t* const* labels, int32_t k, int64_t n,
   m.rs = multi_row(n, m.K0);
   m.cs = m.rs * m.Ls;
   m.s = ar.get<int32_t>(m.K0);
-  m.owner = ar.get<uint64_t>(m.K0);
   m.N = ar.get<unsigned char>(multi_table_bytes(n, k, m.K0, m.Ls));
   std::vector<MultiItem> parts;
   for (int32_t i = 0; i < k; ++i) parts.push_back({0, i});

@@ -24,11 +24,12 @@ struct MultiCtl {
   int32_t done;
   int32_t nprop;      // proposals of the current pass
   int32_t passes, converged, fallback_rounds, clusters;
-  int32_t pad;
+  int32_t stage;      // 1: the batch did not lower the objective; the second
+                      // slot of the pass commits its conflict-free subset
   int64_t pass_evals, pass_boundary;
   int64_t evals, boundary, moves;
   int64_t O, O0;      // objective, and the initial one
-  int64_t dN2, dS2;   // changes of the sums of squares by the current batch
+  int64_t dN2, dS2;   // changes of the sums of squares by the current pass
 };
 
 // One instance (device copy).  The table holds one slice per partition,
@@ -48,7 +49,6 @@ struct MultiInst {
   int2* plist;       // proposals of the pass: (vertex, target)
   int64_t* dprop;    // their gains
   int32_t* s;
-  uint64_t* owner;
   void* N;
   int32_t k;
   int32_t K0, Ls;
@@ -107,7 +107,6 @@ void launch_multi_score(const MultiArgs& a, const MultiItem* tiles, int32_t ntil
                         int mode, int tile, int words, size_t slice_bytes, hipStream_t st);
 void launch_multi_apply(const MultiArgs& a, const MultiItem* parts, int32_t nparts, bool wide,
                         int32_t cells_max, hipStream_t st);
-void launch_multi_commit(const MultiArgs& a, const int32_t* ids, int32_t nids, bool wide,
-                         hipStream_t st);
+void launch_multi_commit(const MultiArgs& a, const int32_t* ids, int32_t nids, hipStream_t st);
 
 }  // namespace mcc
