@@ -2371,15 +2371,13 @@ int mcc_compare(const int32_t* a, const int32_t* b, int64_t n, mcc_comparison* r
     int64_t known = -1;
     if (multi_table(ar, &b, 1, n, a, st, &small, &known)) {
       MultiCompare* dc = ar.get<MultiCompare>(1);
-      launch_multi_compare(small.a, dc, st);
+      launch_multi_compare(small.a, small.inst[0].Ls, dc, st);
       MultiCompare c;
       d2h(&c, dc, 1, st);
       sync(st);
-      if (c.labels == small.inst[0].Ls) {  // else labels with gaps: dense ids, below
-        finish(small.ctl[0].O, c.rowmax, c.colmax, c.cells, c.rows, c.cols, small.inst[0].K0,
-               c.labels);
-        return MCC_OK;
-      }
+      finish(small.ctl[0].O, c.rowmax, c.colmax, c.cells, c.rows, c.cols, small.inst[0].K0,
+             c.labels);
+      return MCC_OK;
     }
     // the table of (cluster of a, label of b): dense ids of a as the
     // consensus (a itself where its ids are known to lie in [0, n)), b as the

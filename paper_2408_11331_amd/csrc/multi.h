@@ -78,7 +78,7 @@ struct MultiCompare {
   int32_t labels;            // labels that occur
   int32_t pad;
 };
-void launch_multi_compare(const MultiArgs& a, MultiCompare* out, hipStream_t st);
+void launch_multi_compare(const MultiArgs& a, int32_t Ls, MultiCompare* out, hipStream_t st);
 
 // First-occurrence relabelling of up to kMultiCanon ids in [0, n) by one
 // workgroup; *total: the distinct ids, or -1 if one lies outside [0, n) (then
