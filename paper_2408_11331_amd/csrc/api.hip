@@ -350,7 +350,8 @@ struct Solve {
   uint32_t* Lp = nullptr;    // label ids of four partitions a word (slice scorer)
 };
 
-// Workspace of the candidate sets carried over between passes.
+// Workspace of the candidate sets carried over between passes (eight arrays,
+// each up to 255 bytes longer in the arena).
 int64_t carry_bytes(int64_t n, int64_t K0) {
   return 4 * (5 * n + n * kCacheCand + 2 * K0 + (n + 31) / 32) + 8 * 256;
 }
@@ -506,7 +507,7 @@ void align_to_reference(Arena& ar, Solve* S, int32_t maxL, int64_t sumL, int32_t
 void build_solve(Arena& ar, const std::vector<const int32_t*>& hptrs, int64_t n,
                  const int32_t* init, bool want_rows, const mcc_csr* g_validate, Solve* S,
                  hipStream_t st, uint32_t hash_mode = 0, int64_t known_max = -1,
-                 bool want_words = false) {
+                 bool want_words = false, int64_t trace_bytes = 0) {
   const int32_t k = (int32_t)hptrs.size();
   S->n = n;
   S->k = k;
@@ -729,7 +730,8 @@ void build_solve(Arena& ar, const std::vector<const int32_t*>& hptrs, int64_t n,
     const int64_t words = (int64_t)((k + 3) / 4) * n;
     if (want_words && aligned && label_words_ok(k) && slice_shape(n, k, K0, S->maxL, &shape) &&
         ar.fits(4 * words + 4 * (int64_t)k * shape.slice_cells + carry_bytes(n, K0) + 48 * n +
-                64 * (int64_t)K0 + 16 * (sumL + (int64_t)k * K0) + ((int64_t)1 << 20)))
+                64 * (int64_t)K0 + 16 * (sumL + (int64_t)k * K0) + trace_bytes +
+                ((int64_t)1 << 20)))
       S->Lp = ar.get<uint32_t>(words);
     launch_label_transpose(S->lab.dlabels, k, n, S->lab.loff, S->lab.fmap, S->Lvm, st, S->Lp);
   }
@@ -1285,8 +1287,11 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
                 ((flags & MCC_F_HASH_TABLES) ? kHashForce : 0u) |
                     ((flags & MCC_F_HASH_ROWS) ? kHashRows : 0u) |
                     ((flags & MCC_F_HASH_KEYS) ? kHashKeys : 0u),
-                known, lanes_req == 0 && !(flags & MCC_F_ARC_CACHE));
+                known, lanes_req == 0 && !(flags & MCC_F_ARC_CACHE),
+                (flags & MCC_F_TRACE) ? 32 * (int64_t)max_rounds : 0);
 
+    // What the solve must have is taken before the arrays that it can do
+    // without (Arena::fits), so that those never cost a fixed region the room.
     int64_t* dtrace = nullptr;
     if (flags & MCC_F_TRACE) dtrace = ar.get<int64_t>((int64_t)max_rounds * 4);
     Ctl* ctl = ar.get<Ctl>(1);
@@ -1370,16 +1375,6 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
       a.members = ar.get<int32_t>(n);
       a.mscan_tmp = ar.get<int32_t>(scan_tmp_elems(S.K0));
       a.msum_max = S.t.rows ? kRowsMemberMax : kMemberSumMax;
-      const int32_t width = S.maxL <= 256 ? 1 : (S.maxL <= 65536 ? 2 : 0);
-      const int64_t stride = (width * (int64_t)k + 15) & ~(int64_t)15;
-      if (width && ar.fits(n * stride + 256)) {
-        uint8_t* Lc = ar.get<uint8_t>(n * stride);
-        launch_compact_rows(S.Lvm, n, k, width, (int32_t)stride, Lc, st);
-        a.Lc = Lc;
-        a.lc_stride = (int32_t)stride;
-        a.lc_width = width;
-        a.msum_max = kMemberSumMax;
-      }
     }
     if (S.Lp) {
       (void)slice_shape(n, k, S.K0, S.maxL, &a);
@@ -1392,6 +1387,19 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     } else {
       a.Cn = ar.get<uint8_t>(n * a.cn_bytes);
       launch_narrow(S.C, a.Cn, a.cn_bytes, n, st);
+    }
+    int32_t* const ncl = ar.get<int32_t>(1);
+    if (S.t.hashed) {
+      const int32_t width = S.maxL <= 256 ? 1 : (S.maxL <= 65536 ? 2 : 0);
+      const int64_t stride = (width * (int64_t)k + 15) & ~(int64_t)15;
+      if (width && ar.fits(n * stride + 256)) {
+        uint8_t* Lc = ar.get<uint8_t>(n * stride);
+        launch_compact_rows(S.Lvm, n, k, width, (int32_t)stride, Lc, st);
+        a.Lc = Lc;
+        a.lc_stride = (int32_t)stride;
+        a.lc_width = width;
+        a.msum_max = kMemberSumMax;
+      }
     }
     // 32-bit update keys: cells, cluster sizes, per-cluster move counts
     if (S.total + 2 * (int64_t)S.K0 >= ((int64_t)1 << 31)) throw Status{MCC_ENOTSUP};
@@ -1529,7 +1537,6 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     HIPCK(hipEventRecord(e2, st));
 
     launch_finish(S.C, S.rawid, n, out, st);
-    int32_t* ncl = ar.get<int32_t>(1);
     launch_fill_i32(ncl, 1, 0, st);
     launch_count_nonzero(a.s, S.K0, ncl, st);
     int32_t clusters = 0;
