@@ -1256,10 +1256,15 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
         !(flags & ~(MCC_F_TRACE | MCC_F_LITERAL | MCC_F_SYMMETRIC))) {
       unsigned char* const before = ar.mark();
       int64_t* dtrace = nullptr;
-      if (flags & MCC_F_TRACE) dtrace = ar.get<int64_t>((int64_t)max_rounds * 4);
       mcc_problem one{*g, labels, k, init, out};
       MultiResult r;
-      multi_wave(ar, &one, {0}, max_rounds, (flags & MCC_F_LITERAL) != 0, st, &r, dtrace);
+      try {
+        if (flags & MCC_F_TRACE) dtrace = ar.get<int64_t>((int64_t)max_rounds * 4);
+        multi_wave(ar, &one, {0}, max_rounds, (flags & MCC_F_LITERAL) != 0, st, &r, dtrace);
+      } catch (const Status& s) {
+        if (s.code != MCC_ESCRATCH) throw;
+        r = MultiResult{};  // no room for its arrays: the general kernels may take less
+      }
       if (r.err) throw Status{MCC_EINVAL};
       if (r.solved) {
         HIPCK(hipEventRecord(e3, st));
@@ -1277,7 +1282,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
         return MCC_OK;
       }
       ar.rewind(before);  // the scratch array holds what it held without the attempt
-      if (!noalloc && known_max_pays(r.Ls - 1, k)) known = r.Ls - 1;
+      if (!noalloc && r.known && known_max_pays(r.Ls - 1, k)) known = r.Ls - 1;
     }
 
     const hipEvent_t e1 = events.make(), e2 = events.make();

@@ -139,3 +139,22 @@ def test_label_words(mcc):
                  caps_between(max(1 << 15, top - (130 << 20)), top - (2 << 20), 5 << 20) +
                  caps_between(top - (2 << 20), top + (1 << 19), 64 << 10))
     assert max(held) > SCRATCH - (256 << 10)
+
+
+def test_small_instance(mcc):
+    """An instance of the level-by-level kernels whose table of them, with
+    labels far apart, is larger than all that the general ones take."""
+    print("[gpu-case] scratch limit, few clusters", flush=True)
+    rng = np.random.default_rng(4)
+    n, k = 2000, 256
+    u = rng.integers(0, n, 5 * n)
+    rp, col = synth.graph.csr_from_edges(n, u, (u + rng.integers(1, 30, u.size)) % n)
+    base = np.arange(n) * 2 // n
+    lab = np.where(rng.random((k, n)) < 0.2, rng.integers(0, 2, (k, n)), base) * 6140
+    args = (rp, col, lab.astype(np.int32), (rng.random(n) < 0.5).astype(np.int32))
+    top = largest_trace(mcc, args, 0)
+    # the small table alone takes 256 partitions x 6141 labels x 8 int16 counts
+    assert top > SCRATCH - (24 << 20)
+    held = sweep(mcc, args, 0, caps_between(top - (24 << 20), top, 1 << 20) +
+                 caps_between(top - (1 << 20), top + (1 << 20), 128 << 10))
+    assert max(held) > SCRATCH - (256 << 10)
