@@ -2144,15 +2144,24 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
         for (int32_t i : eligible)
           if (probs[i].g.n > 0 && probs[i].g.n <= kMultiCount) todo.push_back(i);
         while (!todo.empty()) {
+          // A wave that finds its table budget full leaves the ranges it found
+          // of the others, so that a later one takes only what it can hold
+          // (each looking all of them over again, 20 000 instances in waves
+          // of 500 would be looked over 400 000 times).
           std::vector<int32_t> wave, later;
-          int64_t vertices = 0;
+          int64_t vertices = 0, table = 0;
           for (int32_t i : todo) {
             const int64_t v = probs[i].g.n <= kMultiVertices ? probs[i].g.n : 0;
-            if (!wave.empty() && vertices + v > kMultiWaveVertices) {
+            const MultiResult& r = mres[i];
+            const int64_t tb = r.Ls > 0 ? multi_table_bytes(probs[i].g.n, probs[i].k, r.K0,
+                                                            (int32_t)r.Ls) : 0;
+            if (!wave.empty() && (vertices + v > kMultiWaveVertices ||
+                                  table + tb > kMultiWaveTable)) {
               later.push_back(i);
             } else {
               wave.push_back(i);
               vertices += v;
+              table += tb;
             }
           }
           Arena ar(st);

@@ -1,0 +1,82 @@
+"""Batches that the level-by-level kernels take in several waves: every
+instance equals the oracle's solve of it.  The instances are copies of a few,
+whose graphs and labels they share, each with an output of its own."""
+import time
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+KEYS = ("passes", "converged", "fallback_rounds", "clusters", "moves", "candidate_evals",
+        "objective_init", "objective")
+
+
+@pytest.fixture(scope="module")
+def mcc():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2408_11331_amd as m
+    m.lib()
+    oracle.build(force=False)
+    return m
+
+
+def copies(mcc, items, count):
+    """count instances, cycling through the items (equal n), which they share."""
+    import torch
+    m = len(items)
+    pick = np.arange(count) % m
+    one = mcc.pack_batch(items)
+    at = lambda sizes: np.concatenate([[0], np.cumsum(sizes)[:-1]]).astype(np.int64)[pick]
+    n = one.n[pick]
+    init = torch.from_numpy(np.stack([i.init for i in items])).cuda()[torch.from_numpy(pick).cuda()]
+    return mcc.PackedBatch(one.row_ptr, one.col, one.labels, init.reshape(-1).contiguous(),
+                           torch.full((int(n.sum()) + 1,), -3, dtype=torch.int32, device="cuda"),
+                           n, one.nnz[pick], one.k[pick], at(one.n + 1), at(one.nnz),
+                           at(one.n * one.k), np.ones(count, bool))
+
+
+def check(pb, items, info, max_rounds, fits=True):
+    assert info["rc"] == 0 and info["solved_in_batch"] == (pb.count if fits else 0)
+    m = len(items)
+    out = pb.out[:-1].cpu().numpy().reshape(pb.count, -1)
+    for j, i in enumerate(items):
+        eo, est, _ = oracle.consensus(i.row_ptr, i.col, i.labels, i.init, max_rounds=max_rounds)
+        assert (out[j::m] == eo).all()
+        for c in range(j, pb.count, max(m, pb.count // 50 // m * m)):
+            st = pb.stats[c].as_dict()
+            for key in KEYS:
+                assert st[key] == est[key], (c, key)
+
+
+def many_clusters(seed):
+    """100 vertices in clusters of their own, 42 labels, 64 partitions: tables of
+    half a megabyte, more than a workgroup of the persistent launch takes."""
+    inst = synth.random_instance(100, 64, 6.0, 42, seed=seed, init="random")
+    inst.labels[:, 0] = 41
+    inst.init = np.random.default_rng(seed).permutation(100).astype(np.int32)
+    return inst
+
+
+def test_waves_of_full_tables(mcc):
+    """Waves of 512 instances, whose tables fill them: eight times the
+    instances take eight times the time, not up to 64."""
+    import torch
+    print("[gpu-case] batch waves of full tables", flush=True)
+    items = [many_clusters(80 + j) for j in range(3)]
+    t = []
+    for count in (1000, 8000):
+        pb = copies(mcc, items, count)
+        best = float("inf")
+        for _ in range(3):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            info = mcc.consensus_batch_packed(pb, max_rounds=4)
+            best = min(best, time.perf_counter() - t0)
+        check(pb, items, info, 4, fits=False)
+        t.append(best)
+    assert t[1] < 16 * t[0], t
