@@ -812,6 +812,10 @@ struct MultiResult {
 // (about 0.2 ms) are a few percent, small enough to bound the workspace.
 constexpr int64_t kMultiWaveVertices = (int64_t)1 << 23;
 constexpr int64_t kMultiWaveTable = (int64_t)1 << 28;
+// Instances and their partitions: a workgroup of 1024 threads looks each of
+// them over, and a launch holds fewer than 2^32 threads (beyond, the runtime
+// reports no error and not all of the grid runs).
+constexpr int64_t kMultiWaveGroups = (int64_t)1 << 20;
 
 // Counts between two rows of a slice: an odd number of 16-byte units.
 int32_t multi_row(int64_t n, int32_t K0) {
@@ -2149,19 +2153,21 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
           // (each looking all of them over again, 20 000 instances in waves
           // of 500 would be looked over 400 000 times).
           std::vector<int32_t> wave, later;
-          int64_t vertices = 0, table = 0;
+          int64_t vertices = 0, table = 0, groups = 0;
           for (int32_t i : todo) {
             const int64_t v = probs[i].g.n <= kMultiVertices ? probs[i].g.n : 0;
             const MultiResult& r = mres[i];
             const int64_t tb = r.Ls > 0 ? multi_table_bytes(probs[i].g.n, probs[i].k, r.K0,
                                                             (int32_t)r.Ls) : 0;
             if (!wave.empty() && (vertices + v > kMultiWaveVertices ||
-                                  table + tb > kMultiWaveTable)) {
+                                  table + tb > kMultiWaveTable ||
+                                  groups + 1 + probs[i].k > kMultiWaveGroups)) {
               later.push_back(i);
             } else {
               wave.push_back(i);
               vertices += v;
               table += tb;
+              groups += 1 + probs[i].k;
             }
           }
           Arena ar(st);

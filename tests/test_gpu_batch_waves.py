@@ -80,3 +80,13 @@ def test_waves_of_full_tables(mcc):
         check(pb, items, info, 4, fits=False)
         t.append(best)
     assert t[1] < 16 * t[0], t
+
+
+def test_many_instances(mcc):
+    """66 000 instances with 64 partitions each: 4.3 million label ranges, more
+    workgroups of 1024 threads than one launch may hold."""
+    print("[gpu-case] batch of 66000 x 100 vertices, k = 64", flush=True)
+    items = [many_clusters(90 + j) for j in range(3)]
+    pb = copies(mcc, items, 66_000)
+    check(pb, items, mcc.consensus_batch_packed(pb, max_rounds=3), 3, fits=False)
+    assert all(pb.stats[j].lanes_used == 0 for j in range(0, pb.count, 1000))
