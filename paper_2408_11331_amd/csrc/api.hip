@@ -151,6 +151,11 @@ class Arena {
     memcpy(staging_.back().data(), src.data(), src.size() * sizeof(T));
     return reinterpret_cast<T*>(staging_.back().data());
   }
+  // The same, taking the buffer over.
+  unsigned char* host(std::vector<unsigned char>&& src) {
+    staging_.push_back(std::move(src));
+    return staging_.back().data();
+  }
   // Device buffer of `count` elements, 256-byte aligned.  Requests are
   // carved from chunks of kChunk bytes (a larger request gets a chunk of its
   // own), taken from the stream's cached chunks when one is large enough.
@@ -848,28 +853,36 @@ int64_t multi_bound(int64_t vertices, int64_t count, int64_t label_ptrs, int64_t
 }
 
 // Host arrays gathered for one upload: a copy from pageable memory costs
-// several microseconds of host time however small it is.
+// several microseconds of host time however small it is.  Long lists are
+// written where they are sent from (room): a batch of 15 000 instances with 20
+// partitions has 12 MB of them, and copying them twice on the way took 4 ms.
 class Upload {
  public:
+  // Room for `count` elements, at the returned offset; at<T>() addresses it
+  // until more is asked for.
+  template <class T>
+  size_t room(size_t count) {
+    const size_t at = (data_.size() + 15) & ~(size_t)15;
+    data_.resize(at + count * sizeof(T));
+    return at;
+  }
+  template <class T>
+  T* at(size_t offset) { return reinterpret_cast<T*>(data_.data() + offset); }
   template <class T>
   size_t put(const std::vector<T>& v) {
-    const size_t at = (data_.size() + 15) & ~(size_t)15;
-    data_.resize(at + v.size() * sizeof(T));
+    const size_t at = room<T>(v.size());
     if (!v.empty()) memcpy(data_.data() + at, v.data(), v.size() * sizeof(T));
     return at;
   }
-  // Overwrites an array put before.
-  template <class T>
-  void set(size_t at, const std::vector<T>& v) {
-    if (!v.empty()) memcpy(data_.data() + at, v.data(), v.size() * sizeof(T));
-  }
+  void reserve(size_t bytes) { data_.reserve(bytes); }
   int64_t size() const { return (int64_t)data_.size(); }
-  // Copies the gathered arrays to d, in stream order.
-  void send_to(Arena& ar, unsigned char* d, hipStream_t st) const {
-    h2d(d, ar.host(data_), (int64_t)data_.size(), st);
+  // Copies the gathered arrays to d, in stream order; they are gone after it.
+  void send_to(Arena& ar, unsigned char* d, hipStream_t st) {
+    const int64_t bytes = size();
+    h2d(d, ar.host(std::move(data_)), bytes, st);
   }
   // The same into room of their own.
-  unsigned char* send(Arena& ar, hipStream_t st) const {
+  unsigned char* send(Arena& ar, hipStream_t st) {
     unsigned char* d = ar.get<unsigned char>(size());
     send_to(ar, d, st);
     return d;
@@ -893,16 +906,11 @@ void multi_ranges(Arena& ar, const mcc_problem* probs, const std::vector<int32_t
   const int32_t count = (int32_t)ids.size();
   S->inst.resize(count);
   S->ctl.resize(count);
-  std::vector<const int32_t*> ptrs;
-  std::vector<MultiItem> labels;
   std::vector<int64_t> voff(count + 1, 0);
-  int64_t n_max = 1;
+  int64_t n_max = 1, pairs = 0;
   for (int32_t j = 0; j < count; ++j) {
     const mcc_problem& p = probs[ids[j]];
-    for (int32_t i = 0; i < p.k; ++i) {
-      ptrs.push_back(p.labels[i]);
-      labels.push_back({j, i});
-    }
+    pairs += p.k;
     n_max = std::max<int64_t>(n_max, p.g.n);
     // state only where the kernels may take the instance
     voff[j + 1] = voff[j] + (p.g.n <= kMultiVertices ? (p.g.n + 63) & ~(int64_t)63 : 0);
@@ -913,10 +921,14 @@ void multi_ranges(Arena& ar, const mcc_problem* probs, const std::vector<int32_t
   int2* plist = passes ? ar.get<int2>(voff[count]) : nullptr;
   int64_t* dprop = passes ? ar.get<int64_t>(voff[count]) : nullptr;
   Upload up;
-  const size_t at_ptrs = up.put(ptrs), at_labels = up.put(labels), at_ctl = up.put(S->ctl),
-               at_inst = up.put(S->inst);
+  up.reserve((size_t)pairs * (sizeof(const int32_t*) + sizeof(MultiItem)) +
+             (size_t)count * (sizeof(MultiCtl) + sizeof(MultiInst)) + 64);
+  const size_t at_ptrs = up.room<const int32_t*>(pairs), at_labels = up.room<MultiItem>(pairs),
+               at_ctl = up.put(S->ctl), at_inst = up.room<MultiInst>(count);
   unsigned char* d = ar.get<unsigned char>(up.size());
   const int32_t* const* dptrs = reinterpret_cast<const int32_t* const*>(d + at_ptrs);
+  const int32_t** ptrs = up.at<const int32_t*>(at_ptrs);
+  MultiItem* labels = up.at<MultiItem>(at_labels);
   int64_t lo = 0;
   for (int32_t j = 0; j < count; ++j) {
     const mcc_problem& p = probs[ids[j]];
@@ -925,7 +937,10 @@ void multi_ranges(Arena& ar, const mcc_problem* probs, const std::vector<int32_t
     m.row_ptr = p.g.row_ptr;
     m.col = p.g.col;
     m.labels = dptrs + lo;
-    lo += p.k;
+    for (int32_t i = 0; i < p.k; ++i, ++lo) {
+      ptrs[lo] = p.labels[i];
+      labels[lo] = {j, i};
+    }
     m.init = p.init;
     m.out = p.out;
     m.k = p.k;
@@ -936,7 +951,7 @@ void multi_ranges(Arena& ar, const mcc_problem* probs, const std::vector<int32_t
       m.dprop = dprop + voff[j];
     }
   }
-  up.set(at_inst, S->inst);
+  if (count) memcpy(up.at<MultiInst>(at_inst), S->inst.data(), count * sizeof(MultiInst));
   up.send_to(ar, d, st);
   S->a.inst = reinterpret_cast<const MultiInst*>(d + at_inst);
   S->a.ctl = reinterpret_cast<MultiCtl*>(d + at_ctl);
@@ -944,7 +959,7 @@ void multi_ranges(Arena& ar, const mcc_problem* probs, const std::vector<int32_t
   S->a.max_rounds = max_rounds;
   S->a.literal = literal ? 1 : 0;
   launch_multi_ranges(S->a, reinterpret_cast<const MultiItem*>(d + at_labels),
-                      (int32_t)labels.size(), n_max, st);
+                      (int32_t)pairs, n_max, st);
   d2h(S->ctl.data(), S->a.ctl, count, st);
   sync(st);
 }
@@ -1004,7 +1019,7 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
   // instances themselves.
   constexpr int32_t kSmallCells = 4096;
   struct Lists {
-    std::vector<MultiItem> parts[2], tiles[kMultiModes];
+    int32_t parts[2] = {}, tiles[kMultiModes] = {};  // lengths
     std::vector<int32_t> ids;
     int32_t cells[2] = {1, 1};
     int words[kMultiModes] = {};
@@ -1021,38 +1036,44 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
   // tiles of 256; below, 256 puts work on more units (LFR 30 k, 30 tiles of
   // 1024: 2.4 ms in tiles of 256).
   const int tile = total_n >= (int64_t)1024 * device_sms() / 2 ? 1024 : 256;
-  auto fill = [&](int w) {
+  auto cells_class = [&](const MultiInst& m) { return m.K0 * m.Ls <= kSmallCells ? 0 : 1; };
+  auto tile_count = [&](const MultiInst& m) { return (int32_t)((m.n + tile - 1) / tile); };
+  // The lists of class w: their lengths and limits, and the lists themselves
+  // where they are sent from.
+  auto put = [&](int w, Upload& up) {
     Lists x;
     const size_t tsz = w ? 4 : 2;
     for (int32_t j : live[w]) {
       const MultiInst& m = hi[j];
-      const int32_t cells = m.K0 * m.Ls, cls = cells <= kSmallCells ? 0 : 1;
-      for (int32_t i = 0; i < m.k; ++i) x.parts[cls].push_back({j, i});
-      x.cells[cls] = std::max(x.cells[cls], cells);
-      const int q = multi_score_mode(m.K0, m.cs, w != 0, tile);
-      for (int32_t v = 0; v < (int32_t)((m.n + tile - 1) / tile); ++v)
-        x.tiles[q].push_back({j, v});
-      x.ids.push_back(j);
+      const int cls = cells_class(m), q = multi_score_mode(m.K0, m.cs, w != 0, tile);
+      x.parts[cls] += m.k;
+      x.cells[cls] = std::max(x.cells[cls], m.K0 * m.Ls);
+      x.tiles[q] += tile_count(m);
       x.words[q] = std::max(x.words[q], (m.K0 + 31) / 32);
       x.slice[q] = std::max(x.slice[q], (size_t)m.cs * tsz);
       x.table[q] = std::max(x.table[q], (size_t)m.cs * tsz * (size_t)m.k);
     }
-    W[w] = x;
-  };
-  auto put = [&](int w, Upload& up) {
-    Lists& x = W[w];
-    for (int c = 0; c < 2; ++c) x.at_parts[c] = up.put(x.parts[c]);
-    for (int q = 0; q < kMultiModes; ++q) x.at_tiles[q] = up.put(x.tiles[q]);
+    x.ids = live[w];
+    for (int c = 0; c < 2; ++c) x.at_parts[c] = up.room<MultiItem>(x.parts[c]);
+    for (int q = 0; q < kMultiModes; ++q) x.at_tiles[q] = up.room<MultiItem>(x.tiles[q]);
     x.at_ids = up.put(x.ids);
+    MultiItem *parts[2], *tiles[kMultiModes];
+    for (int c = 0; c < 2; ++c) parts[c] = up.at<MultiItem>(x.at_parts[c]);
+    for (int q = 0; q < kMultiModes; ++q) tiles[q] = up.at<MultiItem>(x.at_tiles[q]);
+    for (int32_t j : live[w]) {
+      const MultiInst& m = hi[j];
+      MultiItem*& p = parts[cells_class(m)];
+      MultiItem*& t = tiles[multi_score_mode(m.K0, m.cs, w != 0, tile)];
+      for (int32_t i = 0; i < m.k; ++i) *p++ = {j, i};
+      for (int32_t v = 0; v < tile_count(m); ++v) *t++ = {j, v};
+    }
+    W[w] = std::move(x);
   };
   {  // the instances and the lists in one upload
     Upload up;
     up.put(hi);
-    for (int w = 0; w < 2; ++w) {
-      if (live[w].empty()) continue;
-      fill(w);
-      put(w, up);
-    }
+    for (int w = 0; w < 2; ++w)
+      if (!live[w].empty()) put(w, up);
     const unsigned char* d = up.send(ar, st);
     a.inst = reinterpret_cast<const MultiInst*>(d);
     for (int w = 0; w < 2; ++w) W[w].dev = d;
@@ -1060,7 +1081,7 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
   auto items = [&](int w, size_t at) { return reinterpret_cast<const MultiItem*>(W[w].dev + at); };
   for (int w = 0; w < 2; ++w) {
     for (int c = 0; c < 2; ++c)
-      launch_multi_build(a, items(w, W[w].at_parts[c]), (int32_t)W[w].parts[c].size(), w != 0, W[w].cells[c],
+      launch_multi_build(a, items(w, W[w].at_parts[c]), W[w].parts[c], w != 0, W[w].cells[c],
                          st);
   }
   // slots are enqueued ahead in growing chunks; a pass takes one, or two when
@@ -1080,11 +1101,11 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
           const size_t room = tile == 256 ? (16 << 10) : (64 << 10);
           const size_t buf =
               md == kMultiDirect ? 0 : std::max(x.slice[md], std::min(x.table[md], room));
-          launch_multi_score(a, items(w, x.at_tiles[md]), (int32_t)x.tiles[md].size(), w != 0, md, tile,
+          launch_multi_score(a, items(w, x.at_tiles[md]), x.tiles[md], w != 0, md, tile,
                              x.words[md], buf, st);
         }
         for (int c = 0; c < 2; ++c)
-          launch_multi_apply(a, items(w, x.at_parts[c]), (int32_t)x.parts[c].size(), w != 0,
+          launch_multi_apply(a, items(w, x.at_parts[c]), x.parts[c], w != 0,
                              x.cells[c], st);
         launch_multi_commit(a, reinterpret_cast<const int32_t*>(x.dev + x.at_ids),
                             (int32_t)x.ids.size(), st);
@@ -1104,13 +1125,10 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
             res[ids[j]].solved = true;
             res[ids[j]].ctl = hc[j];
           }
-        live[w] = rest;
-        fill(w);
-        if (!rest.empty()) {
-          Upload up;
-          put(w, up);
-          W[w].dev = up.send(ar, st);
-        }
+        live[w] = std::move(rest);
+        Upload up;
+        put(w, up);
+        if (!live[w].empty()) W[w].dev = up.send(ar, st);
       }
     }
     if (!any) break;
