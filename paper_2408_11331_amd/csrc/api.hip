@@ -2047,6 +2047,40 @@ int64_t heuristic_cells_cap(const mcc_problem* probs, const std::vector<int32_t>
   return std::min<int64_t>(std::max<int64_t>(n_max * k_max, (int64_t)1 << 18), kCellsCapMax);
 }
 
+// The instances of a batch that go to the persistent launch although the
+// level-by-level kernels may take them (*tiny); the others that those look
+// over go to *levels.  A workgroup of the persistent launch takes 18 ns for an
+// arc or label (two passes) and 0.2 us an instance with 512 of them at work;
+// the kernels start about four workgroups a partition, 10 ns each, whatever it
+// holds.  So an instance is tiny up to 256 vertices and arcs a partition, and
+// tiny ones go there once they fill a quarter of the workgroups.  A batch of
+// no more instances than workgroups, each of at most 2000 arcs and labels, goes
+// there whole: it is done before the kernels' host has waited three times.
+// Measured (ms, kernels and persistent launch; vertices x partitions, 12 to 16
+// arcs a vertex):
+//   instances   100 x 3      100 x 8      30 x 64      100 x 64     200 x 64     400 x 64
+//   60          0.22  0.17   0.15  0.16   0.20  0.20   0.21  0.25   0.21  0.30   0.22  0.46
+//   300         0.27  0.22   0.20  0.20   0.39  0.27   0.41  0.34   0.41  0.41   0.43  0.65
+//   3000        0.80  1.01   0.78  0.90   2.57  1.55   2.82  2.01   2.85  2.47   3.04  4.07
+//   15 000      3.46  4.84   3.59  4.35   14.2  7.87   14.5  10.1   14.8  12.2   15.3  20.2
+void tiny_instances(const mcc_problem* probs, const std::vector<int32_t>& eligible, int wgpc,
+                    std::vector<int32_t>* tiny, std::vector<int32_t>* levels) {
+  const int64_t groups = (int64_t)device_sms() * wgpc;
+  auto work = [&](const mcc_problem& p) { return p.g.n * p.k + p.g.nnz; };
+  int64_t count = 0, most = 0;
+  for (int32_t i : eligible) {
+    const mcc_problem& p = probs[i];
+    count += p.g.n > 0 && work(p) <= 256 * p.k;
+    most = std::max(most, work(p));
+  }
+  const bool all = most <= 2000 && (int64_t)eligible.size() <= groups;
+  for (int32_t i : eligible) {
+    const mcc_problem& p = probs[i];
+    if (p.g.n <= 0 || p.g.n > kMultiCount) continue;
+    (all || (4 * count >= groups && work(p) <= 256 * p.k) ? tiny : levels)->push_back(i);
+  }
+}
+
 // Workspace that mcc_batch_workspace_bytes grants a call beyond the
 // persistent launch's own, for instances solved one after another.
 constexpr int64_t kAloneBytes = (int64_t)192 << 20;
@@ -2158,13 +2192,51 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
       run.wgpc = wgpc;
       run.max_rounds = max_rounds;
       run.literal = (flags & MCC_F_LITERAL) ? 1 : 0;
+      // One persistent launch over `ids`; the instances beyond its slots are
+      // appended to *large.
+      auto persistent = [&](const std::vector<int32_t>& ids, std::vector<int32_t>* large) {
+        run.ids = ids;
+        int64_t ws = 0;
+        run_batch(run, count, st, &hres, &ws);
+        held(ws);
+        for (int32_t i : ids) {
+          if (hres[i].status == kBatchTooBig) {
+            large->push_back(i);
+            continue;
+          }
+          if (hres[i].status == kBatchInvalid) status[i] = MCC_EINVAL;
+          else if (opts) opts->solved_in_batch += 1;
+          if (hres[i].status != 0 || !stats) continue;
+          mcc_stats& o = stats[i];
+          o.passes = hres[i].passes;
+          o.converged = hres[i].converged;
+          o.fallback_rounds = hres[i].fallback_rounds;
+          o.clusters = hres[i].clusters;
+          o.moves = hres[i].moves;
+          o.candidate_evals = hres[i].candidate_evals;
+          o.objective_init = hres[i].objective_init;
+          o.objective = hres[i].objective;
+          o.lanes_used = run.lanes[i];
+        }
+      };
       // Level by level where the launch shape is left to the library: the
       // instances those kernels take are solved, the others' cluster counts
-      // and label ranges known (up to kMultiCount vertices).
+      // and label ranges known (up to kMultiCount vertices).  Many tiny
+      // instances go to the persistent launch first, and only those that it
+      // has no room for on to these kernels.
+      std::vector<bool> done(count, false);
       if (lanes == 0 && !(opts && opts->wg_per_cu > 0)) {
-        std::vector<int32_t> todo;
-        for (int32_t i : eligible)
-          if (probs[i].g.n > 0 && probs[i].g.n <= kMultiCount) todo.push_back(i);
+        std::vector<int32_t> todo, tiny;
+        tiny_instances(probs, eligible, wgpc, &tiny, &todo);
+        if (!tiny.empty()) {
+          for (int32_t i : tiny) done[i] = true;
+          std::vector<int32_t> large;
+          persistent(tiny, &large);
+          for (int32_t i : large) {
+            done[i] = false;
+            todo.push_back(i);
+          }
+        }
         while (!todo.empty()) {
           // A wave that finds its table budget full leaves the ranges it found
           // of the others, so that a later one takes only what it can hold
@@ -2206,6 +2278,7 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
       std::vector<int32_t> rest, alone;
       for (int32_t i : eligible) {
         const MultiResult& r = mres[i];
+        if (done[i]) continue;
         if (r.known && r.err) {
           status[i] = MCC_EINVAL;
         } else if (r.solved) {
@@ -2223,30 +2296,7 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
         fallback.push_back(i);
         if (opts) opts->solved_in_batch += 1;
       }
-      if (!rest.empty()) {
-        run.ids = rest;
-        int64_t ws = 0;
-        run_batch(run, count, st, &hres, &ws);
-        held(ws);
-      }
-      for (int32_t i : rest) {
-        if (hres[i].status == kBatchTooBig) fallback.push_back(i);
-        else if (hres[i].status == kBatchInvalid) status[i] = MCC_EINVAL;
-        else if (opts) opts->solved_in_batch += 1;
-      }
-      for (int32_t i : rest) {
-        if (hres[i].status != 0 || !stats) continue;
-        mcc_stats& o = stats[i];
-        o.passes = hres[i].passes;
-        o.converged = hres[i].converged;
-        o.fallback_rounds = hres[i].fallback_rounds;
-        o.clusters = hres[i].clusters;
-        o.moves = hres[i].moves;
-        o.candidate_evals = hres[i].candidate_evals;
-        o.objective_init = hres[i].objective_init;
-        o.objective = hres[i].objective;
-        o.lanes_used = run.lanes[i];
-      }
+      if (!rest.empty()) persistent(rest, &fallback);
     }
     for (int32_t i : fallback) {
       const mcc_problem& p = probs[i];

@@ -90,3 +90,60 @@ def test_many_instances(mcc):
     pb = copies(mcc, items, 66_000)
     check(pb, items, mcc.consensus_batch_packed(pb, max_rounds=3), 3, fits=False)
     assert all(pb.stats[j].lanes_used == 0 for j in range(0, pb.count, 1000))
+
+
+@pytest.mark.parametrize("count,n,k", [(15000, 30, 64), (3000, 100, 64), (15000, 100, 8),
+                                       (200, 30, 3)])
+def test_tiny_instances_time(mcc, count, n, k):
+    """Many tiny instances take no longer than 1.5 times the persistent launch
+    that lanes=4 asks for."""
+    import torch
+    print(f"[gpu-case] batch of {count} tiny instances {n} x {k}, time", flush=True)
+    items = [synth.random_instance(n, k, 8.0, 2, seed=60 + j) for j in range(3)]
+    pb = copies(mcc, items, count)
+
+    def best(**kw):
+        t = []
+        for _ in range(8):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            info = mcc.consensus_batch_packed(pb, **kw)
+            t.append(time.perf_counter() - t0)
+        check(pb, items, info, 0)
+        return min(t)
+
+    mine, persistent = best(), best(lanes=4)
+    assert mine < 1.5 * persistent, (mine, persistent)
+
+
+@pytest.mark.parametrize("count", [127, 128, 400])
+def test_tiny_instances_mixed(mcc, count):
+    """Tiny instances on both sides of the number that goes to the persistent
+    launch, among them tables too large for it, label values too large for it,
+    singleton starts and a negative label, beside larger ones."""
+    print(f"[gpu-case] batch of {count} tiny instances, mixed", flush=True)
+    import torch
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    items = [synth.random_instance(20 + j % 90, 5 + j % 60, 4.0, 1 + j % 7, seed=j,
+                                   init=["p0", "singleton", "random"][j % 3])
+             for j in range(count)]
+    for j in (3, 40, 99):
+        items[j] = many_clusters(j)
+    items[5].labels[2] *= 70_001
+    items[6].labels[1, 4] = -2
+    items += [synth.random_instance(3000, 9, 6.0, 8, seed=7 + j) for j in range(3)]
+    single = lambda j: j < count and j % 3 == 1 and j not in (40,)
+    probs = [{"row_ptr": dev(i.row_ptr), "col": dev(i.col), "labels": dev(i.labels),
+              "init": None if single(j) else dev(i.init)} for j, i in enumerate(items)]
+    outs, stats, codes, info = mcc.consensus_batch(probs, max_rounds=20)
+    assert codes == [mcc.MCC_EINVAL if j == 6 else 0 for j in range(len(items))]
+    for j, i in enumerate(items):
+        if j == 6:
+            continue
+        eo, est, _ = oracle.consensus(i.row_ptr, i.col, i.labels, None if single(j) else i.init,
+                                      max_rounds=20)
+        assert np.array_equal(outs[j].cpu().numpy(), eo), j
+        for key in KEYS:
+            assert stats[j][key] == est[key], (j, key)
+    # as many as its workgroups hold, whichever kernels solved them
+    assert info["solved_in_batch"] == len(items) - 5
