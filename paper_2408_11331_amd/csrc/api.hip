@@ -1946,6 +1946,7 @@ struct BatchRun {
   std::vector<int32_t*> outs;    // per problem: output buffer override, or null
   int wgpc = 2;
   int64_t cells_cap = 0;
+  int64_t n_max = 0;             // largest instance of the batch, where ids are a part of it
   int32_t max_rounds = 1000;
   int32_t literal = 0;
 };
@@ -1993,7 +1994,7 @@ float run_batch(const BatchRun& run, int32_t count, hipStream_t st, std::vector<
   BatchWs& w = ba.ws;
   w.n_max = n_max;
   w.k_max = k_max;
-  w.flag_cap = 2 * n_max + 1024;
+  w.flag_cap = 2 * std::max(n_max, run.n_max) + 1024;
   w.cells_cap = run.cells_cap;
   const int64_t slots = std::max<int64_t>(
       1, std::min<int64_t>((int64_t)run.ids.size(), (int64_t)device_sms() * run.wgpc));
@@ -2190,6 +2191,7 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
       run.cells_cap = covered ? std::min(kCellsCapMax, std::max(kCellsCapMin, pow2_ceil(cells)))
                               : heuristic_cells_cap(probs, eligible);
       run.wgpc = wgpc;
+      run.n_max = n_max;
       run.max_rounds = max_rounds;
       run.literal = (flags & MCC_F_LITERAL) ? 1 : 0;
       // One persistent launch over `ids`; the instances beyond its slots are
