@@ -2172,6 +2172,7 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
     HIPCK(hipEventRecord(e0, st));
     std::vector<BatchRes> hres(count);
     std::vector<MultiResult> mres(count);
+    std::vector<bool> counted(count, false);  // solved alone, and counted as batched
     auto held = [&](int64_t bytes) {
       if (opts) opts->workspace_bytes = std::max(opts->workspace_bytes, bytes);
     };
@@ -2226,7 +2227,7 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
       // and label ranges known (up to kMultiCount vertices).  Many tiny
       // instances go to the persistent launch first, and only those that it
       // has no room for on to these kernels.
-      std::vector<bool> done(count, false);
+      std::vector<bool> done(count, false);  // by the persistent launch
       if (lanes == 0 && !(opts && opts->wg_per_cu > 0)) {
         std::vector<int32_t> todo, tiny;
         tiny_instances(probs, eligible, wgpc, &tiny, &todo);
@@ -2296,7 +2297,7 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
         alone.swap(rest);
       for (int32_t i : alone) {
         fallback.push_back(i);
-        if (opts) opts->solved_in_batch += 1;
+        counted[i] = true;
       }
       if (!rest.empty()) persistent(rest, &fallback);
     }
@@ -2310,6 +2311,7 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
       const int rc = mcc_consensus(&p.g, p.labels, p.k, p.init, p.out, &one);
       status[i] = rc;
       if (stats && rc == MCC_OK) stats[i] = one;
+      if (opts && rc == MCC_OK && counted[i]) opts->solved_in_batch += 1;
       held(one.workspace_bytes);
     }
     HIPCK(hipEventRecord(e1, st));
