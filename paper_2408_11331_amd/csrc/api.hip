@@ -104,10 +104,10 @@ class Arena {
   explicit Arena(hipStream_t st) : st_(st) { (void)hipGetDevice(&dev_); }
   // An arena over a fixed device region of `cap` bytes: get() carves from
   // it and throws Status{MCC_ESCRATCH} when it is full; nothing is
-  // allocated, freed or cached.
+  // allocated, freed or cached.  Without a region, an arena that asks for
+  // chunks of `cap` bytes in all (0: any number) and throws the same beyond.
   Arena(hipStream_t st, unsigned char* fixed, size_t cap)
-      : st_(st), fixed_(fixed != nullptr), next_(fixed), left_(fixed ? cap : 0),
-        fixed_cap_(fixed ? cap : 0) {
+      : st_(st), fixed_(fixed != nullptr), next_(fixed), left_(fixed ? cap : 0), cap_(cap) {
     (void)hipGetDevice(&dev_);
   }
   ~Arena() {
@@ -129,7 +129,7 @@ class Arena {
   // Device bytes the arena holds: the chunks taken, or the fixed region's
   // carved part.
   size_t bytes_used() const {
-    if (fixed_) return fixed_cap_ - left_;
+    if (fixed_) return cap_ - left_;
     size_t b = 0;
     for (const Chunk& k : used_) b += k.size;
     return b;
@@ -142,8 +142,12 @@ class Arena {
     left_ += (size_t)(next_ - to);
     next_ = to;
   }
-  // Whether `bytes` more are to be had: always, but for a fixed region.
-  bool fits(int64_t bytes) const { return !fixed_ || bytes <= (int64_t)left_; }
+  // Whether `bytes` more are to be had: always, but for a fixed region or a
+  // cap (there from the current chunk, or from what may still be asked for).
+  bool fits(int64_t bytes) const {
+    return (!fixed_ && !cap_) || bytes <= (int64_t)left_ ||
+           (!fixed_ && bytes <= (int64_t)(cap_ - asked_));
+  }
   // Host buffer that lives as long as the arena (source of async copies).
   template <class T>
   T* host(const std::vector<T>& src) {
@@ -169,8 +173,10 @@ class Arena {
       left_ -= bytes;
       return static_cast<T*>(r);
     }
-    if (fixed_) throw Status{MCC_ESCRATCH};
-    const Chunk k = chunk(std::max(bytes, kChunk));
+    if (fixed_ || (cap_ && bytes > cap_ - asked_)) throw Status{MCC_ESCRATCH};
+    const size_t size = std::max(bytes, cap_ ? std::min(kChunk, cap_ - asked_) : kChunk);
+    asked_ += size;
+    const Chunk k = chunk(size);
     if (bytes >= kChunk) return static_cast<T*>(k.p);  // own chunk; keep the current one
     next_ = static_cast<unsigned char*>(k.p) + bytes;
     left_ = k.size - bytes;
@@ -226,7 +232,8 @@ class Arena {
   std::vector<Chunk> used_;
   unsigned char* next_ = nullptr;
   size_t left_ = 0;
-  size_t fixed_cap_ = 0;
+  size_t cap_ = 0;    // bytes of the fixed region, or most to ask for (0: no limit)
+  size_t asked_ = 0;  // chunk bytes asked for
   std::vector<std::vector<unsigned char>> staging_;
 };
 
@@ -844,12 +851,15 @@ int64_t multi_table_bound(int64_t n, int32_t k) {
 
 // Upper bound of the workspace of one wave over instances like these (the
 // arrays multi_wave takes, allocation by allocation, doubled for the chunk
-// ends, plus a chunk).
+// ends, plus a chunk): all but the tables, and the whole.
+int64_t multi_state(int64_t vertices, int64_t count, int64_t label_ptrs) {
+  return 24 * (vertices + 64 * count) +
+         count * (2 * (int64_t)sizeof(MultiInst) + (int64_t)sizeof(MultiCtl) +
+                  4 * kMultiClusters + 4 * 256) +
+         label_ptrs * 40 + (vertices / 256 + count) * 32;
+}
 int64_t multi_bound(int64_t vertices, int64_t count, int64_t label_ptrs, int64_t table) {
-  const int64_t small = 24 * (vertices + 64 * count) + count * ((int64_t)sizeof(MultiInst) +
-                        (int64_t)sizeof(MultiCtl) + 4 * kMultiClusters + 4 * 256) +
-                        label_ptrs * 40 + (vertices / 256 + count) * 32;
-  return 2 * (small + table) + ((int64_t)16 << 20);
+  return 2 * (multi_state(vertices, count, label_ptrs) + table) + ((int64_t)16 << 20);
 }
 
 // Host arrays gathered for one upload: a copy from pageable memory costs
@@ -965,10 +975,12 @@ void multi_ranges(Arena& ar, const mcc_problem* probs, const std::vector<int32_t
 }
 
 // One wave: the instances probs[ids[j]], results in res[ids[j]].  Instances
-// the kernels do not take are left with their ranges known.
+// the kernels do not take, or whose table alone passes the table budget, are
+// left with their ranges known; those that the others leave no room for are
+// left to another wave, their ranges in res.
 void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>& ids,
                 int32_t max_rounds, bool literal, hipStream_t st, MultiResult* res,
-                int64_t* dtrace = nullptr) {
+                int64_t* dtrace = nullptr, int64_t table_budget = INT64_MAX) {
   const int32_t count = (int32_t)ids.size();
   MultiSet set;
   multi_ranges(ar, probs, ids, max_rounds, literal, true, st, &set);
@@ -991,8 +1003,8 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
     r.err = hc[j].err;
     if (r.err || !multi_fits(m.n, r.K0, r.Ls)) continue;
     const int64_t tb = multi_table_bytes(m.n, m.k, r.K0, (int32_t)r.Ls);
-    if (toff > 0 && toff + tb > kMultiWaveTable) {
-      r.known = false;  // another wave
+    if (toff + tb > table_budget) {
+      r.known = count == 1;
       continue;
     }
     m.K0 = r.K0;
@@ -1214,9 +1226,11 @@ bool densify_pays(int64_t n, int32_t k, int64_t K0, int64_t K1, int64_t Lmax) {
 }
 
 // One solve.  noalloc: the workspace is the device's scratch array instead
-// of the cached chunks (nothing is allocated).
+// of the cached chunks (nothing is allocated).  cap: most bytes of chunks to ask
+// for (0: any number); MCC_ESCRATCH, nothing written, if that is too little.
 int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
-                   const int32_t* init, int32_t* out, mcc_stats* stats, bool noalloc) {
+                   const int32_t* init, int32_t* out, mcc_stats* stats, bool noalloc,
+                   size_t cap = 0) {
   if (!g || k < 1 || g->n < 0 || g->nnz < 0) return MCC_EINVAL;
   const int64_t n = g->n;
   const int32_t max_rounds = stats && stats->max_rounds > 0 ? stats->max_rounds : 1000;
@@ -1255,7 +1269,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
   // the label rows and per-vertex state alone must fit the scratch array
   if (noalloc && (uint64_t)(4 * n * (int64_t)k + 48 * n) > kScratchBytes) return MCC_ESCRATCH;
   try {
-    Arena ar(st, noalloc ? scratch_address() : nullptr, kScratchBytes);
+    Arena ar(st, noalloc ? scratch_address() : nullptr, noalloc ? kScratchBytes : cap);
     struct Events {
       std::vector<hipEvent_t> e;
       hipEvent_t make() {
@@ -2082,36 +2096,31 @@ void tiny_instances(const mcc_problem* probs, const std::vector<int32_t>& eligib
   }
 }
 
-// Workspace that mcc_batch_workspace_bytes grants a call beyond the
-// persistent launch's own, for instances solved one after another.
-constexpr int64_t kAloneBytes = (int64_t)192 << 20;
+// Workspace of a batched call whose persistent launch over all of its
+// instances takes z: arrays below the chunk size are carved from chunks.  Every
+// step of the call keeps to it, whichever kernels take the instances.
+int64_t batch_grant(const BatchSizes& z) { return 2 * z.bytes + ((int64_t)16 << 20); }
 
 // Whether the instances the level-by-level kernels left are better solved
 // one after another by mcc_consensus than in one persistent launch, whose
-// workgroups take one instance each: all of their ranges must be known and
-// their workspace bounded.  Measured: a workgroup takes about 28 ns for an
-// arc or label of its instance (24 SBM instances of up to 20 000 vertices
-// and 64 partitions: 48 ms for the largest, 1.7 M of them), a lone solve
-// about 0.5 ms and 1 ns for each.
-bool rest_alone(const mcc_problem* probs, const std::vector<int32_t>& rest, int32_t count,
-                const std::vector<MultiResult>& mres, int64_t cells_cap, int wgpc) {
-  const BatchSizes z = batch_sizes(probs, rest, count, cells_cap, wgpc);
-  const int64_t grant = std::max(2 * z.bytes + ((int64_t)16 << 20), kAloneBytes);
+// workgroups take one instance each: all of their ranges must be known.
+// Measured: a workgroup takes about 28 ns for an arc or label of its instance
+// (24 SBM instances of up to 20 000 vertices and 64 partitions: 48 ms for the
+// largest, 1.7 M of them), a lone solve about 0.5 ms and 1 ns for each.
+bool rest_alone(const mcc_problem* probs, const std::vector<int32_t>& rest,
+                const std::vector<MultiResult>& mres, int wgpc) {
+  const double groups = (double)std::min<int64_t>((int64_t)rest.size(),
+                                                  (int64_t)device_sms() * wgpc);
   double sum = 0, most = 0, lone = 0;
   for (int32_t i : rest) {
     const mcc_problem& p = probs[i];
-    const MultiResult& r = mres[i];
-    int64_t bound = 0;
-    if (!r.known || r.Ls < 1 ||
-        mcc_workspace_bound(p.g.n, p.g.nnz, p.k, r.Ls - 1, r.K0, 0, &bound) != MCC_OK ||
-        bound > grant)
-      return false;
+    if (!mres[i].known || mres[i].Ls < 1) return false;
     const double w = (double)p.g.nnz + (double)p.g.n * p.k;
     sum += w;
     most = std::max(most, w);
     lone += 0.5 + 1e-6 * w;
   }
-  return lone < 28e-6 * std::max(most, sum / (double)z.slots);
+  return lone < 28e-6 * std::max(most, sum / groups);
 }
 
 }  // namespace
@@ -2172,9 +2181,24 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
     HIPCK(hipEventRecord(e0, st));
     std::vector<BatchRes> hres(count);
     std::vector<MultiResult> mres(count);
-    std::vector<bool> counted(count, false);  // solved alone, and counted as batched
     auto held = [&](int64_t bytes) {
       if (opts) opts->workspace_bytes = std::max(opts->workspace_bytes, bytes);
+    };
+    // Instance i by itself, within `cap` bytes of workspace (0: any): false if
+    // it takes more.
+    auto solve = [&](int32_t i, size_t cap) {
+      const mcc_problem& p = probs[i];
+      mcc_stats one;
+      memset(&one, 0, sizeof one);
+      one.max_rounds = max_rounds;
+      one.flags = flags & MCC_F_LITERAL;
+      one.stream = st;
+      const int rc = consensus_impl(&p.g, p.labels, p.k, p.init, p.out, &one, false, cap);
+      if (cap && rc == MCC_ESCRATCH) return false;
+      status[i] = rc;
+      if (stats && rc == MCC_OK) stats[i] = one;
+      held(one.workspace_bytes);
+      return true;
     };
     if (!eligible.empty()) {
       BatchRun run;
@@ -2192,6 +2216,7 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
       run.cells_cap = covered ? std::min(kCellsCapMax, std::max(kCellsCapMin, pow2_ceil(cells)))
                               : heuristic_cells_cap(probs, eligible);
       run.wgpc = wgpc;
+      const BatchSizes slots = batch_sizes(probs, eligible, count, run.cells_cap, wgpc);
       run.n_max = n_max;
       run.max_rounds = max_rounds;
       run.literal = (flags & MCC_F_LITERAL) ? 1 : 0;
@@ -2244,7 +2269,10 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
           // A wave that finds its table budget full leaves the ranges it found
           // of the others, so that a later one takes only what it can hold
           // (each looking all of them over again, 20 000 instances in waves
-          // of 500 would be looked over 400 000 times).
+          // of 500 would be looked over 400 000 times).  Its state takes at
+          // most half of what the persistent launch over the whole batch
+          // would, its tables the rest; a table beyond the half has a wave of
+          // its own.
           std::vector<int32_t> wave, later;
           int64_t vertices = 0, table = 0, groups = 0;
           for (int32_t i : todo) {
@@ -2252,19 +2280,24 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
             const MultiResult& r = mres[i];
             const int64_t tb = r.Ls > 0 ? multi_table_bytes(probs[i].g.n, probs[i].k, r.K0,
                                                             (int32_t)r.Ls) : 0;
-            if (!wave.empty() && (vertices + v > kMultiWaveVertices ||
-                                  table + tb > kMultiWaveTable ||
-                                  groups + 1 + probs[i].k > kMultiWaveGroups)) {
+            const int64_t g = groups + 1 + probs[i].k;
+            if (!wave.empty() &&
+                (vertices + v > kMultiWaveVertices || g > kMultiWaveGroups ||
+                 table + tb > std::min(kMultiWaveTable, slots.bytes / 2) ||
+                 multi_state(vertices + v, (int64_t)wave.size() + 1, g) > slots.bytes / 2)) {
               later.push_back(i);
             } else {
               wave.push_back(i);
               vertices += v;
               table += tb;
-              groups += 1 + probs[i].k;
+              groups = g;
             }
           }
+          const int64_t room =
+              slots.bytes - multi_state(vertices, (int64_t)wave.size(), groups);
           Arena ar(st);
-          multi_wave(ar, probs, wave, max_rounds, run.literal != 0, st, mres.data());
+          multi_wave(ar, probs, wave, max_rounds, run.literal != 0, st, mres.data(), nullptr,
+                     wave.size() > 1 ? std::min(room, kMultiWaveTable) : room);
           held((int64_t)ar.bytes_used());
           todo.clear();
           for (int32_t i : wave)  // the wave's table budget was full
@@ -2293,27 +2326,15 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
           rest.push_back(i);
         }
       }
-      if (!rest.empty() && rest_alone(probs, rest, count, mres, run.cells_cap, wgpc))
-        alone.swap(rest);
+      if (!rest.empty() && rest_alone(probs, rest, mres, wgpc)) alone.swap(rest);
       for (int32_t i : alone) {
-        fallback.push_back(i);
-        counted[i] = true;
+        // one that takes more workspace than the call may goes to the launch
+        if (!solve(i, (size_t)batch_grant(slots))) rest.push_back(i);
+        else if (opts && status[i] == MCC_OK) opts->solved_in_batch += 1;
       }
       if (!rest.empty()) persistent(rest, &fallback);
     }
-    for (int32_t i : fallback) {
-      const mcc_problem& p = probs[i];
-      mcc_stats one;
-      memset(&one, 0, sizeof one);
-      one.max_rounds = max_rounds;
-      one.flags = flags & MCC_F_LITERAL;
-      one.stream = st;
-      const int rc = mcc_consensus(&p.g, p.labels, p.k, p.init, p.out, &one);
-      status[i] = rc;
-      if (stats && rc == MCC_OK) stats[i] = one;
-      if (opts && rc == MCC_OK && counted[i]) opts->solved_in_batch += 1;
-      held(one.workspace_bytes);
-    }
+    for (int32_t i : fallback) solve(i, 0);
     HIPCK(hipEventRecord(e1, st));
     sync(st);
     if (opts) HIPCK(hipEventElapsedTime(&opts->ms_total, e0, e1));
@@ -2908,22 +2929,7 @@ int mcc_batch_workspace_bytes(const mcc_problem* probs, int32_t count,
     const int64_t cap = covered ? std::min(kCellsCapMax, std::max(kCellsCapMin, pow2_ceil(cells)))
                                 : heuristic_cells_cap(probs, eligible);
     const BatchSizes z = batch_sizes(probs, eligible, count, cap, wgpc);
-    // carved from 16 MiB chunks (larger requests get their own)
-    *bytes = std::max(2 * z.bytes + ((int64_t)16 << 20), kAloneBytes);
-    // the level-by-level kernels' waves
-    int64_t vertices = 0, ptrs = 0, table = 0, largest = 0;
-    for (int32_t i : eligible) {
-      const mcc_problem& p = probs[i];
-      ptrs += p.k;
-      if (p.g.n <= 0 || p.g.n > kMultiVertices) continue;
-      vertices += p.g.n;
-      const int64_t t = multi_table_bound(p.g.n, p.k) + 256;
-      table += t;
-      largest = std::max(largest, t);
-    }
-    const int64_t waved = std::min(vertices, kMultiWaveVertices + kMultiVertices);
-    *bytes = std::max(*bytes, multi_bound(waved, (int64_t)eligible.size(), ptrs,
-                                          std::min(table, kMultiWaveTable + largest)));
+    *bytes = batch_grant(z);
   }
   *bytes = std::max(*bytes, single);
   return MCC_OK;
