@@ -974,13 +974,32 @@ void multi_ranges(Arena& ar, const mcc_problem* probs, const std::vector<int32_t
   sync(st);
 }
 
+// Events of a lone instance's solve: the start of its passes, and on request
+// the begin and end of every slot's scoring.
+struct MultiEvents {
+  hipEvent_t passes = nullptr;
+  bool profile = false;
+  std::vector<hipEvent_t> score;
+  ~MultiEvents() {
+    for (hipEvent_t e : score) (void)hipEventDestroy(e);
+  }
+  void mark(hipStream_t st) {
+    if (!profile) return;
+    hipEvent_t e;
+    HIPCK(hipEventCreate(&e));
+    score.push_back(e);
+    HIPCK(hipEventRecord(e, st));
+  }
+};
+
 // One wave: the instances probs[ids[j]], results in res[ids[j]].  Instances
 // the kernels do not take, or whose table alone passes the table budget, are
 // left with their ranges known; those that the others leave no room for are
 // left to another wave, their ranges in res.
 void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>& ids,
                 int32_t max_rounds, bool literal, hipStream_t st, MultiResult* res,
-                int64_t* dtrace = nullptr, int64_t table_budget = INT64_MAX) {
+                int64_t* dtrace = nullptr, int64_t table_budget = INT64_MAX,
+                MultiEvents* events = nullptr) {
   const int32_t count = (int32_t)ids.size();
   MultiSet set;
   multi_ranges(ar, probs, ids, max_rounds, literal, true, st, &set);
@@ -1096,6 +1115,7 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
       launch_multi_build(a, items(w, W[w].at_parts[c]), W[w].parts[c], w != 0, W[w].cells[c],
                          st);
   }
+  if (events) HIPCK(hipEventRecord(events->passes, st));
   // slots are enqueued ahead in growing chunks; a pass takes one, or two when
   // it falls back
   int64_t enqueued = 0;
@@ -1109,6 +1129,7 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
         // which several share a compute unit (32 and 48 take as long), 64 KiB
         // for large ones (4096 instances 30.6 ms; 31.3 with 48, 32.0 with 32,
         // 33.9 with 96); none for the mode that reads the table from memory
+        if (events) events->mark(st);
         for (int md = 0; md < kMultiModes; ++md) {
           const size_t room = tile == 256 ? (16 << 10) : (64 << 10);
           const size_t buf =
@@ -1116,6 +1137,7 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
           launch_multi_score(a, items(w, x.at_tiles[md]), x.tiles[md], w != 0, md, tile,
                              x.words[md], buf, st);
         }
+        if (events) events->mark(st);
         for (int c = 0; c < 2; ++c)
           launch_multi_apply(a, items(w, x.at_parts[c]), x.parts[c], w != 0,
                              x.cells[c], st);
@@ -1289,14 +1311,18 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     // launches a pass instead of eight or more
     int64_t known = -1;  // the largest label, once the inputs are known to be valid
     if (lanes_req == 0 && n <= kMultiVertices && k <= 256 && (init || n <= kMultiClusters) &&
-        !(flags & ~(MCC_F_TRACE | MCC_F_LITERAL | MCC_F_SYMMETRIC))) {
+        !(flags & ~(MCC_F_TRACE | MCC_F_LITERAL | MCC_F_SYMMETRIC | MCC_F_PROFILE))) {
       unsigned char* const before = ar.mark();
       int64_t* dtrace = nullptr;
       mcc_problem one{*g, labels, k, init, out};
       MultiResult r;
+      MultiEvents ev;
+      ev.passes = events.make();
+      ev.profile = (flags & MCC_F_PROFILE) != 0;
       try {
         if (flags & MCC_F_TRACE) dtrace = ar.get<int64_t>((int64_t)max_rounds * 4);
-        multi_wave(ar, &one, {0}, max_rounds, (flags & MCC_F_LITERAL) != 0, st, &r, dtrace);
+        multi_wave(ar, &one, {0}, max_rounds, (flags & MCC_F_LITERAL) != 0, st, &r, dtrace,
+                   INT64_MAX, &ev);
       } catch (const Status& s) {
         if (s.code != MCC_ESCRATCH) throw;
         r = MultiResult{};  // no room for its arrays: the general kernels may take less
@@ -1313,7 +1339,13 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
           multi_stats(r.ctl, stats);
           stats->workspace_bytes = (int64_t)ar.bytes_used();
           HIPCK(hipEventElapsedTime(&stats->ms_total, e0, e3));
-          stats->ms_passes = stats->ms_total;
+          HIPCK(hipEventElapsedTime(&stats->ms_passes, ev.passes, e3));
+          const int slots = r.ctl.passes + r.ctl.fallback_rounds;
+          for (int j = 0; j < slots && 2 * j + 1 < (int)ev.score.size(); ++j) {
+            float ms = 0.f;
+            HIPCK(hipEventElapsedTime(&ms, ev.score[2 * j], ev.score[2 * j + 1]));
+            stats->ms_score += ms;
+          }
         }
         return MCC_OK;
       }
