@@ -1250,9 +1250,10 @@ bool densify_pays(int64_t n, int32_t k, int64_t K0, int64_t K1, int64_t Lmax) {
 // One solve.  noalloc: the workspace is the device's scratch array instead
 // of the cached chunks (nothing is allocated).  cap: most bytes of chunks to ask
 // for (0: any number); MCC_ESCRATCH, nothing written, if that is too little.
-int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
-                   const int32_t* init, int32_t* out, mcc_stats* stats, bool noalloc,
-                   size_t cap = 0) {
+// lean: without the arrays that a solve can do without.
+int consensus_try(const mcc_csr* g, const int32_t* const* labels, int32_t k,
+                  const int32_t* init, int32_t* out, mcc_stats* stats, bool noalloc, size_t cap,
+                  bool lean) {
   if (!g || k < 1 || g->n < 0 || g->nnz < 0) return MCC_EINVAL;
   const int64_t n = g->n;
   const int32_t max_rounds = stats && stats->max_rounds > 0 ? stats->max_rounds : 1000;
@@ -1310,7 +1311,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     // a small instance with few clusters: the level-by-level kernels, three
     // launches a pass instead of eight or more
     int64_t known = -1;  // the largest label, once the inputs are known to be valid
-    if (lanes_req == 0 && n <= kMultiVertices && k <= 256 && (init || n <= kMultiClusters) &&
+    if (!lean && lanes_req == 0 && n <= kMultiVertices && k <= 256 && (init || n <= kMultiClusters) &&
         !(flags & ~(MCC_F_TRACE | MCC_F_LITERAL | MCC_F_SYMMETRIC | MCC_F_PROFILE))) {
       unsigned char* const before = ar.mark();
       int64_t* dtrace = nullptr;
@@ -1360,7 +1361,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
                 ((flags & MCC_F_HASH_TABLES) ? kHashForce : 0u) |
                     ((flags & MCC_F_HASH_ROWS) ? kHashRows : 0u) |
                     ((flags & MCC_F_HASH_KEYS) ? kHashKeys : 0u),
-                known, lanes_req == 0 && !(flags & MCC_F_ARC_CACHE),
+                known, !lean && lanes_req == 0 && !(flags & MCC_F_ARC_CACHE),
                 (flags & MCC_F_TRACE) ? 32 * (int64_t)max_rounds : 0);
 
     // What the solve must have is taken before the arrays that it can do
@@ -1462,7 +1463,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
       launch_narrow(S.C, a.Cn, a.cn_bytes, n, st);
     }
     int32_t* const ncl = ar.get<int32_t>(1);
-    if (S.t.hashed) {
+    if (S.t.hashed && !lean) {
       const int32_t width = S.maxL <= 256 ? 1 : (S.maxL <= 65536 ? 2 : 0);
       const int64_t stride = (width * (int64_t)k + 15) & ~(int64_t)15;
       if (width && ar.fits(n * stride + 256)) {
@@ -1483,7 +1484,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     // the arcs of a symmetric graph, else pulled (not beside the arc cache,
     // nor where the scratch array has no room for them).
     const bool push = (flags & MCC_F_SYMMETRIC) != 0;
-    if (lanes == 0 && (push || !(flags & MCC_F_ARC_CACHE)) && ar.fits(carry_bytes(n, S.K0))) {
+    if (!lean && lanes == 0 && (push || !(flags & MCC_F_ARC_CACHE)) && ar.fits(carry_bytes(n, S.K0))) {
       if (!push) {
         a.moved = ar.get<uint32_t>((n + 31) / 32);
         launch_fill_i32(reinterpret_cast<int32_t*>(a.moved), (n + 31) / 32, 0, st);
@@ -1531,7 +1532,7 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     // keep the order of the old ones, so no decision changes.  (2 M kNN
     // vertices from singletons: 50 000 clusters after four passes, 180 after
     // eight; LFR 100 k: 700 after four.)
-    const bool shrinks = S.t.hashed && !(flags & (MCC_F_HASH_TABLES | MCC_F_HASH_ROWS |
+    const bool shrinks = !lean && S.t.hashed && !(flags & (MCC_F_HASH_TABLES | MCC_F_HASH_ROWS |
                                                   MCC_F_HASH_KEYS | MCC_F_ARC_CACHE));
     int32_t* const cmap = a.mstart;
     int32_t* const live = a.mcnt;
@@ -1659,6 +1660,16 @@ int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
   } catch (...) {
     return translate(std::current_exception());
   }
+}
+
+// The same, and again without those arrays where the device has no memory for
+// them: nothing is written before the last of them is there.
+int consensus_impl(const mcc_csr* g, const int32_t* const* labels, int32_t k,
+                   const int32_t* init, int32_t* out, mcc_stats* stats, bool noalloc,
+                   size_t cap = 0) {
+  int rc = consensus_try(g, labels, k, init, out, stats, noalloc, cap, false);
+  if (rc == MCC_ENOMEM) rc = consensus_try(g, labels, k, init, out, stats, noalloc, cap, true);
+  return rc;
 }
 
 }  // namespace
