@@ -711,6 +711,7 @@ constexpr int kSetSlots = 2048;
 constexpr int kSetProbe = 64;
 constexpr int kProbeLanes = 16;
 constexpr int64_t kSmallTileMax = (int64_t)1 << 18;  // vertices scored by tiles of 64
+constexpr int64_t kSmallTileFew = (int64_t)5 << 15;  // the same with at most 256 clusters
 static_assert(kMemberSumMax <= kProbeLanes, "member ids of a small cluster fit one probe group");
 
 // Clusters at the heads of a thread's arcs (-1 where the tail is -1): one
@@ -2335,16 +2336,22 @@ void launch_tile(const PassArgs& a, int grid, hipStream_t st) {
   // Vertices a tile: up to 2^18 vertices, tiles of 64 (a launch of 256 would
   // leave compute units without a tile: 15 passes over 100 000 vertices of
   // an LFR graph 5.9 ms against 9.3, 24 over 30 000 3.5 against 7.9).  Above,
-  // tiles of 256 where at most 256 clusters keep the candidates few (2 M kNN
-  // vertices, 51 clusters, scored by tiles: 8.2 ms against 8.8 with 128), else
-  // 128, whose key set holds 16 candidates a vertex (1 M LFR vertices, ten
-  // candidates each, all passes dense: 49.6 ms against 51.4 with 256 and 54.7
-  // with 64).
+  // tiles of 128, whose key set holds 16 candidates a vertex (1 M LFR
+  // vertices, ten candidates each, all passes dense: 49.6 ms against 51.4 with
+  // 256 and 54.7 with 64).  At most 256 clusters keep the candidates few, and
+  // tiles of 256 pay from 2.5 of them a compute unit (kNN shape, 42 partitions,
+  // tiles of 64 and 256: 120 000 vertices 0.74 and 0.78 ms, 160 000 1.82 and
+  // 1.79, 200 000 2.19 and 2.05, 250 000 2.29 and 2.10; 2 M scored by tiles 8.8
+  // with 128, 8.2 with 256).
   // Tiles of 64 also where the candidates are many: with hashed tables, whose
   // starts have one for most arcs, and after a pass with more than twelve.
-  if (TK == kHashed || a.tile_small || a.n <= kSmallTileMax) launch_tile_v<TK, 64>(a, st);
-  else if (a.K0 <= 256) launch_tile_v<TK, 256>(a, st);
-  else launch_tile_v<TK, 128>(a, st);
+  const bool few = a.K0 <= 256;
+  if (TK == kHashed || a.tile_small || a.n <= (few ? kSmallTileFew : kSmallTileMax))
+    launch_tile_v<TK, 64>(a, st);
+  else if (few)
+    launch_tile_v<TK, 256>(a, st);
+  else
+    launch_tile_v<TK, 128>(a, st);
   launch_list<TK>(a, grid, st);
 }
 
