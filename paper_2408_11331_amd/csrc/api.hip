@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <map>
 #include <mutex>
 #include <string>
@@ -974,13 +975,14 @@ void multi_ranges(Arena& ar, const mcc_problem* probs, const std::vector<int32_t
   sync(st);
 }
 
-// Events of a lone instance's solve: the start of its passes, and on request
+// Times of a lone instance's solve: its pass loop by the host's clock (the loop
+// ends with the stream idle; an event would cost 5 of 140 us), and on request
 // the begin and end of every slot's scoring.
-struct MultiEvents {
-  hipEvent_t passes = nullptr;
+struct MultiTimes {
+  float ms_passes = 0.f;
   bool profile = false;
   std::vector<hipEvent_t> score;
-  ~MultiEvents() {
+  ~MultiTimes() {
     for (hipEvent_t e : score) (void)hipEventDestroy(e);
   }
   void mark(hipStream_t st) {
@@ -999,7 +1001,7 @@ struct MultiEvents {
 void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>& ids,
                 int32_t max_rounds, bool literal, hipStream_t st, MultiResult* res,
                 int64_t* dtrace = nullptr, int64_t table_budget = INT64_MAX,
-                MultiEvents* events = nullptr) {
+                MultiTimes* times = nullptr) {
   const int32_t count = (int32_t)ids.size();
   MultiSet set;
   multi_ranges(ar, probs, ids, max_rounds, literal, true, st, &set);
@@ -1115,7 +1117,7 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
       launch_multi_build(a, items(w, W[w].at_parts[c]), W[w].parts[c], w != 0, W[w].cells[c],
                          st);
   }
-  if (events) HIPCK(hipEventRecord(events->passes, st));
+  const auto begin = std::chrono::steady_clock::now();
   // slots are enqueued ahead in growing chunks; a pass takes one, or two when
   // it falls back
   int64_t enqueued = 0;
@@ -1129,7 +1131,7 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
         // which several share a compute unit (32 and 48 take as long), 64 KiB
         // for large ones (4096 instances 30.6 ms; 31.3 with 48, 32.0 with 32,
         // 33.9 with 96); none for the mode that reads the table from memory
-        if (events) events->mark(st);
+        if (times) times->mark(st);
         for (int md = 0; md < kMultiModes; ++md) {
           const size_t room = tile == 256 ? (16 << 10) : (64 << 10);
           const size_t buf =
@@ -1137,7 +1139,7 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
           launch_multi_score(a, items(w, x.at_tiles[md]), x.tiles[md], w != 0, md, tile,
                              x.words[md], buf, st);
         }
-        if (events) events->mark(st);
+        if (times) times->mark(st);
         for (int c = 0; c < 2; ++c)
           launch_multi_apply(a, items(w, x.at_parts[c]), x.parts[c], w != 0,
                              x.cells[c], st);
@@ -1168,6 +1170,9 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
     if (!any) break;
     chunk = std::min(chunk * 2, 16);
   }
+  if (times)
+    times->ms_passes = std::chrono::duration<float, std::milli>(
+                           std::chrono::steady_clock::now() - begin).count();
   for (auto& l : live)
     for (int32_t j : l) {
       res[ids[j]].solved = true;
@@ -1317,13 +1322,12 @@ int consensus_try(const mcc_csr* g, const int32_t* const* labels, int32_t k,
       int64_t* dtrace = nullptr;
       mcc_problem one{*g, labels, k, init, out};
       MultiResult r;
-      MultiEvents ev;
-      ev.passes = events.make();
-      ev.profile = (flags & MCC_F_PROFILE) != 0;
+      MultiTimes times;
+      times.profile = (flags & MCC_F_PROFILE) != 0;
       try {
         if (flags & MCC_F_TRACE) dtrace = ar.get<int64_t>((int64_t)max_rounds * 4);
         multi_wave(ar, &one, {0}, max_rounds, (flags & MCC_F_LITERAL) != 0, st, &r, dtrace,
-                   INT64_MAX, &ev);
+                   INT64_MAX, &times);
       } catch (const Status& s) {
         if (s.code != MCC_ESCRATCH) throw;
         r = MultiResult{};  // no room for its arrays: the general kernels may take less
@@ -1340,11 +1344,11 @@ int consensus_try(const mcc_csr* g, const int32_t* const* labels, int32_t k,
           multi_stats(r.ctl, stats);
           stats->workspace_bytes = (int64_t)ar.bytes_used();
           HIPCK(hipEventElapsedTime(&stats->ms_total, e0, e3));
-          HIPCK(hipEventElapsedTime(&stats->ms_passes, ev.passes, e3));
+          stats->ms_passes = times.ms_passes;
           const int slots = r.ctl.passes + r.ctl.fallback_rounds;
-          for (int j = 0; j < slots && 2 * j + 1 < (int)ev.score.size(); ++j) {
+          for (int j = 0; j < slots && 2 * j + 1 < (int)times.score.size(); ++j) {
             float ms = 0.f;
-            HIPCK(hipEventElapsedTime(&ms, ev.score[2 * j], ev.score[2 * j + 1]));
+            HIPCK(hipEventElapsedTime(&ms, times.score[2 * j], times.score[2 * j + 1]));
             stats->ms_score += ms;
           }
         }
