@@ -27,15 +27,27 @@ def dev(a):
 
 
 class Holding:
-    """Device memory down to about `left` bytes held by tensors."""
+    """Device memory held by tensors: down to about `left` bytes, and then
+    further by 16 MiB a step.  (The runtime may keep freed memory that it
+    neither reports as free nor hands to others, so how much a call finds shows
+    only when it asks.)"""
 
     def __init__(self, left):
         import torch
         self.kept = []
         torch.cuda.empty_cache()
-        for size in (32 << 30, 4 << 30, 512 << 20, 64 << 20, 8 << 20):
-            while torch.cuda.mem_get_info()[0] >= left + size:
-                self.kept.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
+        for size in (32 << 30, 4 << 30, 512 << 20, 64 << 20, 16 << 20):
+            while torch.cuda.mem_get_info()[0] >= left + size and self.more(size):
+                pass
+
+    def more(self, size=16 << 20):
+        """One block more; False when the device has none."""
+        import torch
+        try:
+            self.kept.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
+            return True
+        except torch.OutOfMemoryError:
+            return False
 
     def __enter__(self):
         return self
@@ -47,8 +59,8 @@ class Holding:
 
 
 def test_little_memory(mcc):
-    """The solve takes 0.29 GB with everything, well under 0.65 of it without:
-    it is accepted with that left, and equal."""
+    """The solve takes 0.33 GB with everything, a third of it without: as
+    memory runs out it goes on to do without, with an equal result."""
     import torch
     print("[gpu-case] little device memory", flush=True)
     n, k, c = 1_500_000, 2, 12
@@ -59,18 +71,20 @@ def test_little_memory(mcc):
     noise = rng.random((k, n)) < 0.1
     lab[noise] = rng.integers(0, c, int(noise.sum()))
     args = [dev(rp), dev(col), dev(lab.astype(np.int32)), dev(lab[0].astype(np.int32))]
-    less = 0.65
     out = torch.empty(args[0].numel() - 1, dtype=torch.int32, device="cuda")
     again = torch.empty_like(out)
     mcc.release_workspace()
     _, ref = mcc.consensus(*args, out=out)
     mcc.release_workspace()
     torch.cuda.synchronize()
-    with Holding(int(less * ref["workspace_bytes"])):
-        _, st = mcc.consensus(*args, out=again)
-        torch.cuda.synchronize()
-        assert st["workspace_bytes"] < less * ref["workspace_bytes"]
-        mcc.release_workspace()
+    with Holding(ref["workspace_bytes"]) as held:
+        for _ in range(200):  # until the solve does not find room for everything
+            _, st = mcc.consensus(*args, out=again)
+            torch.cuda.synchronize()
+            mcc.release_workspace()
+            if st["workspace_bytes"] < ref["workspace_bytes"] or not held.more():
+                break
+    assert st["workspace_bytes"] < 0.65 * ref["workspace_bytes"]
     assert torch.equal(out, again)
     for key in KEYS:
         assert st[key] == ref[key], key
