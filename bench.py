@@ -155,10 +155,11 @@ def bench_batch(args):
         "config": {"workload": "sbm_batch", "instances": count,
                    "sum_n": int(sum(i.n for i in insts)), "sum_nnz": int(sum(i.nnz for i in insts)),
                    "sum_nk": int(sum(i.n * i.k for i in insts)),
-                   "solved_in_persistent_kernel": info["solved_in_batch"],
+                   "solved_in_batch": info["solved_in_batch"],
                    "candidate_evals": int(evals),
                    "wg_per_cu": table.wg_per_cu if table is not None else args.wg_per_cu,
-                   "lanes": "autotuned per size bucket" if table is not None else args.lanes},
+                   "lanes": "autotuned per size bucket (persistent launch)" if table is not None
+                   else args.lanes},
         "autotune": None if table is None else {
             "tuned_on_instances": len(probs), "seconds": tune_s,
             "untuned_solves_per_s": count / untuned, "table": table.as_dict()},

@@ -70,8 +70,10 @@ extern "C" {
                                  results do not depend on it) */
 #define MCC_F_SYMMETRIC 0x40u /* the caller states that the graph is symmetric
                                  (every arc (v, u) has a reverse arc (u, v)):
-                                 candidate sets are then carried over between
-                                 passes for vertices with no moved neighbour.
+                                 the candidate sets carried over between passes
+                                 (for vertices with no moved neighbour) are
+                                 then kept up along the movers' arcs instead of
+                                 by a look at every vertex's neighbours.
                                  Results do not change; on a graph that is not
                                  symmetric they may differ from the exact
                                  method, so with MCC_F_VALIDATE the library
@@ -130,19 +132,23 @@ typedef struct {
   int64_t objective_init;  /* sum_i Mirkin(init, P_i) */
   int64_t objective;       /* sum_i Mirkin(out, P_i) */
   float ms_total;          /* wall time of the call on the stream */
-  float ms_passes;         /* time spent in the pass loop */
+  float ms_passes;         /* time spent in the pass loop (0 for an instance of
+                              a batch; small instances: by the host's clock) */
   int64_t boundary;        /* sum over passes of the vertices that had at
                               least one candidate (their label rows are read) */
   float ms_score;          /* with MCC_F_PROFILE: summed duration of the
                               scoring kernels of the executed passes */
-  int32_t lanes_used;      /* the `lanes` the scoring ran with (0 = tiled) */
-  int32_t tables;          /* contingency table layout used: 0 dense blocked,
+  int32_t lanes_used;      /* the `lanes` the scoring ran with (0 = tiled, or
+                              level by level) */
+  int32_t tables;          /* contingency table layout the solve started with:
+                              0 dense, a block or slice for each partition,
                               1 dense interleaved, 2 hashed keys, 3 hashed
                               rows */
   int64_t skipped_evals;   /* of candidate_evals, those not recomputed because
                               an exact bound showed the vertex could not
-                              propose (with MCC_F_SYMMETRIC; they count in
-                              candidate_evals as the method scores them) */
+                              propose (where candidate sets are carried over;
+                              they count in candidate_evals as the method
+                              scores them) */
   int64_t workspace_bytes; /* device workspace the call held (kept by the
                               library for later calls on the stream) */
 } mcc_stats;
@@ -267,6 +273,10 @@ typedef struct {
   void* stream;       /* hipStream_t or NULL */
   int32_t max_rounds; /* per instance; 0 means 1000 */
   uint32_t flags;     /* MCC_F_LITERAL honoured; others ignored */
+  /* lanes, wg_per_cu, tune and tune_cache_path shape the persistent launch (see
+     mcc_consensus_batch).  With lanes or wg_per_cu set every instance goes to
+     it; with both 0 only those that the level-by-level kernels do not take, and
+     a tune table shapes the launch for these alone. */
   int32_t lanes;      /* lanes per vertex for every instance: 4, 8, 16, 32 or 64;
                          0: per instance from the tune table (`tune`, else
                          the file `tune_cache_path`, else a built-in rule) */
@@ -289,11 +299,12 @@ typedef struct {
  * homogeneous partitions the paper solves independently, Methods, "The
  * algorithm").  Instances of up to 65 536 vertices and 256 initial clusters
  * with small contingency tables are solved together, each step of a pass one
- * launch over all of them.  The others, and every instance when lanes or
- * wg_per_cu is set, go to one persistent launch, whose workgroups take one
- * instance at a time from a queue ordered by estimated work (largest first)
- * and run the whole method of mcc_consensus on it; where a few are left,
- * they are solved one after another if that is faster.
+ * launch over all of them ("level by level").  The others, many tiny ones,
+ * and every instance when lanes or wg_per_cu is set, go to one persistent
+ * launch, whose workgroups take one instance at a time from a queue ordered by
+ * estimated work (largest first) and run the whole method of mcc_consensus on
+ * it; where a few are left, they are solved one after another if that is
+ * faster.
  * Instances beyond a workgroup's capacities (more than 256 partitions,
  * label values far above n, large contingency tables) are solved by
  * mcc_consensus on the same stream.  Every out[] and every stats field
@@ -309,7 +320,8 @@ int mcc_consensus_batch(const mcc_problem* probs, int32_t count, mcc_stats* stat
                         mcc_batch_opts* opts);
 
 /*
- * Autotuner of the batched solver (the many-instance launch above).
+ * Autotuner of the batched solver's persistent launch (above; a call that
+ * leaves its shape to the library solves most instances without it).
  * Solves every problem once per candidate lanes value (4, 8, 16, 32, 64),
  * each time in one persistent launch whose workgroups time their own
  * instances, and keeps for each size bucket the lanes value with the
@@ -342,7 +354,8 @@ int mcc_batch_tune(const mcc_problem* probs, int32_t count, const mcc_batch_opts
  * for an instance of n vertices, nnz arcs and k partitions whose label
  * values all lie in [0, max_label], started from an init with `clusters`
  * distinct ids (0: unknown, or singletons), with these flags: every array
- * it sizes from those figures (the contingency tables at the largest size
+ * it sizes from those figures, with those that it leaves out where there is
+ * no room (the contingency tables at the largest size
  * the layouts that can be chosen may take: a hashed row table counts as the
  * key table it may not exceed unless MCC_F_HASH_ROWS is set, plus the
  * alignment to partition 0's labels), arrays below the 16 MiB chunk
@@ -351,10 +364,10 @@ int mcc_batch_tune(const mcc_problem* probs, int32_t count, const mcc_batch_opts
  *
  * mcc_batch_workspace_bytes: the workspace of one mcc_consensus_batch call
  * over these problems and options: the persistent launch's slots as the
- * call would size them (twice over for chunking, plus one chunk), the
- * level-by-level kernels' arrays, 192 MiB (granted to instances solved one
- * after another), or the bound of the largest instance the call hands to
- * mcc_consensus, whichever is largest (instances with k > 256; instances that turn out to exceed a
+ * call would size them over all instances (twice over for chunking, plus one
+ * chunk), to which every step of the call keeps whichever kernels it takes, or
+ * the bound of the largest instance the call hands to mcc_consensus if that is
+ * larger (instances with k > 256; instances that turn out to exceed a
  * slot's table are not foreseen).  The exact figure of a finished call is
  * opts->workspace_bytes.
  *

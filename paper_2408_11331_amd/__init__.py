@@ -315,9 +315,10 @@ def consensus_batch(problems, *, max_rounds=0, flags=0, lanes=0, wg_per_cu=0, st
 
     problems: sequence of dicts with CUDA tensors ``row_ptr`` (int64),
     ``col`` (int32), ``labels`` (int32 [k, n]) and optional ``init``.
-    ``lanes`` 0 takes each instance's lanes per vertex from ``tune`` (a
-    TuneTable), else the table file ``tune_cache_path``, else the built-in
-    rule.  Returns ``(outs, stats, status, info)``: output tensors,
+    With ``lanes`` or ``wg_per_cu`` set every instance goes to the persistent
+    launch; else only those that the level-by-level kernels leave.  ``lanes`` 0
+    takes the lanes per vertex in that launch from ``tune`` (a TuneTable), else
+    the table file ``tune_cache_path``, else the built-in rule.  Returns ``(outs, stats, status, info)``: output tensors,
     per-instance stats dicts, per-instance return codes and the batch call's
     info (instances within the batched solver's capacities, wall time)."""
     import torch

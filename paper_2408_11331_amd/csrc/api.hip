@@ -600,8 +600,8 @@ void build_solve(Arena& ar, const std::vector<const int32_t*>& hptrs, int64_t n,
     // (x, l) holds a label id l of one of x's members, so no clustering has
     // more live rows than the singletons' T0 (the sum over vertices of
     // their distinct ids), and a pass adds at most T0 more, so more than
-    // 2 T0 rows always leave an empty one (rebuilds keep the table about
-    // half full in practice).  Taken when that table is no larger than the
+    // 2 T0 rows always leave an empty one (pass_begin says when the table is
+    // rebuilt).  Taken when that table is no larger than the
     // key table and its cell indices fit 31 bits.
     std::vector<int32_t> Lk = Lh;  // label id bounds of the table's keys
     const int32_t* Lk_dev = S->lab.L;
@@ -1066,8 +1066,8 @@ void multi_wave(Arena& ar, const mcc_problem* probs, const std::vector<int32_t>&
   // Tiles of 1024 vertices read the table a quarter as often as tiles of 256,
   // and are taken once they reach half of the compute units: a batch of 24
   // (280 thousand vertices) takes 0.95 ms in tiles of 1024 and 1.07 ms in
-  // tiles of 256; below, 256 puts work on more units (LFR 30 k, 30 tiles of
-  // 1024: 2.4 ms in tiles of 256).
+  // tiles of 256; below, 256 puts work on more units (30 000 vertices are 118
+  // tiles of 256 or 30 of 1024).
   const int tile = total_n >= (int64_t)1024 * device_sms() / 2 ? 1024 : 256;
   auto cells_class = [&](const MultiInst& m) { return m.K0 * m.Ls <= kSmallCells ? 0 : 1; };
   auto tile_count = [&](const MultiInst& m) { return (int32_t)((m.n + tile - 1) / tile); };
@@ -1626,7 +1626,7 @@ int consensus_try(const mcc_csr* g, const int32_t* const* labels, int32_t k,
     if (S.t.hashed) d2h(&hash_err, S.t.herr, 1, st);
     HIPCK(hipEventRecord(e3, st));
     sync(st);
-    if (hash_err) throw Status{MCC_ENOMEM};  // cannot happen: the table stays half empty
+    if (hash_err) throw Status{MCC_ENOMEM};  // cannot happen: a slot is always empty
     if (flags & MCC_F_TRACE) {
       memset(stats->trace, 0, sizeof(int64_t) * 4 * (size_t)max_rounds);
       d2h(stats->trace, dtrace, (int64_t)4 * hc.passes, st);
@@ -2151,9 +2151,17 @@ int64_t batch_grant(const BatchSizes& z) { return 2 * z.bytes + ((int64_t)16 << 
 // Whether the instances the level-by-level kernels left are better solved
 // one after another by mcc_consensus than in one persistent launch, whose
 // workgroups take one instance each: all of their ranges must be known.
-// Measured: a workgroup takes about 28 ns for an arc or label of its instance
-// (24 SBM instances of up to 20 000 vertices and 64 partitions: 48 ms for the
-// largest, 1.7 M of them), a lone solve about 0.5 ms and 1 ns for each.
+// A workgroup takes 28 ns for an arc or label of its instance at the least:
+// SBM shapes with 160 to 240 blocks 25 (two passes), 33 (three), 50 (four) and
+// 93 (eight), LFR 150 to 1075 (up to 26 passes, tables beyond the caches),
+// singleton starts of 300 to 1000 vertices 92 to 340.  A lone solve takes 0.8
+// to 3.4 ms of these, 0.5 ms and 1 ns for an arc or label at most on the SBM
+// shapes.  The passes are not known, so the line is where the lone solves are
+// ahead of the cheapest launch: instances of 30 000 vertices, 8 partitions and
+// 160 blocks, alone and launched, 8 of them 7.3 and 42 ms, 16 14.7 and 44; of
+// 60 000 vertices, 20 partitions and 240 blocks, 16 16.2 and 57; one singleton
+// start of 1000 vertices 0.84 and 2.5.  (Beyond it LFR instances are the
+// launch's all the same: 64 of 40 000 vertices 178 ms alone.)
 bool rest_alone(const mcc_problem* probs, const std::vector<int32_t>& rest,
                 const std::vector<MultiResult>& mres, int wgpc) {
   const double groups = (double)std::min<int64_t>((int64_t)rest.size(),

@@ -63,7 +63,8 @@ constexpr int32_t kErrGraph = 4;
 //    toff[i] the first global label id of partition i, for cluster counts
 //    whose dense tables would not fit (e.g. singleton starts).  Keys are
 //    never removed; a slot whose count drops to 0 stays, and the table is
-//    rebuilt from the partition before it could fill beyond half;
+//    rebuilt from the partition before a batch could fill it beyond half
+//    (hashed rows: three quarters);
 //  - hashed rows: the same open addressing over keys x << 32 | l alone
 //    (rkeys, 8 bytes a row), each key owning a row of k counts N[r * k + i]
 //    (partition i, label id l in that partition).  With the label ids of
@@ -124,7 +125,7 @@ __device__ inline int32_t hget(const Tables& t, uint64_t key) {
 
 // Slot of `key`, claimed if absent (then `claimed` is incremented: callers
 // add their claims to *hocc once per wave, flush_claims).  The table is
-// sized and rebuilt so that it is never more than half full; should no slot
+// sized and rebuilt so that it always has an empty slot; should none
 // be found, *herr is set (the solve then reports an error) and slot 0 is
 // returned.
 __device__ inline uint32_t hslot(const Tables& t, uint64_t key, int32_t& claimed) {
@@ -454,7 +455,9 @@ struct PassArgs {
   // has its reverse) a move marks the mover and its out-neighbours, which are
   // its in-neighbours; otherwise the movers are the bits of `moved` and every
   // vertex looks its neighbours up (k_pull).  A clean vertex with a cached
-  // set (0 <= cnum <= kCacheCand) skips its arcs.  Null when off.
+  // set of up to kListLanes candidates skips its arcs; one of up to
+  // kCacheCand is bounded by it, and walks them where the bound does not
+  // settle it.  Null when off.
   int32_t* dirty;     // n
   int32_t* cnum;      // n: candidates at the last exact scoring, -1 unknown
   int32_t* ccache;    // n * kCacheCand: the candidates where they fit

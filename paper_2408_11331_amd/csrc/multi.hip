@@ -12,9 +12,10 @@
 // sets, no alignment.
 //
 // Measured against one workgroup an instance (the persistent launch): 4096
-// SBM instances of 200 to 20 000 vertices 155 -> 30.5 ms, 24 of them
+// SBM instances of 200 to 20 000 vertices 155 -> 30 ms, 24 of them
 // 48.4 -> 0.90 ms; against the general pass kernels, 1000 vertices alone
-// 0.55 -> 0.14 ms, 30 000 with 150 clusters 3.4 -> 2.5 ms.
+// 0.55 -> 0.14 ms, 30 000 with 150 clusters 5.2 to 7.6 -> 1.5 to 2.4 ms (the
+// pass count differs between inputs).
 #include "multi.h"
 
 namespace mcc {
@@ -209,7 +210,9 @@ __global__ __launch_bounds__(kLeader) void k_multi_ranges(MultiArgs a, const Mul
 
 // ---------------------------------------------------------------------------
 // The slice of one partition: counted in LDS, stored once; the objective's
-// terms from the same counts, and from partition 0's also the sizes.
+// terms from the same counts, and from partition 0's also the sizes.  Bound by
+// LDS atomics on counts that many labels share (of 4096 instances: LDS busy
+// half of the time, 93 % of it conflicts).
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_multi_build(MultiArgs a, const MultiItem* parts) {
@@ -276,10 +279,14 @@ __global__ __launch_bounds__(kBlock) void k_multi_build(MultiArgs a, const Multi
 //     from memory.
 //  3. The smallest (gain, cluster id); the proposals are appended to the
 //     instance's list.
-// Bound by LDS reads: 2 K0 bytes a label in the row modes (a row starts four
+// A label costs 2 K0 bytes of LDS reads in the row modes (a row starts four
 // banks after the one before: row strides are odd in 16-byte units), against
 // one conflicting read of 64 lanes a candidate of the wave's largest set in
-// the gather mode.
+// the gather mode.  Bound by latency with a third to a half of the vector
+// issue (rows of 32 and 64 clusters over 1.7 M vertices, tiles of 1024: 0.54
+// and 1.33 ms a pass; a wave waits 74 % of its time, the vector units are busy
+// 48 and 35 % of theirs, LDS 21 and 17, 7 to 9 % of that conflicts; 27 and 14
+// waves a compute unit).
 // ---------------------------------------------------------------------------
 constexpr int kCand = 16;
 enum ScoreMode { kGather = 0, kDirect = kMultiDirect, kRows32 = 2, kRows64 = 3 };

@@ -122,7 +122,9 @@ __device__ inline void flush_counts(const PassArgs& a, int64_t evals, int64_t np
 // smallest id without any sort.
 // ---------------------------------------------------------------------------
 constexpr int kMaxLdsPart = 256;  // partitions whose table geometry sits in LDS
-constexpr int kTileCandAvg = 24;  // candidates per vertex that fit the key sets of 64-vertex tiles
+// Candidates a vertex above which a pass counts as one for the wave-per-vertex
+// scorer (three quarters of the 32 that the key sets of 64-vertex tiles hold).
+constexpr int kTileCandAvg = 24;
 constexpr int kCandSetBits = 8;   // deferred vertex: LDS set of its candidate clusters
 constexpr int kCandSet = 1 << kCandSetBits;
 
@@ -1135,10 +1137,12 @@ void k_score_tile(PassArgs a) {
 // The counts of a candidate come from LDS where the tiled scorer gathers them
 // from L2, sixteen lanes a pair.  Bound by latency, about 40 us a tile for
 // the arcs (columns from HBM, then clusters) and 55 us for the sums (label
-// words from HBM, slices from L2) with two workgroups a compute unit; LDS is
-// busy a fifth of the time.  2 M kNN vertices, 51 clusters, 50 partitions, a
-// pass over all of them 1.22 -> 0.56 ms, over half 0.66 -> 0.30, over a
-// twentieth 0.17 -> 0.10 (from the list scorer); the solve 7.4 -> 5.2 ms.
+// words from HBM, slices from L2) with two workgroups a compute unit: waves
+// wait on memory 46 % and for issue 43 % of their time, LDS is busy 20 to 29 %
+// (half of it conflicts), the vector units 20 to 32 %.  2 M kNN vertices, 51
+// clusters, 50 partitions, a pass over all of them 1.22 -> 0.55 ms, over half
+// 0.66 -> 0.30, over a twentieth 0.17 -> 0.11 (from the list scorer); solves of
+// seven inputs 5.3 to 9.2 -> 4.0 to 6.7 ms.
 // One workgroup a compute unit with all of its LDS: 0.68 ms; slices through
 // registers instead of straight to LDS: 0.59; eight lanes a vertex for the
 // arcs: 0.69.

@@ -2,13 +2,13 @@
 
 A pool of problems (a graph, k partitions, an initial consensus) is
 registered once: its arrays are uploaded and stay resident in device
-memory, and each entry is timed once on the multi-workgroup path
-(``mcc_consensus``) and, if it is small enough, alone in the persistent
-batched launch (``mcc_consensus_batch``, one workgroup per instance).
+memory, and each entry is timed once on the single path
+(``mcc_consensus``) and, if it is small enough, in a batched call
+(``mcc_consensus_batch``).
 Requests name a pool entry and arrive at any time.  Worker threads, each
 with its own HIP stream, take requests from one admission queue in arrival
 order: "small" workers take the oldest small request and, when it pays,
-the other waiting small requests with it in one batched launch — a batched
+the other waiting small requests with it in one batched call — a batched
 call lasts about as long as its slowest instance, so requests join the
 call while that stays below the time solving them one by one would take;
 otherwise the request is solved alone.  "Large" workers solve large
@@ -52,8 +52,8 @@ class Entry:
     bound: int             # workspace bound of one solve (library sizing)
     measured: int = 0      # exact workspace of a finished solve, once known
     dev: Optional[dict] = None
-    t_single: Optional[float] = None  # seconds, alone on the multi-workgroup path
-    t_batch: Optional[float] = None   # seconds, alone in a batched launch (None: never batched)
+    t_single: Optional[float] = None  # seconds, alone on the single path
+    t_batch: Optional[float] = None   # seconds, two copies in a batched call (None: never batched)
 
     def workspace(self) -> int:
         return self.measured or self.bound
@@ -107,12 +107,11 @@ class Pool:
 
     def calibrate(self, batch_n_max: int = 16384, batch_ratio_max: float = 4.0,
                   max_rounds: int = 0):
-        """Time every entry alone on the multi-workgroup path and, if it has
-        at most batch_n_max vertices and 256 partitions, two copies of it in
-        one batched launch (after one untimed call of each that sets the
-        path up).  An entry is batched only if two copies take no longer
-        than 1.5 times one copy (else the launch hands it back to the
-        multi-workgroup path one copy after the other) and at most
+        """Time every entry alone on the single path and, if it has at most
+        batch_n_max vertices and 256 partitions, two copies of it in one
+        batched call (after one untimed call of each that sets the path up).
+        An entry is batched only if two copies take no longer than 1.5 times
+        one copy (else the call solves one copy after the other) and at most
         batch_ratio_max times its time alone."""
         import torch
 
