@@ -1799,9 +1799,7 @@ int mcc_canonicalize(const int32_t* in, int32_t* out, int64_t n, int32_t* cluste
     }
     int32_t* err = ar.get<int32_t>(1);
     launch_fill_i32(err, 1, 0, st);
-    int32_t* cflags = ar.get<int32_t>(n + 1);
-    launch_fill_i32(cflags, n + 1, 0, st);
-    launch_cluster_mark(in, n, cflags, err, st);  // range check
+    launch_cluster_mark(in, n, nullptr, err, st);  // range check
     int32_t herr = 0;
     d2h(&herr, err, 1, st);
     sync(st);

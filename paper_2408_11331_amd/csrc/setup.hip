@@ -286,6 +286,8 @@ __global__ __launch_bounds__(kBlock) void k_label_transpose_direct(
 }
 
 // ---- consensus clusters ----------------------------------------------------
+// Marks the ids that occur, and checks that all lie in [0, n) (null flags: the
+// check alone).
 __global__ __launch_bounds__(kBlock) void k_cluster_mark(const int32_t* __restrict__ init, int64_t n,
                                                          int32_t* __restrict__ flags,
                                                          int32_t* __restrict__ err) {
@@ -293,7 +295,7 @@ __global__ __launch_bounds__(kBlock) void k_cluster_mark(const int32_t* __restri
   for (int64_t v = gtid(); v < n; v += gstride()) {
     int32_t x = init[v];
     if (x < 0 || x >= n) bad = 1;
-    else flags[x] = 1;
+    else if (flags) flags[x] = 1;
   }
   if (bad) atomicOr(err, kErrInitRange);
 }
