@@ -175,10 +175,13 @@ class Arena {
       return static_cast<T*>(r);
     }
     if (fixed_ || (cap_ && bytes > cap_ - asked_)) throw Status{MCC_ESCRATCH};
-    const size_t size = std::max(bytes, cap_ ? std::min(kChunk, cap_ - asked_) : kChunk);
+    size_t size = kChunk;
+    if (cap_ && size > cap_ - asked_)  // a part of one, in steps: the cache keeps few sizes
+      size = (cap_ - asked_) & ~(((size_t)4 << 20) - 1);
+    size = std::max(bytes, size);
     asked_ += size;
     const Chunk k = chunk(size);
-    if (bytes >= kChunk) return static_cast<T*>(k.p);  // own chunk; keep the current one
+    if (bytes >= size) return static_cast<T*>(k.p);  // own chunk; keep the current one
     next_ = static_cast<unsigned char*>(k.p) + bytes;
     left_ = k.size - bytes;
     return static_cast<T*>(k.p);
